@@ -165,8 +165,10 @@ int64_t dpg_boundary_points(const dpg_ctx *ctx, double *xyz, int64_t cap);
 /* Element DPG work on the GPU, all in FP64 (Sec. 2 and Sec. 1.2): Gram
  * matrix G of the adjoint graph norm, B and loads l; Cholesky G = L L^H;
  * W = L^-1 [B l]; K = W^H W; static condensation of the fields,
- * S = K_tt - K_tf K_ff^-1 K_ft and s likewise.  Errors: DPG_ENOTPD names
- * the element. */
+ * S = K_tt - K_tf K_ff^-1 K_ft and s likewise.  Elements with the same wave
+ * speed and the same faces on Gamma have equal matrices, which are computed
+ * and stored once per class of such elements; the loads are computed for
+ * every element.  Errors: DPG_ENOTPD names the (first such) element. */
 int dpg_assemble(dpg_ctx *ctx);
 
 /* Multigrid hierarchy on the GPU (Sec. 3), FP64: per level, macro
@@ -175,7 +177,9 @@ int dpg_assemble(dpg_ctx *ctx);
  * of the coarser mesh itself, by the element stage of dpg_assemble at that
  * mesh size), vertex-patch blocks factored and inverted (the inverse kept in
  * FP64, plus an FP32 copy in mixed mode); dense Cholesky of the coarsest
- * operator.  Errors: DPG_ENOTPD names the coarse element, patch or level. */
+ * operator.  Coarse elements with equal children, and patches with equal
+ * coarse elements around their vertex, are formed and stored once.  Errors:
+ * DPG_ENOTPD names the coarse element, patch or level. */
 int dpg_build_hierarchy(dpg_ctx *ctx);
 
 /* Replaces the assembled loads by new right-hand sides for the same operator

@@ -1,6 +1,7 @@
 // C ABI of libdpgmg (include/dpgmg.h): setup, element stage, hierarchy,
 // preconditioned CG with the DPG-MG V-cycle, exports.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstring>
 #include <map>
@@ -172,14 +173,16 @@ bool source_elements(const dpg_ctx *c, std::vector<int32_t> &list) {
 
 // Throws DPG_ENOTPD for the first item whose Cholesky met a non-positive
 // pivot (info[i] = j + 1 for pivot j of item i).
-void check_infos(const int *info, int64_t count, hipStream_t s, const char *what) {
+// With rep (null: the identity), item i is reported as number rep[i].
+void check_infos(const int *info, int64_t count, hipStream_t s, const char *what,
+                 const std::vector<int32_t> *rep = nullptr) {
   if (count <= 0) return;
   std::vector<int> h(count);
   HIP_OK(hipMemcpyAsync(h.data(), info, count * sizeof(int), hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
   for (int64_t i = 0; i < count; ++i)
     if (h[i] != 0)
-      throw DpgError(DPG_ENOTPD, std::string(what) + " " + std::to_string(i) +
+      throw DpgError(DPG_ENOTPD, std::string(what) + " " + std::to_string(rep ? (*rep)[i] : i) +
                                      ": Cholesky pivot " + std::to_string(h[i] - 1) +
                                      " is not positive");
 }
@@ -188,6 +191,123 @@ void check_infos(const int *info, int64_t count, hipStream_t s, const char *what
 void stream_wait(hipStream_t a, hipStream_t b, hipEvent_t ev) {
   HIP_OK(hipEventRecord(ev, a));
   HIP_OK(hipStreamWaitEvent(b, ev, 0));
+}
+
+// Per unknown, the positions of edofs ([nel][n_tr], -1 absent) that hold it,
+// ascending.
+void holders(const std::vector<int32_t> &edofs, int64_t n, std::vector<int32_t> &ptr,
+             std::vector<int32_t> &ent) {
+  ptr.assign(n + 1, 0);
+  for (int32_t t : edofs)
+    if (t >= 0) ptr[t + 1]++;
+  for (int64_t t = 0; t < n; ++t) ptr[t + 1] += ptr[t];
+  ent.assign(ptr[n], 0);
+  std::vector<int32_t> fill(ptr.begin(), ptr.end() - 1);
+  for (size_t k = 0; k < edofs.size(); ++k)
+    if (edofs[k] >= 0) ent[fill[edofs[k]]++] = (int32_t)k;
+}
+
+// ---- classes of equal elements, blocks and patches ------------------------------------
+
+// Classes of count members by key(i, k) (k: 8 numbers); same(i, j) confirms
+// that member i has the layout of the class's first member j.  With more than
+// three quarters as many classes as members, every member is its own class
+// (the element loads then stay columns of the element's own solves).
+template <class Key, class Same>
+void build_classes(Classes &cl, int count, Key &&key, Same &&same) {
+  std::map<std::array<int64_t, 8>, int32_t> id;
+  cl.of_h.resize(count);
+  cl.rep_h.clear();
+  for (int i = 0; i < count; ++i) {
+    std::array<int64_t, 8> k{};
+    key(i, k);
+    auto it = id.find(k);
+    if (it == id.end() || !same(i, cl.rep_h[it->second])) {
+      cl.of_h[i] = (int32_t)cl.rep_h.size();
+      if (it == id.end()) id.emplace(k, cl.of_h[i]);
+      cl.rep_h.push_back(i);
+    } else {
+      cl.of_h[i] = it->second;
+    }
+  }
+  if (4 * (int64_t)cl.rep_h.size() > 3 * (int64_t)count) {
+    cl.rep_h.resize(count);
+    for (int i = 0; i < count; ++i) cl.of_h[i] = cl.rep_h[i] = i;
+  }
+  cl.n = (int)cl.rep_h.size();
+}
+
+// Classes of every level (see Classes): the finest elements (with stored
+// coarse operators the elements of every mesh) by wave speed and faces on
+// Gamma; macro blocks by the classes of their eight children (an order
+// level's blocks are its elements); the coarser level's Galerkin elements are
+// the blocks; patches by the classes of the blocks around the vertex.
+void classify_levels(dpg_ctx *c) {
+  const bool store = c->opt.flags & DPG_STORE_COARSE;
+  for (int l = c->L; l >= 0; --l) {
+    LevelData &f = c->lv[l];
+    const int N = f.N, r = c->N / N;
+    if (l == c->L || store) {
+      build_classes(f.ec, f.nel, [&](int e, std::array<int64_t, 8> &k) {
+        const int i = e % N, j = (e / N) % N, z = e / (N * N);
+        const double ce = c->c_h[(int64_t)i * r + (int64_t)c->N * (j * r + (int64_t)c->N * z * r)];
+        std::memcpy(&k[0], &ce, sizeof(ce));
+        k[1] = (i == 0) | (i == N - 1) << 1 | (j == 0) << 2 | (j == N - 1) << 3 | (z == 0) << 4 |
+               (z == N - 1) << 5;
+      }, [](int, int) { return true; });
+    } else {
+      f.ec.n = c->lv[l + 1].bc.n;
+      f.ec.of_h = c->lv[l + 1].bc.of_h;
+      f.ec.rep_h = c->lv[l + 1].bc.rep_h;
+    }
+    if (l == 0) break;
+    const int Nc = f.mc.Nc;
+    if (f.order) {
+      f.bc.n = f.ec.n;
+      f.bc.of_h = f.ec.of_h;
+      f.bc.rep_h = f.ec.rep_h;
+    } else {
+      const auto &pres = f.mc.blkB_present;
+      const auto &ptr = f.mc.blkB_ptr;
+      build_classes(f.bc, f.nblk, [&](int b, std::array<int64_t, 8> &k) {
+        const int i = b % Nc, j = (b / Nc) % Nc, z = b / (Nc * Nc);
+        for (int ch = 0; ch < 8; ++ch)
+          k[ch] = f.ec.of_h[(2 * i + (ch & 1)) + N * ((2 * j + ((ch >> 1) & 1)) + N * (2 * z + (ch >> 2)))];
+      }, [&](int a, int b) {
+        return ptr[a + 1] - ptr[a] == ptr[b + 1] - ptr[b] &&
+               std::equal(pres.begin() + ptr[a], pres.begin() + ptr[a + 1], pres.begin() + ptr[b]);
+      });
+    }
+    const auto &pp = f.mc.patch_ptr;
+    const auto &slot = f.mc.patch_slot;
+    build_classes(f.pc, (int)pp.size() - 1, [&](int v, std::array<int64_t, 8> &k) {
+      const int vx = v % (Nc + 1), vy = (v / (Nc + 1)) % (Nc + 1), vz = v / ((Nc + 1) * (Nc + 1));
+      for (int ch = 0; ch < 8; ++ch) {
+        const int i = vx - 1 + (ch & 1), j = vy - 1 + ((ch >> 1) & 1), z = vz - 1 + (ch >> 2);
+        const bool in = i >= 0 && j >= 0 && z >= 0 && i < Nc && j < Nc && z < Nc;
+        k[ch] = in ? f.bc.of_h[i + Nc * (j + Nc * z)] : -1;
+      }
+    }, [&](int a, int b) {
+      return pp[a + 1] - pp[a] == pp[b + 1] - pp[b] &&
+             std::memcmp(&slot[8 * pp[a]], &slot[8 * pp[b]],
+                         (size_t)(pp[a + 1] - pp[a]) * 8 * sizeof(int32_t)) == 0;
+    });
+  }
+  std::vector<int32_t> all;   // one upload for every level
+  for (LevelData &f : c->lv)
+    for (Classes *k : {&f.ec, &f.bc, &f.pc}) {
+      all.insert(all.end(), k->of_h.begin(), k->of_h.end());
+      all.insert(all.end(), k->rep_h.begin(), k->rep_h.end());
+    }
+  c->classes.upload(all, &c->bud, c->stream);
+  const int32_t *p = c->classes.p;
+  for (LevelData &f : c->lv)
+    for (Classes *k : {&f.ec, &f.bc, &f.pc}) {
+      k->of = p;
+      k->rep = p + k->of_h.size();
+      p = k->rep + k->rep_h.size();
+    }
+  HIP_OK(hipStreamSynchronize(c->stream));
 }
 
 // ---- element stage -----------------------------------------------------------------
@@ -254,6 +374,218 @@ struct IndicatorArgs {
   double *eta2;
 };
 
+// Member ranges of the element classes: mlist holds the elements sorted by
+// class (and index), cls_ptr the range of each class.
+void members_of(const Classes &ec, std::vector<int32_t> &mlist, std::vector<int32_t> &cls_ptr) {
+  cls_ptr.assign(ec.n + 1, 0);
+  for (int32_t k : ec.of_h) ++cls_ptr[k + 1];
+  for (int k = 0; k < ec.n; ++k) cls_ptr[k + 1] += cls_ptr[k];
+  mlist.resize(ec.of_h.size());
+  std::vector<int32_t> fill(cls_ptr.begin(), cls_ptr.end() - 1);
+  for (size_t e = 0; e < ec.of_h.size(); ++e) mlist[fill[ec.of_h[e]]++] = (int32_t)e;
+}
+
+// Pieces of at most about 1 GB of load columns (nr per element) for the
+// class chunks of the plan.
+void plan_load_pieces(dpg_ctx *c, const Classes &ec, int nr) {
+  ElemPlan &P = c->ep;
+  if (P.pieces_nr == nr && P.pieces_C == P.C) return;
+  const int nt = c->n_test, nf = c->n_field, ntr = c->n_tr, m = c->m, C = P.C;
+  Budget *bd = &c->bud;
+  const hipStream_t s = c->stream;
+  std::vector<int32_t> mlist, ptr;
+  members_of(ec, mlist, ptr);
+  const int most = (int)std::max<int64_t>(1, std::min<int64_t>(62500000LL / ((int64_t)nt * nr), 65535));
+  HIP_OK(hipStreamSynchronize(s));   // the items of earlier pieces may still be read
+  P.pieces.clear();
+  P.mlist.upload(mlist, bd, s);
+  int cap = 0;
+  for (int e0 = 0, k = 0; e0 < ec.n; e0 += C, ++k) {
+    const int cnt = std::min(C, ec.n - e0);
+    for (int j0 = ptr[e0]; j0 < ptr[e0 + cnt]; j0 += most) {
+      LoadPiece L;
+      L.chunk = k;
+      L.j0 = j0;
+      L.cnt = std::min(most, ptr[e0 + cnt] - j0);
+      cap = std::max(cap, L.cnt);
+      std::vector<TrsmItem> tl(cnt), tk(cnt);
+      std::vector<GemmItem> gl(cnt), gs(cnt), gr(cnt);
+      for (int i = 0; i < cnt; ++i) {
+        const int a = std::max(ptr[e0 + i], j0), b = std::min(ptr[e0 + i + 1], j0 + L.cnt);
+        const int nc = std::max(0, b - a) * nr;
+        const int64_t col = nc > 0 ? (int64_t)(a - j0) * nr : 0;
+        const int64_t oG = (int64_t)i * nt * nt, oB = (int64_t)i * nt * m, oK = (int64_t)i * m * m;
+        L.max_cols = std::max(L.max_cols, nc);
+        tl[i] = {oG, col * nt, nt, nc, nt, nt};                              // W_l = L^-1 l
+        gl[i] = {oB, col * nt, col * m, m, nc, nt, nt, nt, m};               // W_B^H W_l
+        tk[i] = {oK, col * m, nf, nc, m, m};                                 // Y_b = L_f^-1 b_f
+        gs[i] = {oK + (int64_t)nf * m, col * m, col * m + nf, ntr, nc, nf, m, m, m};
+        gr[i] = {oB, col * m, col * nt, nt, nc, m, nt, m, nt};               // W_l - W_B X
+      }
+      L.tl.upload(tl, bd, s);
+      L.tk.upload(tk, bd, s);
+      L.gl.upload(gl, bd, s);
+      L.gs.upload(gs, bd, s);
+      L.gr.upload(gr, bd, s);
+      HIP_OK(hipStreamSynchronize(s));
+      P.pieces.push_back(std::move(L));
+    }
+  }
+  for (int k = 0; k < P.ns; ++k) {
+    grow(P.LB[k], (int64_t)cap * nr * nt, bd);
+    grow(P.KL[k], (int64_t)cap * nr * m, bd);
+  }
+  P.pieces_nr = nr;
+  P.pieces_C = C;
+}
+
+// The element stage by classes of equal elements: Gram matrix, B, Cholesky,
+// W = L^-1 B, K = W^H W and the condensation of its field block once per class
+// (27 classes of 4096 elements for a uniform medium at 16^3), and the load
+// columns of all elements of a class beside them by the same solves and
+// products, so that a column goes through the operations it would go through
+// as one of the columns of its own element's [B | l].  Bound by the latency of
+// the factorisation's 64-wide steps where classes are few.  16^3, p = 3, one
+// load: whole step (elements, hierarchy, solve) 122 ms element by element, 60 ms
+// by classes; error indicator with fields at 12^3 14.6 -> 2.8 ms.  With ind, the residuals of the
+// elements of a class are formed together (the error indicator).
+void element_stage_classes(dpg_ctx *c, int l, bool write_matrices, const IndicatorArgs *ind) {
+  const bool fine = l == c->L;
+  LevelData &f = c->lv[l];
+  const int nr = ind ? ind->nr : fine ? c->nrhs : 0;
+  if (ind && (!fine || ind->nr < 1 || ind->nr > c->nrhs))
+    throw DpgError(DPG_EINVAL, "bad indicator columns");
+  const Classes &ec = f.ec;
+  plan_elements(c, ec.n, 0);
+  ElemPlan &P = c->ep;
+  const int nt = c->n_test, nf = c->n_field, ntr = c->n_tr, m = c->m;
+  const int C = P.C, ncls = ec.n, nel = f.nel;
+  if (nr > 0) {
+    plan_load_pieces(c, ec, nr);
+    if (ind)
+      for (int k = 0; k < P.ns; ++k) grow(P.X[k], P.KL[k].n, &c->bud);
+  }
+  for (int k = 0; k < P.ns; ++k) grow(P.wkK[k], dense_work_size(C, nf), &c->bud);
+  const double *kap = fine ? c->kappa.p : f.kappa.p, *Zel = fine ? c->Zel.p : f.Zel.p;
+  const ElemGeom g{f.N, c->side / f.N, c->omega, 1.0, {c->org[0], c->org[1], c->org[2]}, ec.rep};
+  ElemGeom gl = g;
+  gl.elist = P.mlist.p;
+  const int NS = c->prof.on ? 1 : P.ns;
+  const hipStream_t xs[4] = {c->stream, c->aux, c->paux[0], c->paux[1]};
+  const DenseProf dG{&c->prof, nullptr, nt, nullptr, m}, dK{&c->prof, nullptr, nf, nullptr, ntr};
+  const hipEvent_t xj[4] = {nullptr, c->ev_join, c->ev_pjoin[0], c->ev_pjoin[1]};
+  for (int k = 1; k < NS; ++k) stream_wait(c->stream, xs[k], c->ev_fork);
+  for (int e0 = 0, k = 0; e0 < ncls; e0 += C, ++k) {
+    const int cnt = std::min(C, ncls - e0), u = k % NS;
+    const hipStream_t s = xs[u];
+    double2 *G = P.G[u].p, *BL = P.BL[u].p, *K = P.K[u].p, *wk = P.wk[u].p, *wkK = P.wkK[u].p;
+    {
+      ProfScope ps(&c->prof, DPG_K_GRAM, 0, s);
+      launch_gram(c->tables.p, c->testd.p, nt, g, kap, e0, cnt, G, s);
+    }
+    {
+      ProfScope ps(&c->prof, DPG_K_BMAT, 0, s);
+      launch_bmat(c->tables.p, c->testd.p, c->triald.p, nt, m, g, kap, Zel, e0, cnt, BL,
+                  (int64_t)nt * m, s);
+    }
+    {
+      ProfScope ps(&c->prof, DPG_K_POTRF, cnt * f_potrf(nt), s);
+      potrf_batched(G, P.pG.p, cnt, P.info.p + e0, nt, wk, s, &dG);
+    }
+    {
+      ProfScope ps(&c->prof, DPG_K_TRSM, cnt * f_trsm(nt, m), s);
+      trsm_batched(G, BL, P.tG.p, cnt, nt, m, false, wk, true, s, &dG);
+    }
+    {
+      ProfScope ps(&c->prof, DPG_K_GEMM, cnt * f_herk(m, nt), s);
+      gemm_batched(OP_C, OP_N, mk(1, 0), BL, BL, mk(0, 0), K, P.gK.p, cnt, m, m, s, GEMM_HERM);
+    }
+    {
+      ProfScope ps(&c->prof, DPG_K_POTRF, cnt * f_potrf(nf), s);
+      potrf_batched(K, P.pK.p, cnt, P.info.p + ncls + e0, nf, wkK, s, &dK);
+    }
+    {
+      ProfScope ps(&c->prof, DPG_K_TRSM, cnt * f_trsm(nf, ntr), s);
+      trsm_batched(K, K, P.tK.p, cnt, nf, ntr, false, wkK, true, s, &dK);
+    }
+    if (!ind) {
+      {
+        ProfScope ps(&c->prof, DPG_K_GEMM, cnt * f_herk(ntr, nf), s);
+        gemm_batched(OP_C, OP_N, mk(-1, 0), K, K, mk(1, 0), K, P.gS.p, cnt, ntr, ntr, s, GEMM_HERM);
+      }
+      if (write_matrices) {
+        launch_copy_sub(K, (int64_t)m * m, m, nf, nf, ntr, ntr, f.E.p + (int64_t)e0 * ntr * ntr,
+                        (int64_t)ntr * ntr, ntr, cnt, s);
+        if (fine && c->keep_recovery) {   // L = chol(K_ff) and Y_t = L^-1 K_ft
+          launch_copy_sub(K, (int64_t)m * m, m, 0, 0, nf, nf, c->rec_L.p + (int64_t)e0 * nf * nf,
+                          (int64_t)nf * nf, nf, cnt, s);
+          launch_copy_sub(K, (int64_t)m * m, m, 0, nf, nf, ntr,
+                          c->rec_Y.p + (int64_t)e0 * nf * ntr, (int64_t)nf * ntr, nf, cnt, s);
+        }
+      }
+    }
+    for (const LoadPiece &L : P.pieces) {
+      if (nr == 0 || L.chunk != k) continue;
+      double2 *LB = P.LB[u].p, *KL = P.KL[u].p;
+      const double cols = (double)L.cnt * nr;
+      {
+        ProfScope ps(&c->prof, DPG_K_LOAD, 0, s);
+        launch_load(c->tables.p, nt, 0, gl, Zel, c->ld.p, c->src.p, c->u0q.p, nr, L.j0, L.cnt, LB,
+                    (int64_t)nt * nr, s);
+      }
+      const DenseProf none{};
+      {
+        ProfScope ps(&c->prof, DPG_K_OTHER, 0, s);
+        trsm_batched(G, LB, L.tl.p, cnt, nt, L.max_cols, false, wk, true, s, &none);
+      }
+      {
+        ProfScope ps(&c->prof, DPG_K_GEMM, f_gemm(m, cols, nt), s);
+        gemm_batched(OP_C, OP_N, mk(1, 0), BL, LB, mk(0, 0), KL, L.gl.p, cnt, m, L.max_cols, s);
+      }
+      {
+        ProfScope ps(&c->prof, DPG_K_OTHER, 0, s);
+        trsm_batched(K, KL, L.tk.p, cnt, nf, L.max_cols, false, wkK, true, s, &none);
+      }
+      if (ind) {
+        {
+          ProfScope ps(&c->prof, DPG_K_OTHER, 0, s);
+          launch_indicator_x(K, (int64_t)m * m, m, KL, (int64_t)m * nr, nf, ntr, nr, f.edofs.p,
+                             P.mlist.p, ec.of, e0, L.j0, L.cnt, ind->x, f.num.n, P.X[u].p, s);
+        }
+        {
+          ProfScope ps(&c->prof, DPG_K_GEMM, f_gemm(nt, cols, m), s);
+          gemm_batched(OP_N, OP_N, mk(-1, 0), BL, P.X[u].p, mk(1, 0), LB, L.gr.p, cnt, nt,
+                       L.max_cols, s);
+        }
+        ProfScope ps(&c->prof, DPG_K_OTHER, 0, s);
+        launch_colnorm2(LB, (int64_t)nt * nr, nt, nt, 0, nr, P.mlist.p, L.j0, L.cnt, nel,
+                        ind->eta2, s);
+        continue;
+      }
+      {
+        ProfScope ps(&c->prof, DPG_K_GEMM, f_gemm(ntr, cols, nf), s);
+        gemm_batched(OP_C, OP_N, mk(-1, 0), K, KL, mk(1, 0), KL, L.gs.p, cnt, ntr, L.max_cols, s);
+      }
+      for (int r = 0; r < nr; ++r)
+        launch_copy_sub(KL, (int64_t)m * nr, m, nf, r, ntr, 1,
+                        c->s_elem.p + (int64_t)r * nel * ntr, ntr, ntr, L.cnt, s,
+                        P.mlist.p + L.j0);
+      if (c->keep_recovery)             // Y_b = L^-1 b_f
+        launch_copy_sub(KL, (int64_t)m * nr, m, 0, 0, nf, nr, c->rec_Yb.p, (int64_t)nf * nr, nf,
+                        L.cnt, s, P.mlist.p + L.j0);
+    }
+  }
+  for (int k = 1; k < NS; ++k) stream_wait(xs[k], c->stream, xj[k]);
+  if (fine && !ind)
+    for (int r = 0; r < nr; ++r)
+      launch_assemble_vec(f.num.n, c->asm_ptr.p, c->asm_ent.p, c->s_elem.p + (int64_t)r * nel * ntr,
+                          0, c->s_asm.p + (int64_t)r * f.num.n, c->stream);
+  check_infos(P.info.p, ncls, c->stream,
+              fine ? "element Gram matrix" : "coarse-mesh element Gram matrix", &ec.rep_h);
+  check_infos(P.info.p + ncls, ncls, c->stream,
+              fine ? "element field block" : "coarse-mesh element field block", &ec.rep_h);
+}
+
 // Per element (Sec. 1.2): Gram matrix G and [B | l]; G = L L^H;
 // W = L^-1 [B | l]; K = W^H W; static condensation of the field block of K.
 // Chunks of elements are dealt round-robin to four streams.  Level L (the
@@ -271,6 +603,10 @@ void element_stage(dpg_ctx *c, int l, bool write_matrices, const IndicatorArgs *
                    const int32_t *elist = nullptr, int nlist = 0) {
   const bool fine = l == c->L;
   LevelData &f = c->lv[l];
+  if (f.ec.shared() && !elist) {
+    element_stage_classes(c, l, write_matrices, ind);
+    return;
+  }
   const int nr = fine ? c->nrhs : 0;
   plan_elements(c, f.nel, nr);
   ElemPlan &P = c->ep;
@@ -344,15 +680,15 @@ void element_stage(dpg_ctx *c, int l, bool write_matrices, const IndicatorArgs *
       const int64_t nT = f.num.n;
       {
         ProfScope ps(&c->prof, DPG_K_OTHER, 0, s);
-        launch_indicator_x(K, (int64_t)mp * mp, mp, nf, ntr, q, f.edofs.p + (int64_t)e0 * ntr, cnt,
-                           ind->x, nT, P.X[u].p, s);
+        launch_indicator_x(K, (int64_t)mp * mp, mp, K + (int64_t)m * mp, (int64_t)mp * mp, nf, ntr,
+                           q, f.edofs.p, nullptr, nullptr, 0, e0, cnt, ind->x, nT, P.X[u].p, s);
       }
       {
         ProfScope ps(&c->prof, DPG_K_GEMM, cnt * f_gemm(nt, q, m), s);
         gemm_batched(OP_N, OP_N, mk(-1, 0), BL, P.X[u].p, mk(1, 0), BL, P.gR.p, cnt, nt, q, s);
       }
       ProfScope ps(&c->prof, DPG_K_OTHER, 0, s);
-      launch_colnorm2(BL, (int64_t)nt * mp, nt, nt, m, q, e0, cnt, nel, ind->eta2, s);
+      launch_colnorm2(BL, (int64_t)nt * mp, nt, nt, m, q, nullptr, e0, cnt, nel, ind->eta2, s);
       continue;
     }
     {
@@ -557,14 +893,15 @@ void load_by_maps(dpg_ctx *c, const std::vector<int32_t> &list, const int32_t *l
 // order level, the condensed blocks otherwise.
 const double2 *mfull(const LevelData &f) { return f.order ? f.E.p : f.Mfull.p; }
 
-// Chunk size of the macro blocks of a level and the shared workspace sizes.
+// Chunk size of the macro block classes of a level and the shared workspace sizes.
 int macro_chunk(dpg_ctx *c, const LevelData &f) {
   const int ntr = f.ntr_c, nBf = f.nBf, nI = f.nI, nT = nBf + nI;
   const int64_t per = 16LL * ((int64_t)nT * nT + (int64_t)nI * nI + (int64_t)nBf * ntr);
   const int64_t cmax = std::max<int64_t>(1, std::min<int64_t>(2500000000LL / per, 65535));
-  if (f.nblk <= cmax) return f.nblk;
-  const int64_t pairs = (f.nblk + 2 * cmax - 1) / (2 * cmax);   // an even number of chunks
-  return (int)((f.nblk + 2 * pairs - 1) / (2 * pairs));
+  const int nb = f.bc.n;
+  if (nb <= cmax) return nb;
+  const int64_t pairs = (nb + 2 * cmax - 1) / (2 * cmax);   // an even number of chunks
+  return (int)((nb + 2 * pairs - 1) / (2 * pairs));
 }
 
 void plan_macro(dpg_ctx *c, int l) {
@@ -574,7 +911,7 @@ void plan_macro(dpg_ctx *c, int l) {
   const hipStream_t s = c->stream;
   Budget *bd = &c->bud;
   // ntr: element size of the coarser level (the Galerkin products' output)
-  const int ntr = f.ntr_c, nBf = f.nBf, nI = f.nI, nT = nBf + nI, nblk = f.nblk;
+  const int ntr = f.ntr_c, nBf = f.nBf, nI = f.nI, nT = nBf + nI, nblk = f.nblk, ncls = f.bc.n;
   const bool ord = f.order;   // order level: the blocks are the element matrices
   const int CB = macro_chunk(c, f);
   std::vector<double2> ploc_h(f.P.local.size());
@@ -622,27 +959,27 @@ void plan_macro(dpg_ctx *c, int l) {
   std::vector<int64_t> soff(nblk), moff(nblk);
   std::vector<int32_t> sld(nblk, nBf);
   for (int b = 0; b < nblk; ++b) {
-    soff[b] = (int64_t)b * nBf * nBf;
+    soff[b] = (int64_t)f.bc.of_h[b] * nBf * nBf;
     moff[b] = f.mc.blkB_ptr[b];
   }
   P.soff.upload(soff, bd, s);
   P.moff.upload(moff, bd, s);
   P.sld.upload(sld, bd, s);
   P.map.upload(f.mc.blkB_present, bd, s);
-  P.info.ensure(nblk, bd);
+  P.info.ensure(ncls, bd);
   // level outputs and the shared workspaces (the finest level has the most blocks)
   LevelData &cl = c->lv[l - 1];
-  cl.E.ensure((int64_t)nblk * ntr * ntr, bd);
+  cl.E.ensure((int64_t)cl.ec.n * ntr * ntr, bd);
   if (!ord) {
-    f.Mfull.ensure((int64_t)nblk * nBf * nBf, bd);
-    f.Tinv.ensure((int64_t)nblk * nI * nI, bd);
-    f.WH.ensure((int64_t)nblk * nBf * nI, bd);
+    f.Mfull.ensure((int64_t)ncls * nBf * nBf, bd);
+    f.Tinv.ensure((int64_t)ncls * nI * nI, bd);
+    f.WH.ensure((int64_t)ncls * nBf * nI, bd);
   }
   if (c->opt.precision == DPG_MIXED && l < c->L && !ord) {
     f.Tinv32.ensure(f.Tinv.n, bd);
     f.WH32.ensure(f.WH.n, bd);
   }
-  for (int h = 0; h < (nblk > CB ? 2 : 1); ++h) {
+  for (int h = 0; h < (ncls > CB ? 2 : 1); ++h) {
     if (!ord && c->mT[h].n < (int64_t)CB * nT * nT) c->mT[h].alloc((int64_t)CB * nT * nT, bd);
     if (c->mLinv[h].n < (int64_t)CB * nI * nI) c->mLinv[h].alloc((int64_t)CB * nI * nI, bd);
     if (c->mX[h].n < (int64_t)CB * nBf * ntr) c->mX[h].alloc((int64_t)CB * nBf * ntr, bd);
@@ -655,13 +992,13 @@ void plan_macro(dpg_ctx *c, int l) {
 
 // Macro condensation of level l (Sec. 3) and, unless the coarse operators are
 // stored (assembled on their own meshes), the Galerkin element matrices of
-// level l - 1.  Chunks of coarse elements alternate between the two streams
+// level l - 1.  Chunks of block classes alternate between the two streams
 // (each with its own workspaces); on return the main stream has everything.
 void build_macro_level(dpg_ctx *c, int l) {
   LevelData &f = c->lv[l];
   LevelData &cl = c->lv[l - 1];
   MacroPlan &P = f.mp;
-  const int ntr = f.ntr_c, nBf = f.nBf, nI = f.nI, nT = nBf + nI, nblk = f.nblk, CB = P.CB;
+  const int ntr = f.ntr_c, nBf = f.nBf, nI = f.nI, nT = nBf + nI, nblk = f.bc.n, CB = P.CB;
   const bool two = nblk > CB;
   const bool one_stream = c->prof.on;   // profiled launches are timed alone
   const DenseProf dI{&c->prof, nullptr, nI, nullptr, nBf}, dL{&c->prof, nullptr, nI, nullptr, nI};
@@ -677,7 +1014,7 @@ void build_macro_level(dpg_ctx *c, int l) {
     } else {
     {
       ProfScope ps(&c->prof, DPG_K_MACRO_ASM, 0, s);
-      launch_macro_assemble(f.E.p, f.ntr, P.cmap.p, f.N, b0, cnt, nT, T, s);
+      launch_macro_assemble(f.E.p, f.ntr, f.ec.of, P.cmap.p, f.N, f.bc.rep, b0, cnt, nT, T, s);
     }
     {
       ProfScope ps(&c->prof, DPG_K_POTRF, cnt * f_potrf(nI), s);
@@ -745,12 +1082,14 @@ void plan_patches(dpg_ctx *c, int l) {
   if (P.ready) return;
   const hipStream_t s = c->stream;
   Budget *bd = &c->bud;
-  const int np = (int)f.mc.patch_ptr.size() - 1;
+  const int npatch = (int)f.mc.patch_ptr.size() - 1;
+  const int np = f.pc.n;   // classes: one factor and inverse each
   std::vector<int32_t> nv(np);
   int nv_max = 0;
   int64_t maxent = 0;
   for (int v = 0; v < np; ++v) {
-    nv[v] = (int32_t)(f.mc.patch_ptr[v + 1] - f.mc.patch_ptr[v]);
+    const int w = f.pc.rep_h[v];
+    nv[v] = (int32_t)(f.mc.patch_ptr[w + 1] - f.mc.patch_ptr[w]);
     nv_max = std::max(nv_max, (int)nv[v]);
     maxent = std::max<int64_t>(maxent, (int64_t)nv[v] * nv[v]);
   }
@@ -776,7 +1115,11 @@ void plan_patches(dpg_ctx *c, int l) {
       vcut[k] = v;
     }
   }
-  std::vector<int64_t> soff_all(np, 0);
+  std::vector<int64_t> soff_all(npatch, 0);   // by patch, set for the representatives
+  std::vector<int32_t> ld_all(npatch, 0);
+  std::vector<std::vector<int32_t>> members(rec ? np : 0);   // patches of each class
+  if (rec)
+    for (int v = 0; v < npatch; ++v) members[f.pc.of_h[v]].push_back(v);
   int maxcnt[4] = {0, 0, 0, 0};
   int64_t maxuse[4] = {0, 0, 0, 0};   // largest batch footprint of each part (entries)
   for (int half = 0; half < NP; ++half) {
@@ -808,7 +1151,8 @@ void plan_patches(dpg_ctx *c, int l) {
         pi[i] = {o, n, n};
         ti[i] = {o, o, n, n, n, n};
         gi[i] = {o, o, o, n, n, n, n, n, n};
-        soff_all[v0 + i] = o;
+        soff_all[f.pc.rep_h[v0 + i]] = o;
+        ld_all[f.pc.rep_h[v0 + i]] = n;
         o += (int64_t)n * n;
         B.fp += f_potrf(n);
         B.ft += f_trsm(n, n) / 3.0;   // identity right-hand side: L^-1 only
@@ -823,19 +1167,22 @@ void plan_patches(dpg_ctx *c, int l) {
       if (rec) {   // t_v = X_v x_v, y_v = X_v^H t_v on the local vectors of the patch set
         // nr columns, local vectors column by column (leading dimension nloc)
         const int64_t nloc = f.Sset.nloc;
-        std::vector<GemmItem> gyc((size_t)kMaxCols * cnt), gzc((size_t)kMaxCols * cnt);
-        for (int q = 1; q <= kMaxCols; ++q)
-          for (int i = 0; i < cnt; ++i) {
-            const int n = nn[i];
-            const int64_t lo = f.Sset.loc_off_h[v0 + i];
-            gyc[(size_t)(q - 1) * cnt + i] = {off[i], lo, lo, n, q, n, n, (int)nloc, (int)nloc};
-            gzc[(size_t)(q - 1) * cnt + i] = {off[i], lo, lo, n, q, n, n, (int)nloc, (int)nloc};
-          }
+        std::vector<GemmItem> gyc;
+        for (int q = 1; q <= kMaxCols; ++q) {
+          for (int i = 0; i < cnt; ++i)
+            for (int32_t v : members[v0 + i]) {
+              const int n = nn[i];
+              const int64_t lo = f.Sset.loc_off_h[v];
+              gyc.push_back({off[i], lo, lo, n, q, n, n, (int)nloc, (int)nloc});
+            }
+          if (q == 1) B.mcnt = (int)gyc.size();
+        }
+        const std::vector<GemmItem> gzc(gyc);
         B.gyc.upload(gyc, bd, s);
         B.gzc.upload(gzc, bd, s);
       }
       B.t0 = f.Sset.tile_off_h[v0];
-      B.t1 = (v0 + cnt < np) ? f.Sset.tile_off_h[v0 + cnt] : f.Sset.ntiles;
+      B.t1 = (v0 + cnt < np) ? f.Sset.tile_off_h[v0 + cnt] : f.Sset.ntiles;   // by class
       maxcnt[half] = std::max(maxcnt[half], cnt);
       maxuse[half] = std::max(maxuse[half], used);
       P.batches.push_back(std::move(B));
@@ -843,7 +1190,7 @@ void plan_patches(dpg_ctx *c, int l) {
     }
   }
   P.soff_all.upload(soff_all, bd, s);
-  P.ld_all.upload(nv, bd, s);
+  P.ld_all.upload(ld_all, bd, s);
   P.info.ensure(np, bd);
   if (rec) grow(c->ptmp, f.Sset.nloc, bd);
   for (int h = 0; h < NP; ++h) {
@@ -868,8 +1215,8 @@ void build_patches(dpg_ctx *c, int l, int half, hipStream_t s) {
     const DenseProf dp{&c->prof, B.hn.data(), 0, B.hn.data(), 0};
     {
       ProfScope ps(&c->prof, DPG_K_PATCH_GATHER, 0, s);
-      launch_patch_gather(mfull(f), f.nBf, f.mc.Nc, f.patch_ptr.p, f.patch_slot.p, B.v0, B.cnt,
-                          B.nmax, B.off.p, S, s);
+      launch_patch_gather(mfull(f), f.bc.of, f.nBf, f.mc.Nc, f.patch_ptr.p, f.patch_slot.p,
+                          f.pc.rep, B.v0, B.cnt, B.nmax, B.off.p, S, s);
     }
     {
       ProfScope ps(&c->prof, DPG_K_POTRF, B.fp, s);
@@ -902,7 +1249,8 @@ void check_patches(dpg_ctx *c, int l) {
   for (PatchBatch &B : P.batches) {
     double2 *S = c->pS[B.half].p, *wk = c->pwk[B.half].p;
     launch_patch_gather_tiles(f.Mset.t64.p, f.Mset.ent_off.p, f.mpidx.p, f.nBf, f.mc.Nc,
-                              f.patch_ptr.p, f.patch_slot.p, B.v0, B.cnt, B.nmax, B.off.p, S, s);
+                              f.patch_ptr.p, f.patch_slot.p, f.pc.rep, B.v0, B.cnt, B.nmax,
+                              B.off.p, S, s);
     potrf_batched(S, B.pi.p, B.cnt, P.info.p + B.v0, B.nmax, wk, s);
   }
 }
@@ -915,7 +1263,8 @@ void check_patches(dpg_ctx *c, int l) {
 // X = L^-1, then S_v^-1 x_v = X^H (X x_v).  Every patch block is gathered and
 // factored once per smoothing step for all nr columns, and X multiplies an
 // n x nr panel (the local vectors stored column by column), so the
-// refactorisation is amortised over the right-hand sides of a block solve.
+// refactorisation is amortised over the right-hand sides of a block solve, and
+// a class of equal patches is factored once for all of them.
 // The same operator as the stored inverses, rounded differently; HBM traffic
 // and memory traded for matrix-core work.
 void smooth_recompute(dpg_ctx *c, int l, const double2 *x, double2 *y, const double2 *r,
@@ -934,8 +1283,8 @@ void smooth_recompute(dpg_ctx *c, int l, const double2 *x, double2 *y, const dou
     {
       PROF(DPG_K_PATCH_GATHER, 0);
       launch_patch_gather_tiles(f.Mset.t64.p, f.Mset.ent_off.p, f.mpidx.p, f.nBf, f.mc.Nc,
-                                f.patch_ptr.p, f.patch_slot.p, B.v0, B.cnt, B.nmax, B.off.p, S,
-                                s);
+                                f.patch_ptr.p, f.patch_slot.p, f.pc.rep, B.v0, B.cnt, B.nmax,
+                                B.off.p, S, s);
     }
     {
       PROF(DPG_K_POTRF, B.fp);
@@ -950,10 +1299,10 @@ void smooth_recompute(dpg_ctx *c, int l, const double2 *x, double2 *y, const dou
       trsm_batched(S, X, B.ti.p, B.cnt, B.nmax, B.nmax, true, wk, true, s, &dp);
     }
     PROF(DPG_K_GEMM, 0);
-    const GemmItem *gy = B.gyc.p + (int64_t)(nr - 1) * B.cnt;
-    const GemmItem *gz = B.gzc.p + (int64_t)(nr - 1) * B.cnt;
-    gemm_batched(OP_N, OP_N, mk(1, 0), X, xl, mk(0, 0), c->ptmp.p, gy, B.cnt, B.nmax, nr, s);
-    gemm_batched(OP_C, OP_N, mk(1, 0), X, c->ptmp.p, mk(0, 0), yl, gz, B.cnt, B.nmax, nr, s);
+    const GemmItem *gy = B.gyc.p + (int64_t)(nr - 1) * B.mcnt;
+    const GemmItem *gz = B.gzc.p + (int64_t)(nr - 1) * B.mcnt;
+    gemm_batched(OP_N, OP_N, mk(1, 0), X, xl, mk(0, 0), c->ptmp.p, gy, B.mcnt, B.nmax, nr, s);
+    gemm_batched(OP_C, OP_N, mk(1, 0), X, c->ptmp.p, mk(0, 0), yl, gz, B.mcnt, B.nmax, nr, s);
   }
   herm_scatter_cols(H, yl, y, r, mode, theta, nr, s);
 }
@@ -975,6 +1324,10 @@ void plan_coarsest(dpg_ctx *c) {
   c->zoff.upload(std::vector<int64_t>{0}, bd, s);
   c->znn.upload(std::vector<int32_t>{n0}, bd, s);
   c->zld.upload(std::vector<int32_t>{n0}, bd, s);
+  std::vector<int32_t> ptr, ent;
+  holders(z.edofs_h, n0, ptr, ent);
+  c->zptr.upload(ptr, bd, s);
+  c->zent.upload(ent, bd, s);
   c->zinfo.ensure(1, bd);
   HIP_OK(hipStreamSynchronize(s));
 }
@@ -984,7 +1337,7 @@ void build_coarsest(dpg_ctx *c) {
   LevelData &z = c->lv[0];
   const hipStream_t s = c->stream;
   const int n0 = (int)z.num.n;
-  launch_assemble_dense(z.E.p, z.ntr, z.edofs.p, z.nel, n0, c->T0.p, s);
+  launch_assemble_dense(z.E.p, z.ntr, z.ec.of, z.edofs.p, c->zptr.p, c->zent.p, n0, c->T0.p, s);
   HIP_OK(hipMemcpyAsync(c->zF.p, c->T0.p, (size_t)n0 * n0 * 16, hipMemcpyDeviceToDevice, s));
   const DenseProf dz{&c->prof, nullptr, n0, nullptr, n0};
   potrf_batched(c->zF.p, c->zpi.p, 1, c->zinfo.p, n0, c->zwk.p, s, &dz);
@@ -1044,9 +1397,9 @@ void build_hierarchy(dpg_ctx *c) {
   }
   for (int l = c->L; l >= 1; --l) {
     if (!c->lv[l].order)   // an order level factors no interior block
-      check_infos(c->lv[l].mp.info.p, c->lv[l].nblk, c->stream, "interior block of coarse element");
-    check_infos(c->lv[l].pp.info.p, (int64_t)c->lv[l].mc.patch_ptr.size() - 1, c->stream,
-                "vertex patch");
+      check_infos(c->lv[l].mp.info.p, c->lv[l].bc.n, c->stream, "interior block of coarse element",
+                  &c->lv[l].bc.rep_h);
+    check_infos(c->lv[l].pp.info.p, c->lv[l].pc.n, c->stream, "vertex patch", &c->lv[l].pc.rep_h);
   }
   check_infos(c->zinfo.p, 1, c->stream, "coarsest operator");
 }
@@ -1103,11 +1456,11 @@ void condense_level(const LevelData &g, const cplx_t<T> *WH, const cplx_t<T> *fu
   if (g.order) {
     HIP_OK(hipMemcpyAsync(out, full, g.nM * nr * sizeof(cplx_t<T>), hipMemcpyDeviceToDevice, s));
   } else if (nr == 1) {
-    launch_condense_local<T>(WH, g.nI, g.nBf, g.blkI.p, g.nblk, full, cc, s);
+    launch_condense_local<T>(WH, g.bc.of, g.nI, g.nBf, g.blkI.p, g.nblk, full, cc, s);
     launch_condense_reduce<T>(g.nM, g.macroB.p, g.cred_ptr.p, g.cred_ent.p, full, cc, out, s);
   } else {
-    launch_condense_blk<T>(WH, g.nI, g.nBf, g.blkI.p, g.nblk, g.nM, g.macroB.p, g.cred_ptr.p,
-                           g.cred_ent.p, full, cc, out, nr, s);
+    launch_condense_blk<T>(WH, g.bc.of, g.nI, g.nBf, g.blkI.p, g.nblk, g.nM, g.macroB.p,
+                           g.cred_ptr.p, g.cred_ent.p, full, cc, out, nr, s);
   }
 }
 
@@ -1120,11 +1473,11 @@ void expand_level(const LevelData &g, const cplx_t<T> *WH, const cplx_t<T> *Ti,
   if (g.order) {
     HIP_OK(hipMemcpyAsync(out, xm, g.nM * nr * sizeof(cplx_t<T>), hipMemcpyDeviceToDevice, s));
   } else if (nr == 1) {
-    launch_expand<T>(WH, Ti, g.nI, g.nBf, g.blkI.p, g.blkBm.p, g.nblk, full, xm, g.nM, g.macroB.p,
-                     out, s);
+    launch_expand<T>(WH, Ti, g.bc.of, g.nI, g.nBf, g.blkI.p, g.blkBm.p, g.nblk, full, xm, g.nM,
+                     g.macroB.p, out, s);
   } else {
-    launch_expand_blk<T>(WH, Ti, g.nI, g.nBf, g.blkI.p, g.blkBm.p, g.nblk, full, xm, g.nM,
-                         g.macroB.p, out, nr, s);
+    launch_expand_blk<T>(WH, Ti, g.bc.of, g.nI, g.nBf, g.blkI.p, g.blkBm.p, g.nblk, full, xm,
+                         g.nM, g.macroB.p, out, nr, s);
   }
 }
 
@@ -1746,6 +2099,14 @@ template <typename V> int64_t put(const std::vector<V> &v, void *out, int64_t ca
   if (out && cap > 0) std::memcpy(out, v.data(), sizeof(V) * std::min<int64_t>(cap, (int64_t)v.size()));
   return (int64_t)v.size();
 }
+// One matrix of sz entries per member from one per class.
+std::vector<double2> expand_classes(std::vector<double2> v, const Classes &cl, size_t sz) {
+  if (!cl.shared()) return v;
+  std::vector<double2> out(cl.of_h.size() * sz);
+  for (size_t e = 0; e < cl.of_h.size(); ++e)
+    std::copy_n(v.begin() + cl.of_h[e] * sz, sz, out.begin() + e * sz);
+  return out;
+}
 template <typename V> std::vector<int64_t> widen(const std::vector<V> &v) {
   return std::vector<int64_t>(v.begin(), v.end());
 }
@@ -1814,7 +2175,7 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
     c->side = mesh->side;
     for (int k = 0; k < 3; ++k) c->org[k] = mesh->origin[k];
     const int64_t nel = (int64_t)c->N * c->N * c->N;
-    c->c_h.assign(nel, 1.0);
+    c->c_h.assign(nel, 1.0);   // wave speed per element
     if (mat && mat->c)
       for (int64_t e = 0; e < nel; ++e) {
         if (!(mat->c[e] > 0)) throw DpgError(DPG_EINVAL, "wave speed must be positive");
@@ -1877,6 +2238,10 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
         f.P.build(f.mc, f.num, g.num, f.el);
       }
       f.nblk = f.mc.Nc * f.mc.Nc * f.mc.Nc;
+    }
+    classify_levels(c);
+    for (int l = 1; l <= c->L; ++l) {
+      LevelData &f = c->lv[l];
       f.nBf = f.mc.nBf;
       f.nI = f.mc.nI;
       f.nM = f.mc.nM;
@@ -1916,7 +2281,7 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
         for (int64_t k = f.mc.blkB_ptr[b]; k < f.mc.blkB_ptr[b + 1]; ++k)
           midx.push_back(f.mc.macro_of[f.mc.blkB[(int64_t)b * f.nBf + f.mc.blkB_present[k]]]);
       }
-      f.Mset.build(msz, midx, f.nM, !mixed || l == c->L, mixed, &c->bud, s);
+      f.Mset.build(msz, midx, f.nM, !mixed || l == c->L, mixed, &c->bud, s, &f.bc.of_h);
       const int np = (int)f.mc.patch_ptr.size() - 1;
       std::vector<int32_t> psz(np);
       for (int v = 0; v < np; ++v) psz[v] = (int32_t)(f.mc.patch_ptr[v + 1] - f.mc.patch_ptr[v]);
@@ -1926,11 +2291,11 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
           for (int64_t k = f.mc.blkB_ptr[b]; k < f.mc.blkB_ptr[b + 1]; ++k)
             pidx[(size_t)b * f.nBf + f.mc.blkB_present[k]] = (int32_t)(k - f.mc.blkB_ptr[b]);
         f.mpidx.upload(pidx, &c->bud, s);
-        f.Sset.build(psz, f.mc.patch_idx, f.nM, false, false, &c->bud, s);
+        f.Sset.build(psz, f.mc.patch_idx, f.nM, false, false, &c->bud, s, &f.pc.of_h);
         f.Sset.xl64.alloc(f.Sset.nloc, &c->bud);
         f.Sset.yl64.alloc(f.Sset.nloc, &c->bud);
       } else {
-        f.Sset.build(psz, f.mc.patch_idx, f.nM, !mixed, mixed, &c->bud, s);
+        f.Sset.build(psz, f.mc.patch_idx, f.nM, !mixed, mixed, &c->bud, s, &f.pc.of_h);
       }
       f.Mset.prof = &c->prof;
       f.Sset.prof = &c->prof;
@@ -1990,15 +2355,8 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
     // element load assembly lists of the finest mesh
     LevelData &top = c->lv[c->L];
     {
-      const int64_t n = top.num.n;
-      std::vector<int32_t> cnt(n + 1, 0), ent;
-      for (int32_t t : top.edofs_h)
-        if (t >= 0) cnt[t + 1]++;
-      for (int64_t t = 0; t < n; ++t) cnt[t + 1] += cnt[t];
-      ent.assign(cnt[n], 0);
-      std::vector<int32_t> fill(cnt.begin(), cnt.end() - 1);
-      for (size_t k = 0; k < top.edofs_h.size(); ++k)
-        if (top.edofs_h[k] >= 0) ent[fill[top.edofs_h[k]]++] = (int32_t)k;
+      std::vector<int32_t> cnt, ent;
+      holders(top.edofs_h, top.num.n, cnt, ent);
       c->asm_ptr.upload(cnt, &c->bud, s);
       c->asm_ent.upload(ent, &c->bud, s);
     }
@@ -2009,6 +2367,8 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
     c->partial.alloc(2 * kDotBlocks, &c->bud);
     c->sc.alloc(8, &c->bud);
     HIP_OK(hipHostMalloc((void **)&c->host_sc, 8 * sizeof(double), 0));
+    // (the bytes without sharing decide, so that what can be recovered does
+    // not depend on the medium)
     const int64_t rec_bytes = 16LL * top.nel * ((int64_t)c->n_field * c->n_field +
                                                 (int64_t)c->n_field * (c->n_tr + c->nrhs));
     c->keep_recovery = rec_bytes <= 4000000000LL;
@@ -2035,12 +2395,12 @@ int dpg_assemble(dpg_ctx *c) {
     if (c->released) throw DpgError(DPG_ESTATE, "setup data released");
     auto t0 = clk::now();
     LevelData &top = c->lv[c->L];
-    top.E.ensure((int64_t)top.nel * c->n_tr * c->n_tr, &c->bud);
+    top.E.ensure((int64_t)top.ec.n * c->n_tr * c->n_tr, &c->bud);
     c->s_elem.ensure(std::max<int64_t>(1, (int64_t)c->nrhs * top.nel * c->n_tr), &c->bud);
     c->s_asm.ensure(std::max<int64_t>(1, (int64_t)c->nrhs * top.num.n), &c->bud);
     if (c->keep_recovery) {
-      c->rec_L.ensure((int64_t)top.nel * c->n_field * c->n_field, &c->bud);
-      c->rec_Y.ensure((int64_t)top.nel * c->n_field * c->n_tr, &c->bud);
+      c->rec_L.ensure((int64_t)top.ec.n * c->n_field * c->n_field, &c->bud);
+      c->rec_Y.ensure((int64_t)top.ec.n * c->n_field * c->n_tr, &c->bud);
       c->rec_Yb.ensure(std::max<int64_t>(1, (int64_t)top.nel * c->n_field * c->nrhs), &c->bud);
     }
     element_stage(c, c->L, true);
@@ -2107,7 +2467,13 @@ int dpg_release_setup(dpg_ctx *c) {
         P.K[k].release();
         P.wk[k].release();
         P.X[k].release();
+        P.LB[k].release();
+        P.KL[k].release();
+        P.wkK[k].release();
       }
+      P.pieces.clear();
+      P.mlist.release();
+      P.pieces_nr = -1;
       P.mp = -1;
       P.nel = -1;
       P.gR_nr = 0;
@@ -2257,8 +2623,8 @@ int dpg_get_fields(dpg_ctx *c, const double *x, int nrhs, double *fields_out) {
     for (int k = 0; k < nrhs; ++k) {
       HIP_OK(hipMemcpyAsync(c->sB.p, x + 2 * nT * k, nT * 16,
                             dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
-      launch_fields(c->rec_L.p, c->rec_Y.p, c->rec_Yb.p, c->n_field, c->n_tr, c->nrhs, k, top.edofs.p,
-                    top.nel, c->sB.p, out.p, c->stream);
+      launch_fields(c->rec_L.p, c->rec_Y.p, c->rec_Yb.p, top.ec.of, c->n_field, c->n_tr, c->nrhs, k,
+                    top.edofs.p, top.nel, c->sB.p, out.p, c->stream);
       HIP_OK(hipMemcpyAsync(fields_out + 2 * nfe * k, out.p, nfe * 16,
                             dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, c->stream));
       HIP_OK(hipStreamSynchronize(c->stream));
@@ -2503,7 +2869,7 @@ int64_t dpg_export(const dpg_ctx *cc, int what, int level, void *out, int64_t ca
       case DPG_X_COARSE_E: {
         if (c->released) throw DpgError(DPG_ESTATE, "setup data released");
         if (!f.E.p) throw DpgError(DPG_ESTATE, "element matrices not computed yet");
-        rc = put(f.E.download(s), out, cap);
+        rc = put(expand_classes(f.E.download(s), f.ec, (size_t)f.ntr * f.ntr), out, cap);
         break;
       }
       case DPG_X_ELEM_RHS: {
@@ -2523,7 +2889,7 @@ int64_t dpg_export(const dpg_ctx *cc, int what, int level, void *out, int64_t ca
         std::vector<double2> full = f.order ? f.E.download(s) : f.Mfull.download(s), v;
         for (int b = 0; b < f.nblk; ++b) {
           const int64_t k0 = f.mc.blkB_ptr[b], n = f.mc.blkB_ptr[b + 1] - k0;
-          const double2 *Mb = full.data() + (int64_t)b * f.nBf * f.nBf;
+          const double2 *Mb = full.data() + (int64_t)f.bc.of_h[b] * f.nBf * f.nBf;
           for (int64_t j = 0; j < n; ++j)
             for (int64_t i = 0; i < n; ++i)
               v.push_back(Mb[f.mc.blkB_present[k0 + i] + (int64_t)f.mc.blkB_present[k0 + j] * f.nBf]);

@@ -395,6 +395,7 @@ __global__ __launch_bounds__(256) void k_csr_blk(int64_t nrows, int nr,
 // c_b[sl, k] = sum_i WH_b[sl, i] rc[I_b(i), k] for the KC columns of blockIdx.y.
 template <typename T>
 __global__ __launch_bounds__(256) void k_condense_local_blk(const cplx_t<T> *__restrict__ WH,
+                                                            const int32_t *__restrict__ bcls,
                                                             int nI, int nBf,
                                                             const int32_t *__restrict__ blkI,
                                                             const cplx_t<T> *__restrict__ rc,
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(256) void k_condense_local_blk(const cplx_t<T> *__r
     rI[i][k] = k < kc ? rc[(int64_t)blkI[(int64_t)b * nI + i] * nr + k0 + k] : czero<C>();
   }
   __syncthreads();
-  const C *W = WH + (int64_t)b * nBf * nI;
+  const C *W = WH + (int64_t)bcls[b] * nBf * nI;
   for (int sl = threadIdx.x; sl < nBf; sl += 256) {
     C acc[KC];
 #pragma unroll
@@ -460,7 +461,8 @@ __global__ __launch_bounds__(256) void k_scatter_macro_blk(int64_t nM, int nr,
 // one wave per interior unknown i, KC columns per workgroup.
 template <typename T>
 __global__ __launch_bounds__(256) void k_expand_blk(const cplx_t<T> *__restrict__ WH,
-                                                    const cplx_t<T> *__restrict__ Tinv, int nI,
+                                                    const cplx_t<T> *__restrict__ Tinv,
+                                                    const int32_t *__restrict__ bcls, int nI,
                                                     int nBf, const int32_t *__restrict__ blkI,
                                                     const int32_t *__restrict__ blkBm,
                                                     const cplx_t<T> *__restrict__ rc,
@@ -481,8 +483,8 @@ __global__ __launch_bounds__(256) void k_expand_blk(const cplx_t<T> *__restrict_
     rIs[i][k] = k < kc ? rc[(int64_t)blkI[(int64_t)b * nI + i] * nr + k0 + k] : czero<C>();
   }
   __syncthreads();
-  const C *W = WH + (int64_t)b * nBf * nI;
-  const C *Ti = Tinv + (int64_t)b * nI * nI;
+  const C *W = WH + (int64_t)bcls[b] * nBf * nI;
+  const C *Ti = Tinv + (int64_t)bcls[b] * nI * nI;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int i = wave; i < nI; i += 4) {
     C acc[KC];
@@ -785,13 +787,14 @@ void launch_csr_blk(int64_t nrows, const int64_t *ptr, const int32_t *col, const
 }
 
 template <typename T>
-void launch_condense_blk(const cplx_t<T> *WH, int nI, int nBf, const int32_t *blkI, int nblk,
-                         int64_t nM, const int64_t *macro_B, const int32_t *red_ptr,
+void launch_condense_blk(const cplx_t<T> *WH, const int32_t *bcls, int nI, int nBf,
+                         const int32_t *blkI, int nblk, int64_t nM, const int64_t *macro_B,
+                         const int32_t *red_ptr,
                          const int32_t *red_ent, const cplx_t<T> *rc, cplx_t<T> *c,
                          cplx_t<T> *rB, int nr, hipStream_t s) {
   if (nI > kBMaxI) throw DpgError(-1, "macro block too large");
-  hipLaunchKernelGGL((k_condense_local_blk<T>), dim3(nblk, cdiv(nr, KC)), dim3(256), 0, s, WH, nI,
-                     nBf, blkI, rc, c, nr);
+  hipLaunchKernelGGL((k_condense_local_blk<T>), dim3(nblk, cdiv(nr, KC)), dim3(256), 0, s, WH,
+                     bcls, nI, nBf, blkI, rc, c, nr);
   LAUNCH_OK();
   hipLaunchKernelGGL((k_condense_reduce_blk<T>), dim3(cdiv(nM * nr, 256)), dim3(256), 0, s, nM, nr,
                      macro_B, red_ptr, red_ent, rc, c, rB);
@@ -799,10 +802,10 @@ void launch_condense_blk(const cplx_t<T> *WH, int nI, int nBf, const int32_t *bl
 }
 
 template <typename T>
-void launch_expand_blk(const cplx_t<T> *WH, const cplx_t<T> *Tinv, int nI, int nBf,
-                       const int32_t *blkI, const int32_t *blkBm, int nblk, const cplx_t<T> *rc,
-                       const cplx_t<T> *eB, int64_t nM, const int64_t *macro_B, cplx_t<T> *ec,
-                       int nr, hipStream_t s) {
+void launch_expand_blk(const cplx_t<T> *WH, const cplx_t<T> *Tinv, const int32_t *bcls, int nI,
+                       int nBf, const int32_t *blkI, const int32_t *blkBm, int nblk,
+                       const cplx_t<T> *rc, const cplx_t<T> *eB, int64_t nM,
+                       const int64_t *macro_B, cplx_t<T> *ec, int nr, hipStream_t s) {
   // the boundary and interior values of KC columns of one macro block stay in
   // LDS; beyond 64 KB (order 4 in FP64) the kernel asks for more, up to the
   // 160 KB a gfx950 workgroup can hold
@@ -814,8 +817,8 @@ void launch_expand_blk(const cplx_t<T> *WH, const cplx_t<T> *Tinv, int nI, int n
   hipLaunchKernelGGL((k_scatter_macro_blk<T>), dim3(cdiv(nM * nr, 256)), dim3(256), 0, s, nM, nr,
                      macro_B, eB, ec);
   LAUNCH_OK();
-  hipLaunchKernelGGL((k_expand_blk<T>), dim3(nblk, cdiv(nr, KC)), dim3(256), lds, s, WH, Tinv, nI,
-                     nBf, blkI, blkBm, rc, eB, ec, nr);
+  hipLaunchKernelGGL((k_expand_blk<T>), dim3(nblk, cdiv(nr, KC)), dim3(256), lds, s, WH, Tinv,
+                     bcls, nI, nBf, blkI, blkBm, rc, eB, ec, nr);
   LAUNCH_OK();
 }
 
@@ -899,18 +902,21 @@ template void launch_csr_blk<double>(int64_t, const int64_t *, const int32_t *, 
                                      const double2 *, double2 *, int, int, hipStream_t);
 template void launch_csr_blk<float>(int64_t, const int64_t *, const int32_t *, const float *,
                                     const float2 *, float2 *, int, int, hipStream_t);
-template void launch_condense_blk<double>(const double2 *, int, int, const int32_t *, int, int64_t,
-                                          const int64_t *, const int32_t *, const int32_t *,
-                                          const double2 *, double2 *, double2 *, int, hipStream_t);
-template void launch_condense_blk<float>(const float2 *, int, int, const int32_t *, int, int64_t,
-                                         const int64_t *, const int32_t *, const int32_t *,
-                                         const float2 *, float2 *, float2 *, int, hipStream_t);
-template void launch_expand_blk<double>(const double2 *, const double2 *, int, int,
-                                        const int32_t *, const int32_t *, int, const double2 *,
-                                        const double2 *, int64_t, const int64_t *, double2 *, int,
-                                        hipStream_t);
-template void launch_expand_blk<float>(const float2 *, const float2 *, int, int, const int32_t *,
-                                       const int32_t *, int, const float2 *, const float2 *,
-                                       int64_t, const int64_t *, float2 *, int, hipStream_t);
+template void launch_condense_blk<double>(const double2 *, const int32_t *, int, int,
+                                          const int32_t *, int, int64_t, const int64_t *,
+                                          const int32_t *, const int32_t *, const double2 *,
+                                          double2 *, double2 *, int, hipStream_t);
+template void launch_condense_blk<float>(const float2 *, const int32_t *, int, int,
+                                         const int32_t *, int, int64_t, const int64_t *,
+                                         const int32_t *, const int32_t *, const float2 *,
+                                         float2 *, float2 *, int, hipStream_t);
+template void launch_expand_blk<double>(const double2 *, const double2 *, const int32_t *, int,
+                                        int, const int32_t *, const int32_t *, int,
+                                        const double2 *, const double2 *, int64_t,
+                                        const int64_t *, double2 *, int, hipStream_t);
+template void launch_expand_blk<float>(const float2 *, const float2 *, const int32_t *, int, int,
+                                       const int32_t *, const int32_t *, int, const float2 *,
+                                       const float2 *, int64_t, const int64_t *, float2 *, int,
+                                       hipStream_t);
 
 }  // namespace dpg

@@ -58,15 +58,16 @@ void launch_csr_blk(int64_t nrows, const int64_t *ptr, const int32_t *col, const
 // Macro condensation and expansion of nr columns (see launch_condense_local,
 // launch_condense_reduce, launch_expand).
 template <typename T>
-void launch_condense_blk(const cplx_t<T> *WH, int nI, int nBf, const int32_t *blkI, int nblk,
-                         int64_t nM, const int64_t *macro_B, const int32_t *red_ptr,
+void launch_condense_blk(const cplx_t<T> *WH, const int32_t *bcls, int nI, int nBf,
+                         const int32_t *blkI, int nblk, int64_t nM, const int64_t *macro_B,
+                         const int32_t *red_ptr,
                          const int32_t *red_ent, const cplx_t<T> *rc, cplx_t<T> *c,
                          cplx_t<T> *rB, int nr, hipStream_t s);
 template <typename T>
-void launch_expand_blk(const cplx_t<T> *WH, const cplx_t<T> *Tinv, int nI, int nBf,
-                       const int32_t *blkI, const int32_t *blkBm, int nblk, const cplx_t<T> *rc,
-                       const cplx_t<T> *eB, int64_t nM, const int64_t *macro_B, cplx_t<T> *ec,
-                       int nr, hipStream_t s);
+void launch_expand_blk(const cplx_t<T> *WH, const cplx_t<T> *Tinv, const int32_t *bcls, int nI,
+                       int nBf, const int32_t *blkI, const int32_t *blkBm, int nblk,
+                       const cplx_t<T> *rc, const cplx_t<T> *eB, int64_t nM,
+                       const int64_t *macro_B, cplx_t<T> *ec, int nr, hipStream_t s);
 
 // Column-major [nr][n] <-> interleaved [n][nr] (FP64).
 void launch_interleave(int64_t n, int nr, const double2 *cols, double2 *blk, hipStream_t s);

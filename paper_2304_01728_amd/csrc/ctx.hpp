@@ -16,8 +16,32 @@
 
 namespace dpg {
 
+// Classes of equal matrices.  All elements are translated copies of one box, so
+// two of them with the same wave speed and the same faces on Gamma have equal
+// element matrices; two macro blocks with equal children (and two patches with
+// equal blocks around them) are equal in turn.  Each class is computed and
+// stored once, by the arithmetic its first member would go through alone, so
+// the matrices are bit for bit those of a setup without classes.  Classes are
+// numbered by their first members; with too little to share (more than three
+// quarters as many classes as members) every member is a class of its own.
+struct Classes {
+  int n = 0;                         // classes
+  std::vector<int32_t> of_h, rep_h;  // class of each member; first member of each class
+  const int32_t *of = nullptr, *rep = nullptr;   // the same on the device (dpg_ctx::classes)
+  bool shared() const { return n < (int)of_h.size(); }
+};
+
 // Prepared once per mesh (and per number of loads): item tables on the device
 // and fixed workspaces, so that the setup phases only queue kernels.
+
+// Loads of the elements of one chunk of element classes: a range of the
+// elements sorted by class, with the items of the products and solves by the
+// chunk's factors (one item per class of the chunk, some without columns).
+struct LoadPiece {
+  int chunk = 0, j0 = 0, cnt = 0, max_cols = 0;
+  DevBuf<TrsmItem> tl, tk;
+  DevBuf<GemmItem> gl, gs, gr;
+};
 
 // Element stage: chunks of C elements are dealt to ns streams, each with its
 // own G, [B l], K and diagonal-block-inverse buffers.
@@ -33,6 +57,11 @@ struct ElemPlan {
   DevBuf<double2> X[4];
   DevBuf<GemmItem> gR;
   int gR_nr = 0, gR_C = 0;
+  // with shared classes (nel = their number, mp = m): the loads by pieces
+  DevBuf<double2> LB[4], KL[4], wkK[4];
+  DevBuf<int32_t> mlist;             // elements sorted by class
+  std::vector<LoadPiece> pieces;
+  int pieces_nr = -1, pieces_C = 0;
 };
 
 // Load updates by maps per element class.  Elements with equal wave speed and
@@ -61,7 +90,7 @@ struct MacroPlan {
   DevBuf<GemmItem> gS, gTi, gWH, gX, gA;
   DevBuf<int64_t> idoff, soff, moff;
   DevBuf<int32_t> idn, cmap, sld, map;
-  DevBuf<int> info;    // [nblk]
+  DevBuf<int> info;    // [block classes]
 };
 
 // Patch factors and inverses of one level, in batches that fit the patch
@@ -69,7 +98,7 @@ struct MacroPlan {
 struct PatchBatch {
   int half = 0;                      // part: 0 .. 2 on the extra streams, 3 on the main
                                      // stream (each part with its own workspaces)
-  int v0 = 0, cnt = 0, nmax = 0;
+  int v0 = 0, cnt = 0, nmax = 0;     // patch classes v0 .. v0 + cnt - 1
   int64_t t0 = 0, t1 = 0;
   double fp = 0, ft = 0, fg = 0;
   DevBuf<int64_t> off;
@@ -80,14 +109,16 @@ struct PatchBatch {
   DevBuf<GemmItem> gi;
   DevBuf<GemmItem> gyc, gzc;         // recomputed inverses, t = X x_v and y_v = X^H t for
                                      // nr = 1 .. kMaxCols columns stored column by
-                                     // column: items (nr - 1) cnt + i
+                                     // column: items (nr - 1) mcnt + i over the
+                                     // patches of the batch's classes
+  int mcnt = 0;
 };
 struct PatchPlan {
   bool ready = false;
   std::vector<PatchBatch> batches;
   DevBuf<int64_t> soff_all;
   DevBuf<int32_t> ld_all;
-  DevBuf<int> info;    // [npatch]
+  DevBuf<int> info;    // [patch classes]
 };
 
 // One mesh of the hierarchy.  Level 0 is the coarsest mesh, level L the finest.
@@ -99,7 +130,8 @@ struct LevelData {
   Numbering num;
   std::vector<int32_t> edofs_h;
   DevBuf<int32_t> edofs;
-  DevBuf<double2> E;                 // element matrices [nel][n_tr^2]
+  Classes ec, bc, pc;                // of the elements, macro blocks and vertex patches
+  DevBuf<double2> E;                 // element matrices [ec.n][n_tr^2]
   DevBuf<double> kappa, Zel;         // per element c^-2 and Z on a coarser mesh whose
                                      // operator is assembled directly ("store")
   // macro grid (levels >= 1)
@@ -108,8 +140,8 @@ struct LevelData {
   Prolongation P;
   int nblk = 0, nBf = 0, nI = 0;
   int64_t nM = 0;
-  DevBuf<double2> Mfull;             // [nblk][nBf^2] condensed blocks, full local layout
-  DevBuf<double2> Tinv, WH;          // [nblk][nI^2], [nblk][nBf nI]
+  DevBuf<double2> Mfull;             // [bc.n][nBf^2] condensed blocks, full local layout
+  DevBuf<double2> Tinv, WH;          // [bc.n][nI^2], [bc.n][nBf nI]
   DevBuf<float2> Tinv32, WH32;
   DevBuf<int32_t> blkI, blkBm;       // [nblk][nI] canonical, [nblk][nBf] macro index / -1
   DevBuf<int64_t> macroB;            // [nM] canonical index of each macro unknown
@@ -197,12 +229,13 @@ struct dpg_ctx {
   dpg::DevBuf<double> src;
   dpg::DevBuf<double2> u0q;          // impedance data at the boundary load points, all loads
   std::vector<dpg::LevelData> lv;
+  dpg::DevBuf<int32_t> classes;      // the class lists of every level
   int L = 0;
   bool keep_recovery = false;
   dpg::DevBuf<double2> s_elem;       // [nrhs][nel][n_tr] condensed element loads
   dpg::DevBuf<double2> s_asm;        // [nrhs][n_trace] assembled loads
   dpg::DevBuf<int32_t> asm_ptr, asm_ent;
-  dpg::DevBuf<double2> rec_L, rec_Y, rec_Yb;  // [nel][nf^2], [nel][nf n_tr], [nel][nrhs nf]
+  dpg::DevBuf<double2> rec_L, rec_Y, rec_Yb;  // [ec.n][nf^2], [ec.n][nf n_tr], [nel][nrhs nf]
   dpg::DevBuf<int32_t> elist;        // elements of a point-source load update
   dpg::LoadMaps lm;                  // load updates without the element chain
   // coarsest mesh
@@ -218,7 +251,7 @@ struct dpg_ctx {
   dpg::DevBuf<dpg::TrsmItem> zti;
   dpg::DevBuf<dpg::GemmItem> zgi;
   dpg::DevBuf<int64_t> zoff;
-  dpg::DevBuf<int32_t> znn, zld;
+  dpg::DevBuf<int32_t> znn, zld, zptr, zent;   // zptr, zent: elements holding each unknown
   dpg::DevBuf<int> zinfo;
   // outer CG (FP64, finest macro grid)
   dpg::DevBuf<double2> b, x, r, z, zo, pv, q, xfull, sB;

@@ -468,11 +468,12 @@ __global__ __launch_bounds__(256) void k_pack(const int4 *__restrict__ tdesc, in
 }  // namespace
 
 void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t> &idx_concat,
-                    int64_t nvec_, bool fp64, bool fp32, Budget *bud, hipStream_t s) {
+                    int64_t nvec_, bool fp64, bool fp32, Budget *bud, hipStream_t s,
+                    const std::vector<int32_t> *cls) {
   nblk = (int)sizes.size();
   nvec = nvec_;
   n_h = sizes;
-  std::vector<int64_t> toff(nblk), eoff(nblk), cpo(nblk), rpo(nblk), loff(nblk);
+  std::vector<int64_t> toff, ceoff, eoff(nblk), cpo(nblk), rpo(nblk), loff(nblk);
   int64_t t = 0, p = 0, lo = 0, ii = 0;
   nent = 0;
   packed = 0;
@@ -483,24 +484,29 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
   std::vector<int32_t> gi;
   for (int b = 0; b < nblk; ++b) {
     const int n = sizes[b], nt = (n + 31) / 32;
-    toff[b] = t;
-    eoff[b] = nent;
-    nent += tile_entry(0, nt);
+    const int cl = cls ? (*cls)[b] : b;
+    const bool first = cl == (int)toff.size();   // classes are numbered by first block
+    if (first) {
+      toff.push_back(t);
+      ceoff.push_back(nent);
+      t += (int64_t)nt * (nt + 1) / 2;
+      nent += tile_entry(0, nt);
+      packed += (int64_t)n * (n + 1) / 2;
+    }
+    eoff[b] = ceoff[cl];
     cpo[b] = p;
     p += colbase(nt);
     rpo[b] = p;
     p += (int64_t)nt * (nt + 1) / 2 * 32;
     loff[b] = lo;
-    t += (int64_t)nt * (nt + 1) / 2;
     lo += (int64_t)nt * 32;
-    packed += (int64_t)n * (n + 1) / 2;
     full += (int64_t)n * n;
     for (int i = 0; i < 32 * nt; ++i) gi.push_back(i < n ? idx_concat[ii + i] : -1);
     ii += n;
     for (int J = 0; J < nt; ++J) {
       for (int seg = 0; seg * kSeg <= J; ++seg) un.push_back(make_int4(b, J, seg * kSeg, seg));
       rw.push_back(make_int2(b, J));
-      for (int I = 0; I <= J; ++I) td.push_back(make_int4(b, I, J, 0));
+      for (int I = 0; first && I <= J; ++I) td.push_back(make_int4(b, I, J, 0));
     }
   }
   if (ii != (int64_t)idx_concat.size()) throw DpgError(-1, "HermSet: index list size mismatch");

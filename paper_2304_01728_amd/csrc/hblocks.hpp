@@ -56,7 +56,8 @@ struct HermSet {
   int64_t nent = 0;          // stored tile entries
   int64_t full = 0;          // sum of n_b^2 (entries of the full blocks)
   std::vector<int32_t> n_h;  // block sizes (host)
-  std::vector<int64_t> tile_off_h, ent_off_h;   // per block: first tile index, first entry
+  std::vector<int64_t> tile_off_h;   // per class: first tile index
+  std::vector<int64_t> ent_off_h;    // per block: first entry of its class
   std::vector<int64_t> loc_off_h;                // per block: first row of its local vectors
   DevBuf<int32_t> bn;
   DevBuf<int64_t> ent_off, cp_off, rp_off, loc_off;
@@ -68,7 +69,7 @@ struct HermSet {
   // the same for the FP32 apply by column pairs (strips); partials in p32
   DevBuf<int4> sunits, srowd;
   int64_t snunits = 0, snpart = 0;
-  DevBuf<int4> tdesc;        // (block, I, J, 0) per stored tile (packing)
+  DevBuf<int4> tdesc;        // (representative block, I, J, 0) per stored tile (packing)
   DevBuf<int32_t> red_ptr;   // CSR over vector entries
   DevBuf<int32_t> red_ent;   // offsets into the local vectors
   DevBuf<double2> t64;       // tiles, FP64
@@ -81,9 +82,13 @@ struct HermSet {
   // algorithmic entries: packed Hermitian n(n+1)/2 per block
   int64_t packed_entries() const { return packed; }
 
-  // idx: per block the vector index of each local row (concatenated).
+  // idx: per block the vector index of each local row (concatenated).  cls
+  // (or null: every block its own): the class of each block; the blocks of a
+  // class are the same matrix and share one copy of its tiles, packed from
+  // the class's first block.
   void build(const std::vector<int32_t> &sizes, const std::vector<int32_t> &idx_concat,
-             int64_t nvec_, bool fp64, bool fp32, Budget *bud, hipStream_t s);
+             int64_t nvec_, bool fp64, bool fp32, Budget *bud, hipStream_t s,
+             const std::vector<int32_t> *cls = nullptr);
   // Fill the tiles from dense column-major sources: block b reads
   // src[src_off[b] + map(i) + map(j) * ld[b]] where map is the identity when
   // map_off[b] < 0, else map[map_off[b] + i].

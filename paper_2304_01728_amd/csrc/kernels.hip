@@ -25,10 +25,12 @@ constexpr int kMaxB = 2048, kMaxI = 1024;
 constexpr int kAsmCols = 32;
 template <int ROWS>
 __global__ __launch_bounds__(256) void k_macro_assemble(const double2 *__restrict__ E, int n_tr,
+                                                        const int32_t *__restrict__ ecls,
                                                         const int32_t *__restrict__ child_inv,
-                                                        int N, int b0, int nT,
+                                                        int N, const int32_t *__restrict__ blist,
+                                                        int b0, int nT,
                                                         double2 *__restrict__ T) {
-  const int c0 = blockIdx.x * kAsmCols, b = b0 + blockIdx.y;
+  const int c0 = blockIdx.x * kAsmCols, b = blist[b0 + blockIdx.y];
   const int Nc = N / 2;
   const int ci = b % Nc, cj = (b / Nc) % Nc, ck = b / (Nc * Nc);
   const int64_t n2 = (int64_t)n_tr * n_tr;
@@ -36,7 +38,7 @@ __global__ __launch_bounds__(256) void k_macro_assemble(const double2 *__restric
 #pragma unroll
   for (int ch = 0; ch < 8; ++ch) {
     const int e = (2 * ci + (ch & 1)) + N * ((2 * cj + ((ch >> 1) & 1)) + N * (2 * ck + (ch >> 2)));
-    Ech[ch] = E + (int64_t)e * n2;
+    Ech[ch] = E + (int64_t)ecls[e] * n2;
   }
   int lr[ROWS][8];
 #pragma unroll
@@ -108,9 +110,9 @@ __device__ __forceinline__ double2 herm_tile_entry(const double2 *__restrict__ b
 __global__ __launch_bounds__(256) void k_patch_gather_tiles(
     const double2 *__restrict__ tiles, const int64_t *__restrict__ ent_off,
     const int32_t *__restrict__ pidx, int nBf, int Nc, const int64_t *__restrict__ pptr,
-    const int32_t *__restrict__ pslot, int v0, const int64_t *__restrict__ dst_off,
-    double2 *__restrict__ S) {
-  const int v = v0 + blockIdx.x;
+    const int32_t *__restrict__ pslot, const int32_t *__restrict__ vlist, int v0,
+    const int64_t *__restrict__ dst_off, double2 *__restrict__ S) {
+  const int v = vlist[v0 + blockIdx.x];
   const int64_t p0 = pptr[v];
   const int n = (int)(pptr[v + 1] - p0);
   const int jb = blockIdx.y * 8;
@@ -154,12 +156,14 @@ __global__ __launch_bounds__(256) void k_patch_gather_tiles(
 // without it are skipped by a uniform branch and each entry loads only from
 // the cells that hold its column.  Cells are summed in order.
 constexpr int kGatCols = 8;
-__global__ __launch_bounds__(256) void k_patch_gather(const double2 *__restrict__ Mfull, int nBf,
+__global__ __launch_bounds__(256) void k_patch_gather(const double2 *__restrict__ Mfull,
+                                                      const int32_t *__restrict__ bcls, int nBf,
                                                       int Nc, const int64_t *__restrict__ pptr,
-                                                      const int32_t *__restrict__ pslot, int v0,
+                                                      const int32_t *__restrict__ pslot,
+                                                      const int32_t *__restrict__ vlist, int v0,
                                                       const int64_t *__restrict__ dst_off,
                                                       double2 *__restrict__ S) {
-  const int v = v0 + blockIdx.x;
+  const int v = vlist[v0 + blockIdx.x];
   const int64_t p0 = pptr[v];
   const int n = (int)(pptr[v + 1] - p0);
   const int jb = blockIdx.y * kGatCols;
@@ -170,7 +174,7 @@ __global__ __launch_bounds__(256) void k_patch_gather(const double2 *__restrict_
   for (int c = 0; c < 8; ++c) {
     const int ci = vx - 1 + (c & 1), cj = vy - 1 + ((c >> 1) & 1), ck = vz - 1 + (c >> 2);
     blk[c] = (ci >= 0 && cj >= 0 && ck >= 0 && ci < Nc && cj < Nc && ck < Nc)
-                 ? ci + Nc * (cj + Nc * ck) : -1;
+                 ? bcls[ci + Nc * (cj + Nc * ck)] : -1;
   }
   const int32_t *sl = pslot + p0 * 8;
   double2 *Sv = S + dst_off[blockIdx.x];
@@ -210,23 +214,28 @@ __global__ __launch_bounds__(256) void k_identity(const int64_t *__restrict__ of
   for (int i = threadIdx.x & 63; i < n; i += 64) xc[i] = mk(i == j ? 1.0 : 0.0, 0.0);
 }
 
+// One workgroup per column of T0: the column is cleared, then the columns of
+// the (at most eight) elements that hold its unknown are added one element
+// after the other, in element order.  (One workgroup for the whole matrix
+// took 4.5 ms at n0 = 2332, 27 elements of 290 unknowns.)
 __global__ __launch_bounds__(256) void k_assemble_dense(const double2 *__restrict__ E, int n_tr,
+                                                        const int32_t *__restrict__ ecls,
                                                         const int32_t *__restrict__ edofs,
-                                                        int nel, int n0,
+                                                        const int32_t *__restrict__ ptr,
+                                                        const int32_t *__restrict__ ent, int n0,
                                                         double2 *__restrict__ T0) {
-  for (int64_t k = threadIdx.x; k < (int64_t)n0 * n0; k += 256) T0[k] = mk(0.0, 0.0);
-  __syncthreads();
-  const int n2 = n_tr * n_tr;
-  for (int e = 0; e < nel; ++e) {
-    const int32_t *d = edofs + (int64_t)e * n_tr;
-    for (int k = threadIdx.x; k < n2; k += 256) {
-      const int gi = d[k % n_tr], gj = d[k / n_tr];
-      if (gi >= 0 && gj >= 0) {
-        double2 *dst = &T0[gi + (int64_t)gj * n0];
-        *dst = cadd(*dst, E[(int64_t)e * n2 + k]);
-      }
-    }
+  const int j = blockIdx.x;
+  double2 *col = T0 + (int64_t)j * n0;
+  for (int i = threadIdx.x; i < n0; i += 256) col[i] = mk(0.0, 0.0);
+  for (int32_t q = ptr[j]; q < ptr[j + 1]; ++q) {
     __syncthreads();
+    const int e = ent[q] / n_tr, lj = ent[q] % n_tr;
+    const int32_t *d = edofs + (int64_t)e * n_tr;
+    const double2 *Ec = E + ((int64_t)ecls[e] * n_tr + lj) * n_tr;
+    for (int i = threadIdx.x; i < n_tr; i += 256) {
+      const int gi = d[i];
+      if (gi >= 0) col[gi] = cadd(col[gi], Ec[i]);
+    }
   }
 }
 
@@ -253,7 +262,8 @@ __global__ __launch_bounds__(256) void k_csr(int64_t nrows, const int64_t *__res
 // Seven or more workgroups per block keep the GPU busy on the coarse levels,
 // which have few blocks.
 template <typename T>
-__global__ __launch_bounds__(256) void k_condense_local(const cplx_t<T> *__restrict__ WH, int nI,
+__global__ __launch_bounds__(256) void k_condense_local(const cplx_t<T> *__restrict__ WH,
+                                                        const int32_t *__restrict__ bcls, int nI,
                                                         int nBf, const int32_t *__restrict__ blkI,
                                                         const cplx_t<T> *__restrict__ rc,
                                                         cplx_t<T> *__restrict__ c) {
@@ -264,7 +274,7 @@ __global__ __launch_bounds__(256) void k_condense_local(const cplx_t<T> *__restr
   const int sl = blockIdx.y * 64 + lane;
   for (int i = threadIdx.x; i < nI; i += 256) rI[i] = rc[blkI[(int64_t)b * nI + i]];
   __syncthreads();
-  const C *W = WH + (int64_t)b * nBf * nI;
+  const C *W = WH + (int64_t)bcls[b] * nBf * nI;
   C a0, a1;
   a0.x = a0.y = 0;
   a1.x = a1.y = 0;
@@ -313,7 +323,8 @@ constexpr int kExpRows = 16;
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_expand(const cplx_t<T> *__restrict__ WH,
-                                                const cplx_t<T> *__restrict__ Tinv, int nI,
+                                                const cplx_t<T> *__restrict__ Tinv,
+                                                const int32_t *__restrict__ bcls, int nI,
                                                 int nBf, const int32_t *__restrict__ blkI,
                                                 const int32_t *__restrict__ blkBm,
                                                 const cplx_t<T> *__restrict__ rc,
@@ -333,8 +344,8 @@ __global__ __launch_bounds__(256) void k_expand(const cplx_t<T> *__restrict__ WH
   }
   for (int i = threadIdx.x; i < nI; i += 256) rI[i] = rc[blkI[(int64_t)b * nI + i]];
   __syncthreads();
-  const C *W = WH + (int64_t)b * nBf * nI;
-  const C *Ti = Tinv + (int64_t)b * nI * nI;
+  const C *W = WH + (int64_t)bcls[b] * nBf * nI;
+  const C *Ti = Tinv + (int64_t)bcls[b] * nI * nI;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int i = i0 + wave; i < i1; i += 4) {
     C u, v;
@@ -372,7 +383,8 @@ __global__ __launch_bounds__(256) void k_assemble_vec(int64_t n, const int32_t *
 
 __global__ __launch_bounds__(256) void k_fields(const double2 *__restrict__ recL,
                                                 const double2 *__restrict__ recY,
-                                                const double2 *__restrict__ recYb, int nf,
+                                                const double2 *__restrict__ recYb,
+                                                const int32_t *__restrict__ ecls, int nf,
                                                 int ntr, int nrhs, int col,
                                                 const int32_t *__restrict__ edofs,
                                                 const double2 *__restrict__ x,
@@ -385,9 +397,9 @@ __global__ __launch_bounds__(256) void k_fields(const double2 *__restrict__ recL
     xt[j] = t >= 0 ? x[t] : mk(0.0, 0.0);
   }
   __syncthreads();
-  const double2 *Y = recY + (int64_t)e * nf * ntr;
+  const double2 *Y = recY + (int64_t)ecls[e] * nf * ntr;
   const double2 *Yb = recYb + ((int64_t)e * nrhs + col) * nf;
-  const double2 *L = recL + (int64_t)e * nf * nf;
+  const double2 *L = recL + (int64_t)ecls[e] * nf * nf;
   for (int i = threadIdx.x; i < nf; i += 256) {
     double2 acc = Yb[i];
     for (int j = 0; j < ntr; ++j) acc = csub(acc, cmul(Y[i + (int64_t)j * nf], xt[j]));
@@ -406,30 +418,37 @@ __global__ __launch_bounds__(256) void k_fields(const double2 *__restrict__ recL
 }
 
 // Error indicator, step 1: the unknowns [x_f; x_t] of element e0 + blockIdx.x
-// for load column blockIdx.y.  K holds, per element (stride ks, leading
-// dimension ld), the factor L of K_ff in its first nf columns and
-// Y = L^-1 [K_ft | b] in the columns after: x_f = L^-H (Y_b - Y_t x_t).
+// (or elist[e0 + blockIdx.x]) for load column blockIdx.y.  K holds, per item
+// or element class (stride ks, leading dimension ld), the factor L of K_ff in
+// its first nf columns and Y_t = L^-1 K_ft in the columns after, Yb (stride
+// ys, leading dimension ld) the columns L^-1 b: x_f = L^-H (Y_b - Y_t x_t).
 // X[i] is m x nr (leading dimension m = nf + ntr), x_t gathered from x
 // (column r at x + r nvec) through the element map (-1: absent, zero).
 __global__ __launch_bounds__(256) void k_indicator_x(const double2 *__restrict__ K, int64_t ks,
-                                                     int ld, int nf, int ntr, int nr,
+                                                     int ld, const double2 *__restrict__ Ybs,
+                                                     int64_t ys, int nf, int ntr, int nr,
                                                      const int32_t *__restrict__ edofs,
+                                                     const int32_t *__restrict__ elist,
+                                                     const int32_t *__restrict__ ecls, int k0,
+                                                     int e0,
                                                      const double2 *__restrict__ x, int64_t nvec,
                                                      double2 *__restrict__ X) {
   __shared__ double2 v[kMaxI];
   __shared__ double2 xt[kMaxB];
-  const int e = blockIdx.x, r = blockIdx.y, m = nf + ntr;
+  const int r = blockIdx.y, m = nf + ntr;
+  const int e = elist ? elist[e0 + blockIdx.x] : e0 + (int)blockIdx.x;
   const double2 *xr = x + (int64_t)r * nvec;
-  double2 *Xe = X + ((int64_t)e * nr + r) * m;
+  double2 *Xe = X + ((int64_t)blockIdx.x * nr + r) * m;
   for (int j = threadIdx.x; j < ntr; j += 256) {
     const int32_t t = edofs[(int64_t)e * ntr + j];
     xt[j] = t >= 0 ? xr[t] : mk(0.0, 0.0);
     Xe[nf + j] = xt[j];
   }
   __syncthreads();
-  const double2 *Ke = K + (int64_t)e * ks;
+  const double2 *Ke = K + (elist ? ecls[e] - k0 : (int64_t)blockIdx.x) * ks;
+  const double2 *Yb = Ybs + blockIdx.x * ys + (int64_t)r * ld;
   for (int i = threadIdx.x; i < nf; i += 256) {
-    double2 acc = Ke[i + (int64_t)(m + r) * ld];
+    double2 acc = Yb[i];
     for (int j = 0; j < ntr; ++j) acc = csub(acc, cmul(Ke[i + (int64_t)(nf + j) * ld], xt[j]));
     v[i] = acc;
   }
@@ -444,14 +463,17 @@ __global__ __launch_bounds__(256) void k_indicator_x(const double2 *__restrict__
   for (int i = threadIdx.x; i < nf; i += 256) Xe[i] = v[i];
 }
 
-// Error indicator, step 3: out[r * nel_out + e0 + e] = || W[e](:, c0 + r) ||^2
-// over n rows (W per element at stride ws, leading dimension ld).
+// Error indicator, step 3: out[r * nel_out + e] = || W[k](:, c0 + r) ||^2 over
+// n rows, e = e0 + k or elist[e0 + k] (W per item at stride ws, leading
+// dimension ld).
 __global__ __launch_bounds__(256) void k_colnorm2(const double2 *__restrict__ W, int64_t ws,
-                                                  int ld, int n, int c0, int e0, int64_t nel_out,
-                                                  double *__restrict__ out) {
+                                                  int ld, int n, int c0,
+                                                  const int32_t *__restrict__ elist, int e0,
+                                                  int64_t nel_out, double *__restrict__ out) {
   __shared__ double red[256];
-  const int e = blockIdx.x, r = blockIdx.y;
-  const double2 *w = W + (int64_t)e * ws + (int64_t)(c0 + r) * ld;
+  const int r = blockIdx.y;
+  const int e = elist ? elist[e0 + blockIdx.x] : e0 + (int)blockIdx.x;
+  const double2 *w = W + (int64_t)blockIdx.x * ws + (int64_t)(c0 + r) * ld;
   double acc = 0.0;
   for (int i = threadIdx.x; i < n; i += 256) acc += w[i].x * w[i].x + w[i].y * w[i].y;
   red[threadIdx.x] = acc;
@@ -460,7 +482,7 @@ __global__ __launch_bounds__(256) void k_colnorm2(const double2 *__restrict__ W,
     if (threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[(int64_t)r * nel_out + e0 + e] = red[0];
+  if (threadIdx.x == 0) out[(int64_t)r * nel_out + e] = red[0];
 }
 
 template <typename C> __global__ void k_zero(int64_t n, C *a) {
@@ -580,17 +602,21 @@ __global__ __launch_bounds__(256) void k_update_p(int64_t n, double2 *__restrict
 
 // ---- launchers --------------------------------------------------------------------------
 
-void launch_macro_assemble(const double2 *E, int n_tr, const int32_t *child_inv, int N, int b0,
+void launch_macro_assemble(const double2 *E, int n_tr, const int32_t *ecls,
+                           const int32_t *child_inv, int N, const int32_t *blist, int b0,
                            int count, int nT, double2 *T, hipStream_t s) {
   if (count <= 0) return;
   if (count > 65535 || nT > 256 * 12) throw DpgError(-1, "macro assembly grid too large");
   const dim3 g(cdiv(nT, kAsmCols), count);
   if (nT <= 256 * 4)
-    hipLaunchKernelGGL(k_macro_assemble<4>, g, dim3(256), 0, s, E, n_tr, child_inv, N, b0, nT, T);
+    hipLaunchKernelGGL(k_macro_assemble<4>, g, dim3(256), 0, s, E, n_tr, ecls, child_inv, N,
+                       blist, b0, nT, T);
   else if (nT <= 256 * 8)
-    hipLaunchKernelGGL(k_macro_assemble<8>, g, dim3(256), 0, s, E, n_tr, child_inv, N, b0, nT, T);
+    hipLaunchKernelGGL(k_macro_assemble<8>, g, dim3(256), 0, s, E, n_tr, ecls, child_inv, N,
+                       blist, b0, nT, T);
   else
-    hipLaunchKernelGGL(k_macro_assemble<12>, g, dim3(256), 0, s, E, n_tr, child_inv, N, b0, nT, T);
+    hipLaunchKernelGGL(k_macro_assemble<12>, g, dim3(256), 0, s, E, n_tr, ecls, child_inv, N,
+                       blist, b0, nT, T);
   LAUNCH_OK();
 }
 
@@ -605,20 +631,22 @@ void launch_copy_sub(const double2 *src, int64_t src_stride, int lds, int r0, in
 
 void launch_patch_gather_tiles(const double2 *tiles, const int64_t *ent_off, const int32_t *pidx,
                                int nBf, int Nc, const int64_t *patch_ptr,
-                               const int32_t *patch_slot, int v0, int count, int nmax,
-                               const int64_t *dst_off, double2 *S, hipStream_t s) {
+                               const int32_t *patch_slot, const int32_t *vlist, int v0,
+                               int count, int nmax, const int64_t *dst_off, double2 *S,
+                               hipStream_t s) {
   if (count <= 0) return;
   hipLaunchKernelGGL(k_patch_gather_tiles, dim3(count, cdiv(nmax, kGatCols)), dim3(256), 0, s,
-                     tiles, ent_off, pidx, nBf, Nc, patch_ptr, patch_slot, v0, dst_off, S);
+                     tiles, ent_off, pidx, nBf, Nc, patch_ptr, patch_slot, vlist, v0, dst_off, S);
   LAUNCH_OK();
 }
 
-void launch_patch_gather(const double2 *Mfull, int nBf, int Nc, const int64_t *patch_ptr,
-                         const int32_t *patch_slot, int v0, int count, int nmax,
+void launch_patch_gather(const double2 *Mfull, const int32_t *bcls, int nBf, int Nc,
+                         const int64_t *patch_ptr, const int32_t *patch_slot,
+                         const int32_t *vlist, int v0, int count, int nmax,
                          const int64_t *dst_off, double2 *S, hipStream_t s) {
   if (count <= 0) return;
   hipLaunchKernelGGL(k_patch_gather, dim3(count, cdiv(nmax, kGatCols)), dim3(256), 0, s, Mfull,
-                     nBf, Nc, patch_ptr, patch_slot, v0, dst_off, S);
+                     bcls, nBf, Nc, patch_ptr, patch_slot, vlist, v0, dst_off, S);
   LAUNCH_OK();
 }
 
@@ -630,9 +658,12 @@ void launch_identity(const int64_t *off, const int32_t *n, int count, int nmax, 
   LAUNCH_OK();
 }
 
-void launch_assemble_dense(const double2 *E, int n_tr, const int32_t *edofs, int nel, int n0,
-                           double2 *T0, hipStream_t s) {
-  hipLaunchKernelGGL(k_assemble_dense, dim3(1), dim3(256), 0, s, E, n_tr, edofs, nel, n0, T0);
+void launch_assemble_dense(const double2 *E, int n_tr, const int32_t *ecls, const int32_t *edofs,
+                           const int32_t *ptr, const int32_t *ent, int n0, double2 *T0,
+                           hipStream_t s) {
+  if (n0 <= 0) return;
+  hipLaunchKernelGGL(k_assemble_dense, dim3(n0), dim3(256), 0, s, E, n_tr, ecls, edofs, ptr, ent,
+                     n0, T0);
   LAUNCH_OK();
 }
 
@@ -646,11 +677,12 @@ void launch_csr(int64_t nrows, const int64_t *ptr, const int32_t *col, const T *
 }
 
 template <typename T>
-void launch_condense_local(const cplx_t<T> *WH, int nI, int nBf, const int32_t *blkI, int nblk,
-                           const cplx_t<T> *rc, cplx_t<T> *c, hipStream_t s) {
+void launch_condense_local(const cplx_t<T> *WH, const int32_t *bcls, int nI, int nBf,
+                           const int32_t *blkI, int nblk, const cplx_t<T> *rc, cplx_t<T> *c,
+                           hipStream_t s) {
   if (nI > kMaxI || nBf > kMaxB) throw DpgError(-1, "macro block too large");
-  hipLaunchKernelGGL((k_condense_local<T>), dim3(nblk, cdiv(nBf, 64)), dim3(256), 0, s, WH, nI,
-                     nBf, blkI, rc, c);
+  hipLaunchKernelGGL((k_condense_local<T>), dim3(nblk, cdiv(nBf, 64)), dim3(256), 0, s, WH, bcls,
+                     nI, nBf, blkI, rc, c);
   LAUNCH_OK();
 }
 
@@ -664,16 +696,16 @@ void launch_condense_reduce(int64_t nM, const int64_t *macro_B, const int32_t *r
 }
 
 template <typename T>
-void launch_expand(const cplx_t<T> *WH, const cplx_t<T> *Tinv, int nI, int nBf,
-                   const int32_t *blkI, const int32_t *blkBm, int nblk, const cplx_t<T> *rc,
-                   const cplx_t<T> *eB, int64_t nM, const int64_t *macro_B, cplx_t<T> *ec,
-                   hipStream_t s) {
+void launch_expand(const cplx_t<T> *WH, const cplx_t<T> *Tinv, const int32_t *bcls, int nI,
+                   int nBf, const int32_t *blkI, const int32_t *blkBm, int nblk,
+                   const cplx_t<T> *rc, const cplx_t<T> *eB, int64_t nM, const int64_t *macro_B,
+                   cplx_t<T> *ec, hipStream_t s) {
   if (nI > kMaxI || nBf > kMaxB) throw DpgError(-1, "macro block too large");
   hipLaunchKernelGGL((k_scatter_macro<T>), dim3(cdiv(nM, 256)), dim3(256), 0, s, nM, macro_B, eB,
                      ec);
   LAUNCH_OK();
-  hipLaunchKernelGGL((k_expand<T>), dim3(nblk, cdiv(nI, kExpRows)), dim3(256), 0, s, WH, Tinv, nI,
-                     nBf, blkI, blkBm, rc, eB, ec);
+  hipLaunchKernelGGL((k_expand<T>), dim3(nblk, cdiv(nI, kExpRows)), dim3(256), 0, s, WH, Tinv,
+                     bcls, nI, nBf, blkI, blkBm, rc, eB, ec);
   LAUNCH_OK();
 }
 
@@ -684,29 +716,31 @@ void launch_assemble_vec(int64_t n, const int32_t *ptr, const int32_t *ent, cons
   LAUNCH_OK();
 }
 
-void launch_fields(const double2 *recL, const double2 *recY, const double2 *recYb, int nf,
-                   int ntr, int nrhs, int col, const int32_t *edofs, int nel, const double2 *x,
-                   double2 *out, hipStream_t s) {
+void launch_fields(const double2 *recL, const double2 *recY, const double2 *recYb,
+                   const int32_t *ecls, int nf, int ntr, int nrhs, int col, const int32_t *edofs,
+                   int nel, const double2 *x, double2 *out, hipStream_t s) {
   if (nf > kMaxI || ntr > kMaxB) throw DpgError(-1, "element too large for field recovery");
-  hipLaunchKernelGGL(k_fields, dim3(nel), dim3(256), 0, s, recL, recY, recYb, nf, ntr, nrhs, col,
-                     edofs, x, out);
+  hipLaunchKernelGGL(k_fields, dim3(nel), dim3(256), 0, s, recL, recY, recYb, ecls, nf, ntr, nrhs,
+                     col, edofs, x, out);
   LAUNCH_OK();
 }
 
-void launch_indicator_x(const double2 *K, int64_t ks, int ld, int nf, int ntr, int nr,
-                        const int32_t *edofs, int count, const double2 *x, int64_t nvec,
-                        double2 *X, hipStream_t s) {
+void launch_indicator_x(const double2 *K, int64_t ks, int ld, const double2 *Yb, int64_t ys,
+                        int nf, int ntr, int nr, const int32_t *edofs, const int32_t *elist,
+                        const int32_t *ecls, int k0, int e0, int count, const double2 *x,
+                        int64_t nvec, double2 *X, hipStream_t s) {
   if (nf > kMaxI || ntr > kMaxB) throw DpgError(-1, "element too large for the error indicator");
   if (count <= 0 || nr <= 0) return;
-  hipLaunchKernelGGL(k_indicator_x, dim3(count, nr), dim3(256), 0, s, K, ks, ld, nf, ntr, nr,
-                     edofs, x, nvec, X);
+  hipLaunchKernelGGL(k_indicator_x, dim3(count, nr), dim3(256), 0, s, K, ks, ld, Yb, ys, nf, ntr,
+                     nr, edofs, elist, ecls, k0, e0, x, nvec, X);
   LAUNCH_OK();
 }
 
-void launch_colnorm2(const double2 *W, int64_t ws, int ld, int n, int c0, int ncols, int e0,
-                     int count, int64_t nel_out, double *out, hipStream_t s) {
+void launch_colnorm2(const double2 *W, int64_t ws, int ld, int n, int c0, int ncols,
+                     const int32_t *elist, int e0, int count, int64_t nel_out, double *out,
+                     hipStream_t s) {
   if (count <= 0 || ncols <= 0) return;
-  hipLaunchKernelGGL(k_colnorm2, dim3(count, ncols), dim3(256), 0, s, W, ws, ld, n, c0, e0,
+  hipLaunchKernelGGL(k_colnorm2, dim3(count, ncols), dim3(256), 0, s, W, ws, ld, n, c0, elist, e0,
                      nel_out, out);
   LAUNCH_OK();
 }
@@ -765,21 +799,25 @@ template void launch_csr<double>(int64_t, const int64_t *, const int32_t *, cons
                                  const double2 *, double2 *, int, hipStream_t);
 template void launch_csr<float>(int64_t, const int64_t *, const int32_t *, const float *,
                                 const float2 *, float2 *, int, hipStream_t);
-template void launch_condense_local<double>(const double2 *, int, int, const int32_t *, int,
-                                            const double2 *, double2 *, hipStream_t);
-template void launch_condense_local<float>(const float2 *, int, int, const int32_t *, int,
-                                           const float2 *, float2 *, hipStream_t);
+template void launch_condense_local<double>(const double2 *, const int32_t *, int, int,
+                                            const int32_t *, int, const double2 *, double2 *,
+                                            hipStream_t);
+template void launch_condense_local<float>(const float2 *, const int32_t *, int, int,
+                                           const int32_t *, int, const float2 *, float2 *,
+                                           hipStream_t);
 template void launch_condense_reduce<double>(int64_t, const int64_t *, const int32_t *,
                                              const int32_t *, const double2 *, const double2 *,
                                              double2 *, hipStream_t);
 template void launch_condense_reduce<float>(int64_t, const int64_t *, const int32_t *,
                                             const int32_t *, const float2 *, const float2 *,
                                             float2 *, hipStream_t);
-template void launch_expand<double>(const double2 *, const double2 *, int, int, const int32_t *,
-                                    const int32_t *, int, const double2 *, const double2 *,
-                                    int64_t, const int64_t *, double2 *, hipStream_t);
-template void launch_expand<float>(const float2 *, const float2 *, int, int, const int32_t *,
-                                   const int32_t *, int, const float2 *, const float2 *, int64_t,
-                                   const int64_t *, float2 *, hipStream_t);
+template void launch_expand<double>(const double2 *, const double2 *, const int32_t *, int, int,
+                                    const int32_t *, const int32_t *, int, const double2 *,
+                                    const double2 *, int64_t, const int64_t *, double2 *,
+                                    hipStream_t);
+template void launch_expand<float>(const float2 *, const float2 *, const int32_t *, int, int,
+                                   const int32_t *, const int32_t *, int, const float2 *,
+                                   const float2 *, int64_t, const int64_t *, float2 *,
+                                   hipStream_t);
 
 }  // namespace dpg

@@ -8,9 +8,11 @@ namespace dpg {
 // ---- hierarchy setup (FP64) ----------------------------------------------------
 
 // T[b] (nT x nT, nT = nBf + nI) = sum over the 8 children of coarse element
-// b0 + b of their element matrices E (n_tr x n_tr).  child_inv [8][nT] gives
-// each position of [B slots | I] its local index in each child, or -1.
-void launch_macro_assemble(const double2 *E, int n_tr, const int32_t *child_inv, int N, int b0,
+// blist[b0 + b] of their element matrices E[ecls[e]] (n_tr x n_tr).  child_inv
+// [8][nT] gives each position of [B slots | I] its local index in each child,
+// or -1.
+void launch_macro_assemble(const double2 *E, int n_tr, const int32_t *ecls,
+                           const int32_t *child_inv, int N, const int32_t *blist, int b0,
                            int count, int nT, double2 *T, hipStream_t s);
 
 // dst[d(b)][i + j ldd] = src[b][r0 + i + (c0 + j) lds] for i < rows, j < cols,
@@ -20,11 +22,13 @@ void launch_copy_sub(const double2 *src, int64_t src_stride, int lds, int r0, in
                      int cols, double2 *dst, int64_t dst_stride, int ldd, int count,
                      hipStream_t s, const int32_t *dlist = nullptr);
 
-// Lower triangle of the patch block S_v (n_v x n_v) gathered from the macro
-// blocks of the <= 8 coarse cells around vertex v: S[i,j] = sum_c M_c[slot_c(i),
-// slot_c(j)], j <= i.
-void launch_patch_gather(const double2 *Mfull, int nBf, int Nc, const int64_t *patch_ptr,
-                         const int32_t *patch_slot, int v0, int count, int nmax,
+// Lower triangle of the patch block S_v (n_v x n_v) of the vertices v =
+// vlist[v0 ...], gathered from the macro blocks of the <= 8 coarse cells
+// around v: S[i,j] = sum_c M_c[slot_c(i), slot_c(j)], j <= i, with M_c =
+// Mfull[bcls[c]].
+void launch_patch_gather(const double2 *Mfull, const int32_t *bcls, int nBf, int Nc,
+                         const int64_t *patch_ptr, const int32_t *patch_slot,
+                         const int32_t *vlist, int v0, int count, int nmax,
                          const int64_t *dst_off, double2 *S, hipStream_t s);
 
 // The same lower triangle with the macro blocks read from their packed FP64
@@ -32,16 +36,20 @@ void launch_patch_gather(const double2 *Mfull, int nBf, int Nc, const int64_t *p
 // = packed position of local slot s of block b (-1 absent).
 void launch_patch_gather_tiles(const double2 *tiles, const int64_t *ent_off, const int32_t *pidx,
                                int nBf, int Nc, const int64_t *patch_ptr,
-                               const int32_t *patch_slot, int v0, int count, int nmax,
-                               const int64_t *dst_off, double2 *S, hipStream_t s);
+                               const int32_t *patch_slot, const int32_t *vlist, int v0,
+                               int count, int nmax, const int64_t *dst_off, double2 *S,
+                               hipStream_t s);
 
 // X[b] = identity of size n[b] (column-major, leading dimension n[b]).
 void launch_identity(const int64_t *off, const int32_t *n, int count, int nmax, double2 *X,
                      hipStream_t s);
 
-// Dense T0 (n0 x n0) = sum over elements of E scattered by edofs (-1 skipped).
-void launch_assemble_dense(const double2 *E, int n_tr, const int32_t *edofs, int nel, int n0,
-                           double2 *T0, hipStream_t s);
+// Dense T0 (n0 x n0) = sum over elements e of E[ecls[e]] scattered by edofs
+// (-1 skipped); ptr / ent: per unknown the entries e n_tr + (local index) that
+// hold it, e ascending.
+void launch_assemble_dense(const double2 *E, int n_tr, const int32_t *ecls, const int32_t *edofs,
+                           const int32_t *ptr, const int32_t *ent, int n0, double2 *T0,
+                           hipStream_t s);
 
 // ---- solve phase ---------------------------------------------------------------
 
@@ -51,11 +59,13 @@ void launch_csr(int64_t nrows, const int64_t *ptr, const int32_t *col, const T *
                 const cplx_t<T> *x, cplx_t<T> *y, int add, hipStream_t s);
 
 // Macro condensation of a trace vector rc through the blocks of one level.
-// Per block: WH = (T_II^-1 T_IB)^H (nBf x nI), Tinv = T_II^-1 (nI x nI).
+// Per class of equal blocks: WH = (T_II^-1 T_IB)^H (nBf x nI), Tinv =
+// T_II^-1 (nI x nI); block b has class bcls[b].
 // c_b = WH_b rc[I_b] (nBf slots).
 template <typename T>
-void launch_condense_local(const cplx_t<T> *WH, int nI, int nBf, const int32_t *blkI, int nblk,
-                           const cplx_t<T> *rc, cplx_t<T> *c, hipStream_t s);
+void launch_condense_local(const cplx_t<T> *WH, const int32_t *bcls, int nI, int nBf,
+                           const int32_t *blkI, int nblk, const cplx_t<T> *rc, cplx_t<T> *c,
+                           hipStream_t s);
 // rB[m] = rc[macro_B[m]] - sum over (block, slot) holding m of c_b[slot].
 template <typename T>
 void launch_condense_reduce(int64_t nM, const int64_t *macro_B, const int32_t *red_ptr,
@@ -63,8 +73,9 @@ void launch_condense_reduce(int64_t nM, const int64_t *macro_B, const int32_t *r
                             cplx_t<T> *rB, hipStream_t s);
 // ec[macro_B[m]] = eB[m]; ec[I_b] = Tinv_b rc[I_b] - WH_b^H eB_b.
 template <typename T>
-void launch_expand(const cplx_t<T> *WH, const cplx_t<T> *Tinv, int nI, int nBf,
-                   const int32_t *blkI, const int32_t *blkBm, int nblk, const cplx_t<T> *rc,
+void launch_expand(const cplx_t<T> *WH, const cplx_t<T> *Tinv, const int32_t *bcls, int nI,
+                   int nBf, const int32_t *blkI, const int32_t *blkBm, int nblk,
+                   const cplx_t<T> *rc,
                    const cplx_t<T> *eB, int64_t nM, const int64_t *macro_B, cplx_t<T> *ec,
                    hipStream_t s);
 
@@ -75,24 +86,31 @@ void launch_assemble_vec(int64_t n, const int32_t *ptr, const int32_t *ent, cons
 
 // Field recovery (Sec. 1.2, static condensation undone): per element,
 // x_f = K_ff^-1 (b_f - K_ft x_t) = L^-H (Y_b - Y_t x_t) with L = chol(K_ff),
-// Y_t = L^-1 K_ft ([nel][nf][ntr]) and Y_b = L^-1 b_f ([nel][nrhs][nf]) kept
-// from the element stage; load column col.  out[e][nf].
-void launch_fields(const double2 *recL, const double2 *recY, const double2 *recYb, int nf,
-                   int ntr, int nrhs, int col, const int32_t *edofs, int nel, const double2 *x,
-                   double2 *out, hipStream_t s);
+// Y_t = L^-1 K_ft (recL, recY: per element class, that of e is ecls[e]) and
+// Y_b = L^-1 b_f ([nel][nrhs][nf]) kept from the element stage; load column
+// col.  out[e][nf].
+void launch_fields(const double2 *recL, const double2 *recY, const double2 *recYb,
+                   const int32_t *ecls, int nf, int ntr, int nrhs, int col, const int32_t *edofs,
+                   int nel, const double2 *x, double2 *out, hipStream_t s);
 
 // DPG residual error indicator (Sec. 1.2): per element and load column r,
 // X(:, r) = [x_f; x_t] with x_t gathered from x + r nvec through edofs and
 // x_f = L^-H (Y_b - Y_t x_t), where K (stride ks, leading dimension ld) holds
-// L = chol(K_ff) in its first nf columns and Y = L^-1 [K_ft | b] after them.
+// L = chol(K_ff) in its first nf columns and Y_t = L^-1 K_ft in the next ntr,
+// and column r of Y_b is at Yb + i ys + r ld.  Item i is element e0 + i with
+// K matrix i; with elist (sorted elements) element elist[e0 + i] with K matrix
+// ecls[elist[e0 + i]] - k0.
 // X: [count][nr][m], m = nf + ntr.
-void launch_indicator_x(const double2 *K, int64_t ks, int ld, int nf, int ntr, int nr,
-                        const int32_t *edofs, int count, const double2 *x, int64_t nvec,
-                        double2 *X, hipStream_t s);
-// out[r nel_out + e0 + e] = sum_i |W[e](i, c0 + r)|^2, i < n, for e < count,
-// r < ncols (W per element at stride ws, leading dimension ld).
-void launch_colnorm2(const double2 *W, int64_t ws, int ld, int n, int c0, int ncols, int e0,
-                     int count, int64_t nel_out, double *out, hipStream_t s);
+void launch_indicator_x(const double2 *K, int64_t ks, int ld, const double2 *Yb, int64_t ys,
+                        int nf, int ntr, int nr, const int32_t *edofs, const int32_t *elist,
+                        const int32_t *ecls, int k0, int e0, int count, const double2 *x,
+                        int64_t nvec, double2 *X, hipStream_t s);
+// out[r nel_out + e] = sum_i |W[k](i, c0 + r)|^2, i < n, e = e0 + k (or
+// elist[e0 + k]), for k < count, r < ncols (W per item at stride ws, leading
+// dimension ld).
+void launch_colnorm2(const double2 *W, int64_t ws, int ld, int n, int c0, int ncols,
+                     const int32_t *elist, int e0, int count, int64_t nel_out, double *out,
+                     hipStream_t s);
 
 // a[0..n) = 0 (a kernel, not a memset: safe inside captured graphs).
 template <typename C> void launch_zero(int64_t n, C *a, hipStream_t s);
