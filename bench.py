@@ -27,6 +27,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E
 FP64_PEAK_TFLOPS = 78.6      # MI355X dense FP64 matrix (= vector) peak
 FP32_PEAK_TFLOPS = 157.3
+FP32_VECTOR_PEAK_TFLOPS = 78.6   # one multiply-add per lane (no packed pairs)
 
 
 def make_options(D, w, torch_stream=None, device_ptrs=True, columnwise=False, recompute=False):
@@ -47,8 +48,8 @@ def loads_of(w):
 
 # Classes timed around exactly one kernel symbol; the composite dense classes
 # (potrf, trsm, gemm) each cover several kernels and are reported separately.
-SINGLE_KERNEL = ("apply64", "apply32", "applyb64", "applyb32", "gram", "bmat", "load",
-                 "macro_asm", "patch_gather")
+SINGLE_KERNEL = ("apply64", "apply32", "applyb64", "applyb32", "applyg64", "applyg32", "gram",
+                 "bmat", "load", "macro_asm", "patch_gather")
 DENSE = ("potrf", "trsm", "gemm")
 # the kernels of the dense routines, each launch timed alone (the setup runs on
 # one stream while kernels are profiled)
@@ -105,6 +106,12 @@ def roofline_for(stats, workload):
         achieved = work / n / (avg_ms * 1e-3) / 1e12
         return {"kernel": sym, "bound": "mfma", "achieved": achieved, "peak": FP32_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": achieved / FP32_PEAK_TFLOPS, "traffic": None,
+                "launches": n, "avg_ms": avg_ms, "work_per_launch": work / n}
+    if cls in ("applyg64", "applyg32"):   # vector units; work = algorithmic flops
+        achieved = work / n / (avg_ms * 1e-3) / 1e12
+        peak = FP64_PEAK_TFLOPS if cls == "applyg64" else FP32_VECTOR_PEAK_TFLOPS
+        return {"kernel": sym, "bound": "valu", "achieved": achieved, "peak": peak,
+                "unit": "TFLOP/s", "frac": achieved / peak, "traffic": None,
                 "launches": n, "avg_ms": avg_ms, "work_per_launch": work / n}
     if cls == "applyb64":   # FP64 matrix cores; work = algorithmic flops
         achieved = work / n / (avg_ms * 1e-3) / 1e12

@@ -336,8 +336,10 @@ int64_t dpg_export(const dpg_ctx *ctx, int what, int level, void *out, int64_t c
  * class, the launches timed so far, their summed duration and their summed
  * algorithmic work: bytes for the single-column block-apply kernels (packed
  * Hermitian blocks, each read once), flops for the dense kernels (LAPACK
- * counts) and for the multi-column block applies (8 n^2 nr real flops per
- * block of order n applied to nr columns).  Classes follow the kernel
+ * counts) and for the block applies in which a tile serves several columns:
+ * those of many right-hand sides (DPG_K_APPLYB*) and of groups of equal blocks
+ * or few FP64 right-hand sides (DPG_K_APPLYG*); 8 n^2 nr real flops per block of
+ * order n applied to nr columns.  Classes follow the kernel
  * symbols; DPG_K_POTRF and DPG_K_TRSM time whole Cholesky and forward-solve
  * routines (several kernels each), and DPG_K_POTRF_DIAG ... DPG_K_TRSM_UPDATE
  * their kernels one by one, each launch with its share of the routine's
@@ -350,7 +352,7 @@ enum {
   DPG_K_TRANSFER = 13, DPG_K_CG = 14, DPG_K_OTHER = 15, DPG_K_APPLYB64 = 16,
   DPG_K_APPLYB32 = 17, DPG_K_POTRF_DIAG = 18, DPG_K_POTRF_PANEL = 19,
   DPG_K_POTRF_UPDATE = 20, DPG_K_TRSM_INV = 21, DPG_K_TRSM_SOLVE = 22,
-  DPG_K_TRSM_UPDATE = 23, DPG_K_NCLASS = 24
+  DPG_K_TRSM_UPDATE = 23, DPG_K_APPLYG64 = 24, DPG_K_APPLYG32 = 25, DPG_K_NCLASS = 26
 };
 typedef struct {
   int64_t launches;

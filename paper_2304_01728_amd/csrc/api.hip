@@ -1700,6 +1700,10 @@ void ensure_block(dpg_ctx *c, int nr) {
   if (nr <= c->bcap) return;
   const bool mixed = c->opt.precision == DPG_MIXED;
   Budget *bd = &c->bud;
+  for (LevelData &f : c->lv) {   // the partials are taken last, from what is left
+    f.Mb.part64.release();
+    f.Sb.part64.release();
+  }
   for (int l = 1; l <= c->L; ++l) {
     LevelData &f = c->lv[l];
     const int64_t nc = c->lv[l - 1].num.n, nM = f.nM, ncb = (int64_t)f.nblk * f.nBf;
@@ -1739,6 +1743,11 @@ void ensure_block(dpg_ctx *c, int nr) {
     HIP_OK(hipHostMalloc((void **)&c->host_bsc, 8 * kMaxCols * sizeof(double), 0));
     HIP_OK(hipHostMalloc((void **)&c->host_bact, kMaxCols * sizeof(int), 0));
   }
+  for (int l = 1; l <= c->L; ++l) {
+    c->lv[l].Mb.ensure_part(c->lv[l].Mset, nr, bd);
+    c->lv[l].Sb.ensure_part(c->lv[l].Sset, nr, bd);
+  }
+  c->T0b.ensure_part(c->T0set, nr, bd);
   c->bcap = nr;
 }
 
@@ -2291,7 +2300,7 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
           for (int64_t k = f.mc.blkB_ptr[b]; k < f.mc.blkB_ptr[b + 1]; ++k)
             pidx[(size_t)b * f.nBf + f.mc.blkB_present[k]] = (int32_t)(k - f.mc.blkB_ptr[b]);
         f.mpidx.upload(pidx, &c->bud, s);
-        f.Sset.build(psz, f.mc.patch_idx, f.nM, false, false, &c->bud, s, &f.pc.of_h);
+        f.Sset.build(psz, f.mc.patch_idx, f.nM, false, false, &c->bud, s, &f.pc.of_h, false);
         f.Sset.xl64.alloc(f.Sset.nloc, &c->bud);
         f.Sset.yl64.alloc(f.Sset.nloc, &c->bud);
       } else {

@@ -32,85 +32,113 @@ __global__ __launch_bounds__(256) void k_gather_blk(int64_t nloc, int nr,
   xl[e] = g >= 0 ? x[(int64_t)g * nr + k] : czero<cplx_t<T>>();
 }
 
-// One wave per (block b, tile row I): Y_I (32 x nr) = sum_J A_IJ X_J over the
-// stored upper tiles of row I (J >= I) and the conjugate transposes of the
-// stored tiles of column I (J < I), so no partial sums leave the wave.
+// ---- the block apply on the matrix cores ------------------------------------------------
 //
-// FP32, on the matrix cores.  Y_I (32 x 32, columns past
-// nr are padding) accumulates three real 32x32x32 products per tile (the
+// Columns: the local vectors of the blocks of a group, times the right-hand
+// sides (HermGroup).  A unit (group, tile row I) forms Y_I = sum_J A_IJ X_J of a
+// chunk of 32 columns over the stored upper tiles of row I (J >= I) and the
+// conjugate transposes of the stored tiles of column I (J < I), so no partial
+// sums leave it; every tile is read by two units, of which one finds it in a
+// cache.  Workgroup g runs on XCD g % 8, so each XCD is given a contiguous range
+// of units: the rows of one group then share its tiles and X in one L2.
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+struct RowUnit {
+  int64_t ent, base;   // tiles of the class; row 0, first column of the chunk in the local vectors
+  int I, nt, ld, nc;   // row step of the local vectors and columns of the chunk
+  bool on;
+};
+
+__device__ __forceinline__ RowUnit row_unit(const int2 *__restrict__ rows, const ChunkMap &cm,
+                                            const HermGroup *__restrict__ grp, int nr) {
+  RowUnit u;
+  const int per = (cm.total + 7) / 8;
+  int w = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8), c = 0;
+  u.on = w < cm.total;
+  if (!u.on) return u;
+  while (w >= cm.cnt[c]) w -= cm.cnt[c++];
+  const int2 r = rows[w];
+  const HermGroup g = grp[r.x];
+  u.ent = g.ent;
+  u.I = r.y;
+  u.nt = g.nt;
+  u.ld = g.gw * nr;
+  u.nc = min(32, u.ld - 32 * c);
+  u.base = (int64_t)g.base * nr + 32 * c;
+  return u;
+}
+
+// FP32.  Y_I accumulates three real products per tile (the
 // three-multiplication complex product: a quarter fewer matrix-core
 // operations, and an imaginary part formed as p3 - p1 - p2, which in FP32
 // can lose digits when it is small against |A||X|; this path is the
 // mixed-precision preconditioner, corrected by the FP64 outer iteration),
-// with v_mfma_f32_32x32x2f32: lane l supplies A[l%32][k] and B[k][l%32] for
+// with v_mfma_f32_32x32x2f32 (lane l supplies A[l%32][k] and B[k][l%32] for
 // k = l/32 of each two-column slice, and receives result row
-// 8(v/4) + 4(l/32) + v%4, column l%32 in register v.  The tile A_IJ is
-// staged in LDS column by column (double-buffered, rows XOR-swizzled per
-// group of four columns); X_J goes straight from global memory into the
-// B operands, which for nr = 32 are contiguous 512-byte rows.  The next
-// tile and X_J are loaded while the current ones are multiplied.
-// Workgroup g runs on XCD g % 8, so each XCD is given a contiguous range of
-// tile rows: the rows of one block then share its tiles and X in one L2.
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef double v4d __attribute__((ext_vector_type(4)));
-
-__global__ __launch_bounds__(64, 2) void k_rows_mfma(const float2 *__restrict__ tiles,
-                                                  const int2 *__restrict__ rows, int64_t nrows,
-                                                  const int32_t *__restrict__ bn,
-                                                  const int64_t *__restrict__ ent_off,
-                                                  const int64_t *__restrict__ loc_off,
-                                                  const float2 *__restrict__ xl,
-                                                  float2 *__restrict__ yl, int nr) {
-  __shared__ float2 As[2][32 * 32];
-  const int64_t per = (nrows + 7) / 8;
-  const int64_t w = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (w >= nrows) return;
+// 8(v/4) + 4(l/32) + v%4, column l%32 in register v) or, up to 16 columns,
+// two 16-row blocks of v_mfma_f32_16x16x4f32 (half the cycles; lane l: row or
+// column l%16, k = l/16 of a four-column slice, result row 4(l/16) + v).  Both
+// add the products of a result one by one in the order of k, fused, so the
+// results do not depend on the shape.  The tile A_IJ is staged in LDS column by
+// column (rows XOR-swizzled per group of four columns); X_J
+// goes straight from global memory into the B operands, which for 32 columns
+// are contiguous 512-byte rows.  A tile's registers are loaded again as soon as
+// it is staged, and an X operand's as soon as it is multiplied, so one register
+// set each is in flight through the whole step and three waves fit a SIMD.
+template <int NC>
+__device__ __forceinline__ void rows32(const RowUnit &u, const float2 *__restrict__ tiles,
+                                       const float2 *__restrict__ xl, float2 *__restrict__ yl,
+                                       float2 *buf) {
+  constexpr int NX = NC / 2;   // X entries per lane and tile
   const int lane = threadIdx.x, a = lane >> 3, q = lane & 7;
-  const int kk = lane >> 5, n = lane & 31;
-  // columns past nr read column nr - 1: B column n only feeds result column
+  const int kk = NC == 32 ? lane >> 5 : lane >> 4, n = lane & (NC - 1);
+  const int I = u.I, nt = u.nt;
+  // columns past nc read column nc - 1: B column n only feeds result column
   // n, and those results are not stored
-  const int ncl = n < nr ? n : nr - 1;
-  const int2 bi = rows[w];
-  const int b = bi.x, I = bi.y;
-  const int nt = (bn[b] + 31) >> 5;
-  const int64_t e0 = ent_off[b];
+  const int ncl = min(n, u.nc - 1);
   // a diagonal tile stores the sub-blocks a <= q only (slot diag_slot(a, q))
   const bool dup = a <= q;
   const int dsl = dup ? diag_slot(a, q) : 0;
-  const float2 *xb = xl + loc_off[b] * nr + ncl;
-  auto load = [&](int J, float2 *tt, float2 *xx) {
+  const float2 *xb = xl + u.base + ncl + (int64_t)kk * u.ld;
+  const int64_t xs = (int64_t)(64 / NC) * u.ld;   // step of a lane's X entries
+  float2 t[16], x[NX];
+  auto load_tile = [&](int J) {
     // (wave-uniform branch, constant strides: immediate load offsets); lanes
     // below the diagonal of a diagonal tile read slot 0 (in range), their
     // values are not staged
     if (J != I) {
-      const float2 *tp = tiles + e0 + (J > I ? tile_entry(I, J) : tile_entry(J, I)) + lane;
+      const float2 *tp = tiles + u.ent + (J > I ? tile_entry(I, J) : tile_entry(J, I)) + lane;
 #pragma unroll
-      for (int k = 0; k < 16; ++k) tt[k] = tp[k * 64];
+      for (int k = 0; k < 16; ++k) t[k] = tp[k * 64];
     } else {
-      const float2 *tp = tiles + e0 + tile_entry(I, I) + dsl;
+      const float2 *tp = tiles + u.ent + tile_entry(I, I) + dsl;
 #pragma unroll
-      for (int k = 0; k < 16; ++k) tt[k] = tp[k * kDiagSlots];
+      for (int k = 0; k < 16; ++k) t[k] = tp[k * kDiagSlots];
     }
-    const float2 *xp = xb + (int64_t)(32 * J + kk) * nr;
-#pragma unroll
-    for (int s = 0; s < 16; ++s) xx[s] = xp[(int64_t)2 * s * nr];
   };
   // three real products (Gauss): p1 = Re A Re X, p2 = Im A Im X,
   // p3 = (Re A + Im A)(Re X + Im X); Re Y = p1 - p2, Im Y = p3 - p1 - p2
   v16f p1, p2, p3;
+  v4f q1[2], q2[2], q3[2];
+  if constexpr (NC == 32) {
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    p1[v] = 0.f;
-    p2[v] = 0.f;
-    p3[v] = 0.f;
+    for (int v = 0; v < 16; ++v) {
+      p1[v] = 0.f;
+      p2[v] = 0.f;
+      p3[v] = 0.f;
+    }
+  } else {
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) q1[rb] = q2[rb] = q3[rb] = v4f{0.f, 0.f, 0.f, 0.f};
   }
-  // one tile: start loading tile Jn into tn/xn, stage t as A_IJ in LDS,
-  // multiply; the scheduling barriers keep the loads ahead of the products
-  auto step = [&](int J, int Jn, const float2 *t, const float2 *x, float2 *tn, float2 *xn) {
-    load(Jn, tn, xn);
-    __builtin_amdgcn_sched_barrier(0);
+  load_tile(0);
+#pragma unroll
+  for (int s = 0; s < NX; ++s) x[s] = xb[s * xs];
+#pragma unroll 1
+  for (int J = 0; J < nt; ++J) {
     const bool up = J >= I;
-    float2 *buf = As[J & 1];
     // the lane holds stored entries (4a + i, 4q + j) at 4i + j; A_IJ is the
     // stored tile (J >= I) or the conjugate transpose of tile (J, I)
     if (J != I) {
@@ -140,97 +168,131 @@ __global__ __launch_bounds__(64, 2) void k_rows_mfma(const float2 *__restrict__ 
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int s = 0; s < 16; ++s) {
-      const float2 av = buf[(2 * s + kk) * 32 + (n ^ (2 * (s >> 1)))];
-      p1 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, x[s].x, p1, 0, 0, 0);
-      p2 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, x[s].y, p2, 0, 0, 0);
-      p3 = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x + av.y, x[s].x + x[s].y, p3, 0, 0, 0);
-    }
+    const int Jn = min(J + 1, nt - 1);   // the loads after the last tile repeat it
+    load_tile(Jn);
     __builtin_amdgcn_sched_barrier(0);
-  };
-  // two register sets in turn; the load after the last tile repeats it
-  float2 tA[16], xA[16], tB[16], xB[16];
-  load(0, tA, xA);
-  int J = 0;
-  for (; J + 1 < nt; J += 2) {
-    step(J, J + 1, tA, xA, tB, xB);
-    step(J + 1, J + 2 < nt ? J + 2 : J + 1, tB, xB, tA, xA);
-  }
-  if (J < nt) step(J, J, tA, xA, tB, xB);
-  if (n >= nr) return;
-  float2 *yb = yl + (loc_off[b] + 32 * I) * nr + n;
+    const float2 *xn = xb + (int64_t)32 * Jn * u.ld;
+    if constexpr (NC == 32) {
+      float2 av = buf[kk * 32 + n];
 #pragma unroll
-  for (int v = 0; v < 16; ++v)
-    yb[(int64_t)(8 * (v >> 2) + 4 * kk + (v & 3)) * nr] =
-        make_float2(p1[v] - p2[v], p3[v] - p1[v] - p2[v]);
+      for (int s = 0; s < 16; ++s) {
+        const float2 ac = av;
+        if (s < 15) av = buf[(2 * (s + 1) + kk) * 32 + (n ^ (2 * ((s + 1) >> 1)))];
+        p1 = __builtin_amdgcn_mfma_f32_32x32x2f32(ac.x, x[s].x, p1, 0, 0, 0);
+        p2 = __builtin_amdgcn_mfma_f32_32x32x2f32(ac.y, x[s].y, p2, 0, 0, 0);
+        p3 = __builtin_amdgcn_mfma_f32_32x32x2f32(ac.x + ac.y, x[s].x + x[s].y, p3, 0, 0, 0);
+        x[s] = xn[s * xs];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      float2 av[2] = {buf[kk * 32 + n], buf[kk * 32 + 16 + n]};
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        const float2 ac[2] = {av[0], av[1]};
+        if (s < 7) {
+          av[0] = buf[(4 * (s + 1) + kk) * 32 + (n ^ (2 * (s + 1)))];
+          av[1] = buf[(4 * (s + 1) + kk) * 32 + ((16 + n) ^ (2 * (s + 1)))];
+        }
+        const float xsum = x[s].x + x[s].y;
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+          q1[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ac[rb].x, x[s].x, q1[rb], 0, 0, 0);
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+          q2[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ac[rb].y, x[s].y, q2[rb], 0, 0, 0);
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+          q3[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ac[rb].x + ac[rb].y, xsum, q3[rb], 0, 0, 0);
+        x[s] = xn[s * xs];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  if (n >= u.nc) return;
+  float2 *yb = yl + u.base + (int64_t)32 * I * u.ld + n;
+  if constexpr (NC == 32) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      yb[(int64_t)(8 * (v >> 2) + 4 * kk + (v & 3)) * u.ld] =
+          make_float2(p1[v] - p2[v], p3[v] - p1[v] - p2[v]);
+  } else {
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        yb[(int64_t)(16 * rb + 4 * kk + v) * u.ld] =
+            make_float2(q1[rb][v] - q2[rb][v], q3[rb][v] - q1[rb][v] - q2[rb][v]);
+  }
 }
 
-// FP64 form on the matrix cores (v_mfma_f64_16x16x4f64: lane l supplies
-// A[l%16][k] and B[k][l%16] for k = l/16 of each four-column step, and
-// receives result row 4v + l/16, column l%16 in element v).  A wave forms
-// Y_I as 2 x 2 blocks of 16 x 16, each complex product as four real ones
-// (the outer-iteration operator keeps full FP64 accuracy).  The tile A_IJ is
-// staged in LDS column by column (stride 33, double-buffered); X_J goes from
-// global memory straight into the B operands; the next tile and X_J are
-// loaded into a second register set while the current ones are multiplied
-// (one wave per SIMD, eight independent accumulators).
-__global__ __launch_bounds__(64) void k_rows_mfma64(const double2 *__restrict__ tiles,
-                                                    const int2 *__restrict__ rows, int64_t nrows,
-                                                    const int32_t *__restrict__ bn,
-                                                    const int64_t *__restrict__ ent_off,
-                                                    const int64_t *__restrict__ loc_off,
-                                                    const double2 *__restrict__ xl,
-                                                    double2 *__restrict__ yl, int nr) {
-  __shared__ double2 As[2][32 * 33];
-  const int64_t per = (nrows + 7) / 8;
-  const int64_t w = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (w >= nrows) return;
+__global__ __launch_bounds__(64, 3) void k_rows_mfma(const float2 *__restrict__ tiles,
+                                                     const int2 *__restrict__ rows,
+                                                     const ChunkMap cm,
+                                                     const HermGroup *__restrict__ grp,
+                                                     const float2 *__restrict__ xl,
+                                                     float2 *__restrict__ yl, int nr) {
+  __shared__ float2 buf[32 * 32];
+  const RowUnit u = row_unit(rows, cm, grp, nr);
+  if (!u.on) return;
+  if (u.nc <= 16) rows32<16>(u, tiles, xl, yl, buf);
+  else rows32<32>(u, tiles, xl, yl, buf);
+}
+
+// FP64 form (v_mfma_f64_16x16x4f64: lane l supplies A[l%16][k] and B[k][l%16]
+// for k = l/16 of each four-column step, and receives result row 4v + l/16,
+// column l%16 in element v).  One wave per unit: Y_I as 2 x (1 or 2) blocks of
+// 16 x 16, each complex product as four real ones (the outer-iteration operator
+// keeps full FP64 accuracy).  The tile A_IJ is staged in
+// LDS column by column (stride 33); X_J goes from global memory straight into
+// the B operands; registers are loaded again as soon as they are staged or
+// multiplied, as in the FP32 form (two waves per SIMD).
+template <int NC>
+__device__ __forceinline__ void rows64(const RowUnit &u, const double2 *__restrict__ tiles,
+                                       const double2 *__restrict__ xl, double2 *__restrict__ yl,
+                                       double2 *buf) {
+  constexpr int NB = NC == 32 ? 2 : 1;
   const int lane = threadIdx.x, a = lane >> 3, q = lane & 7;
-  const int li = lane & 15, lk = lane >> 4;
-  // columns past nr read column nr - 1; their results are not stored
-  const int c0 = li < nr ? li : nr - 1, c1 = 16 + li < nr ? 16 + li : nr - 1;
-  const int2 bi = rows[w];
-  const int b = bi.x, I = bi.y;
-  const int nt = (bn[b] + 31) >> 5;
-  const int64_t e0 = ent_off[b];
+  const int li = lane & 15, lk = lane >> 4, I = u.I, nt = u.nt;
+  // columns past nc read column nc - 1; their results are not stored
+  const int c0 = min(li, u.nc - 1), c1 = min(16 + li, u.nc - 1);
   // a diagonal tile stores the sub-blocks a <= q only (slot diag_slot(a, q))
   const bool dup = a <= q;
   const int dsl = dup ? diag_slot(a, q) : 0;
-  const double2 *xb = xl + loc_off[b] * nr;
-  auto load = [&](int J, double2 *tt, double2 *xx) {
+  const double2 *xb = xl + u.base;
+  double2 t[16], x[8 * NB];
+  auto load_tile = [&](int J) {
     // (wave-uniform branch, constant strides: immediate load offsets); lanes
     // below the diagonal of a diagonal tile read slot 0 (in range), their
     // values are not staged
     if (J != I) {
-      const double2 *tp = tiles + e0 + (J > I ? tile_entry(I, J) : tile_entry(J, I)) + lane;
+      const double2 *tp = tiles + u.ent + (J > I ? tile_entry(I, J) : tile_entry(J, I)) + lane;
 #pragma unroll
-      for (int k = 0; k < 16; ++k) tt[k] = tp[k * 64];
+      for (int k = 0; k < 16; ++k) t[k] = tp[k * 64];
     } else {
-      const double2 *tp = tiles + e0 + tile_entry(I, I) + dsl;
+      const double2 *tp = tiles + u.ent + tile_entry(I, I) + dsl;
 #pragma unroll
-      for (int k = 0; k < 16; ++k) tt[k] = tp[k * kDiagSlots];
-    }
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      const double2 *xr = xb + (int64_t)(32 * J + 4 * ks + lk) * nr;
-      xx[2 * ks] = xr[c0];
-      xx[2 * ks + 1] = xr[c1];
+      for (int k = 0; k < 16; ++k) t[k] = tp[k * kDiagSlots];
     }
   };
-  v4d are[2][2], aim[2][2];
+  auto load_x = [&](int J, int ks) {
+    const double2 *xr = xb + (int64_t)(32 * J + 4 * ks + lk) * u.ld;
+    x[NB * ks] = xr[c0];
+    if constexpr (NB == 2) x[2 * ks + 1] = xr[c1];
+  };
+  v4d are[2][NB], aim[2][NB];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < NB; ++j) {
       are[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
       aim[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
     }
-  auto step = [&](int J, int Jn, const double2 *t, const double2 *x, double2 *tn, double2 *xn) {
-    load(Jn, tn, xn);
-    __builtin_amdgcn_sched_barrier(0);
+  load_tile(0);
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) load_x(0, ks);
+#pragma unroll 1
+  for (int J = 0; J < nt; ++J) {
     const bool up = J >= I;
-    double2 *buf = As[J & 1];
     // the lane holds stored entries (4a + i, 4q + j) at 4i + j; A_IJ is the
     // stored tile (J >= I) or the conjugate transpose of tile (J, I)
     if (J != I) {
@@ -260,53 +322,69 @@ __global__ __launch_bounds__(64) void k_rows_mfma64(const double2 *__restrict__ 
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int Jn = min(J + 1, nt - 1);   // the loads after the last tile repeat it
+    load_tile(Jn);
+    __builtin_amdgcn_sched_barrier(0);
+    double2 an[2] = {buf[lk * 33 + li], buf[lk * 33 + 16 + li]};
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-      const int c = 4 * ks + lk;
-      const double2 ar[2] = {buf[c * 33 + li], buf[c * 33 + 16 + li]};
-      const double2 xv[2] = {x[2 * ks], x[2 * ks + 1]};
+      const double2 ar[2] = {an[0], an[1]};
+      if (ks < 7) {
+        const int c = 4 * (ks + 1) + lk;
+        an[0] = buf[c * 33 + li];
+        an[1] = buf[c * 33 + 16 + li];
+      }
+      double2 xv[NB];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) xv[j] = x[NB * ks + j];
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NB; ++j)
           are[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[i].x, xv[j].x, are[i][j], 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NB; ++j)
           aim[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[i].x, xv[j].y, aim[i][j], 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NB; ++j)
           are[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ar[i].y, xv[j].y, are[i][j], 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NB; ++j)
           aim[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[i].y, xv[j].x, aim[i][j], 0, 0, 0);
+      load_x(Jn, ks);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  double2 tA[16], xA[16], tB[16], xB[16];
-  load(0, tA, xA);
-  int J = 0;
-  for (; J + 1 < nt; J += 2) {
-    step(J, J + 1, tA, xA, tB, xB);
-    step(J + 1, J + 2 < nt ? J + 2 : J + 1, tB, xB, tA, xA);
   }
-  if (J < nt) step(J, J, tA, xA, tB, xB);
-  double2 *yb = yl + (loc_off[b] + 32 * I) * nr;
+  double2 *yb = yl + u.base + (int64_t)(32 * I) * u.ld;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < NB; ++j) {
       const int col = 16 * j + li;
-      if (col >= nr) continue;
+      if (col >= u.nc) continue;
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        yb[(int64_t)(16 * i + 4 * v + lk) * nr + col] = make_double2(are[i][j][v], aim[i][j][v]);
+        yb[(int64_t)(16 * i + 4 * v + lk) * u.ld + col] = make_double2(are[i][j][v], aim[i][j][v]);
     }
+}
+
+__global__ __launch_bounds__(64, 2) void k_rows_mfma64(const double2 *__restrict__ tiles,
+                                                       const int2 *__restrict__ rows,
+                                                       const ChunkMap cm,
+                                                       const HermGroup *__restrict__ grp,
+                                                       const double2 *__restrict__ xl,
+                                                       double2 *__restrict__ yl, int nr) {
+  __shared__ double2 buf[32 * 33];
+  const RowUnit u = row_unit(rows, cm, grp, nr);
+  if (!u.on) return;
+  if (u.nc <= 16) rows64<16>(u, tiles, xl, yl, buf);
+  else rows64<32>(u, tiles, xl, yl, buf);
 }
 
 // With FWD the result (d, k) also goes to the local rows of the next block
@@ -673,6 +751,44 @@ void HermBlockBufs::ensure(const HermSet &H, int nr, bool fp64, bool fp32, Budge
   cap = nr;
 }
 
+void HermBlockBufs::ensure_part(const HermSet &H, int nr, Budget *bud) {
+  const int64_t n = H.npart * std::min(nr, kUnitCols);
+  if (!H.t64.p || H.t32.p || H.gnunits64 > 0 || part64.n >= n) return;
+  if ((bud && bud->limit > 0) || n * 16 > 2000000000LL) return;
+  try {
+    part64.alloc(n, bud);
+  } catch (const DpgError &) {
+    (void)hipGetLastError();
+  }
+}
+
+template <typename T>
+void launch_rows(HermSet &H, const cplx_t<T> *xl, cplx_t<T> *yl, int nr, hipStream_t s) {
+  constexpr bool F64 = sizeof(T) == 8;
+  const int64_t *cw = H.nrow_w;
+  // chunk c: the units of the groups with more than 32 c columns
+  ChunkMap cm;
+  int64_t total = 0;
+  for (int c = 0; c < kMaxGroup; ++c) {
+    const int w = 32 * c / nr + 1;
+    if (w > kMaxGroup || cw[w] == 0) break;
+    cm.cnt[c] = (int32_t)cw[w];
+    total += cw[w];
+  }
+  const int64_t per = (total + 7) / 8;
+  if (8 * per > INT32_MAX) throw DpgError(-1, "block apply: too many tile rows");
+  cm.total = (int32_t)total;
+  ProfScope ps(H.prof, F64 ? DPG_K_APPLYB64 : DPG_K_APPLYB32,
+               8.0 * (double)H.full * nr, s);
+  if constexpr (F64)
+    hipLaunchKernelGGL(k_rows_mfma64, dim3((unsigned)(8 * per)), dim3(64), 0, s, H.t64.p, H.grow.p,
+                       cm, H.grp.p, xl, yl, nr);
+  else
+    hipLaunchKernelGGL(k_rows_mfma, dim3((unsigned)(8 * per)), dim3(64), 0, s, H.t32.p, H.grow.p,
+                       cm, H.grp.p, xl, yl, nr);
+  LAUNCH_OK();
+}
+
 template <typename T, int MODE>
 void launch_scatter_blk(const HermSet &H, int nr, const cplx_t<T> *yl, const cplx_t<T> *R,
                         cplx_t<T> *Y, T theta, const HermSet *fwd, cplx_t<T> *fxl,
@@ -722,22 +838,16 @@ void herm_apply_blk(HermSet &H, HermBlockBufs &W, const cplx_t<T> *X, cplx_t<T> 
                        nr, H.gidx.p, X, xl);
     LAUNCH_OK();
   }
-  {
-    ProfScope ps(H.prof, sizeof(T) == 8 ? DPG_K_APPLYB64 : DPG_K_APPLYB32,
-                 8.0 * (double)H.full * nr, s);
-    if constexpr (sizeof(T) == 4) {
-      const int64_t per = (H.nrows + 7) / 8;
-      if (8 * per > INT32_MAX) throw DpgError(-1, "block apply: too many tile rows");
-      hipLaunchKernelGGL(k_rows_mfma, dim3((unsigned)(8 * per)), dim3(64), 0, s, tiles, H.rows.p,
-                         H.nrows, H.bn.p, H.ent_off.p, H.loc_off.p, xl, yl, nr);
-    } else {
-      const int64_t per = (H.nrows + 7) / 8;
-      if (8 * per > INT32_MAX) throw DpgError(-1, "block apply: too many tile rows");
-      hipLaunchKernelGGL(k_rows_mfma64, dim3((unsigned)(8 * per)), dim3(64), 0, s, tiles,
-                         H.rows.p, H.nrows, H.bn.p, H.ent_off.p, H.loc_off.p, xl, yl, nr);
+  bool rows = true;
+  if constexpr (sizeof(T) == 8) {
+    // not in mixed precision, whose solutions feel the last bit of the outer
+    // iteration
+    if (nr <= kUnitCols && H.gnunits64 == 0 && !H.t32.p && W.part64.n >= H.npart * nr) {
+      launch_units_cols(H, xl, W.part64.p, yl, nr, s);
+      rows = false;
     }
-    LAUNCH_OK();
   }
+  if (rows) launch_rows<T>(H, xl, yl, nr, s);
   ProfScope ps(H.prof, DPG_K_REDUCE, 0.0, s);
   switch (mode) {
     case RED_SET: launch_scatter_blk<T, RED_SET>(H, nr, yl, R, Y, theta, fwd, fxl, s); break;
@@ -892,6 +1002,8 @@ void cgb_update_p(int64_t n, int nr, double2 *p, const double2 *z, const double 
   LAUNCH_OK();
 }
 
+template void launch_rows<double>(HermSet &, const double2 *, double2 *, int, hipStream_t);
+template void launch_rows<float>(HermSet &, const float2 *, float2 *, int, hipStream_t);
 template void herm_apply_blk<double>(HermSet &, HermBlockBufs &, const double2 *, double2 *,
                                      const double2 *, int, double, int, hipStream_t, bool,
                                      HermSet *, HermBlockBufs *);

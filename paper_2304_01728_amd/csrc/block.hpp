@@ -23,7 +23,21 @@ struct HermBlockBufs {
   // local vectors zeroed when allocated: a forward (below) writes only the
   // rows a vector entry maps to
   void ensure(const HermSet &H, int nr, bool fp64, bool fp32, Budget *bud, hipStream_t s);
+  // Partials for at most kUnitCols columns (launch_units_cols): up to 2 GB a
+  // set, and none under a memory budget, which they must not use up; without
+  // them a block apply goes through launch_rows, which needs none.
+  DevBuf<double2> part64;
+  void ensure_part(const HermSet &H, int nr, Budget *bud);
 };
+
+// Up to this many FP64 columns of a set without groups, each tile is read once
+// for all of them (launch_units_cols, bound by HBM); beyond, the tile rows go to
+// the matrix cores (launch_rows), which read every tile twice.  12^3, p = 3,
+// varying medium, FP64 solve with 2 / 4 / 6 / 8 columns: 25 / 31 / 39 / 48 ms by
+// units, about 46 ms by rows.  The tiles of groups come from caches, there the
+// rows are faster (16^3, p = 3, uniform medium, 2 / 3 columns: 34 / 44 ms against
+// 41 / 53).
+constexpr int kUnitCols = 7;
 
 // Y <- epilogue(sum_b R_b^T A_b R_b X) for nr columns (modes as herm_apply).
 // gathered: W already holds the local rows of X (a previous application
@@ -33,6 +47,11 @@ struct HermBlockBufs {
 // may hold stale finite values from another width; they meet only the zero
 // padding of the tiles.  One column goes through herm_apply (the single-
 // vector local vectors of the sets).
+// The products of the blocks with nr local vectors each (the columns of a group
+// together, see HermGroup) on the matrix cores: yl = A xl.
+template <typename T>
+void launch_rows(HermSet &H, const cplx_t<T> *xl, cplx_t<T> *yl, int nr, hipStream_t s);
+
 template <typename T>
 void herm_apply_blk(HermSet &H, HermBlockBufs &W, const cplx_t<T> *X, cplx_t<T> *Y,
                     const cplx_t<T> *R, int mode, T theta, int nr, hipStream_t s,

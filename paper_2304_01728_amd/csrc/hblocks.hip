@@ -1,7 +1,9 @@
 // Hermitian block sets: packing and apply kernels (see hblocks.hpp).
 #include <algorithm>
-#include <numeric>
+#include <cstring>
+#include <map>
 
+#include "block.hpp"
 #include "hblocks.hpp"
 #include "kernels.hpp"
 
@@ -166,6 +168,7 @@ __host__ __device__ __forceinline__ int64_t row_slot(int nt, int I, int J) {
 // tiles), which pays in FP32, where they weigh twice as much against the
 // tiles; FP64 streams its 16 KB tiles faster as segments.
 constexpr int kChunk = 4;
+constexpr int kStripBlocks = 4;   // blocks of a group per wave (k_strips_grp)
 
 // Row-sum slots of a block with nt tile columns (ns = ceil(nt / 2) strips):
 // row I is covered by the strips s >= I / 2, its slots are contiguous, and
@@ -257,6 +260,87 @@ __global__ __launch_bounds__(256) void k_units(const cplx_t<T> *__restrict__ til
     cacc[j] = cadd(cacc[j], shfl_xor_c(cacc[j], 32));
   }
   if (ra < 4) part[d1.z + 4 * cb + ra] = sel4(cacc[0], cacc[1], cacc[2], cacc[3], ra);
+}
+
+// The units of a group's blocks (a group's local vectors are interleaved: row i
+// of block m at i gw + m): both tiles are loaded once for all blocks, from a
+// cache except for the first group of its class, and every block gets the
+// arithmetic of k_units in the same order, so the partials are bit for bit the
+// same.  Bound by the vector units and the cross-lane sums, about 1000 cycles per
+// block and tile against 7300 for the tile's 16 KB at a SIMD's share of the HBM
+// rate.  The x entries of the next block are loaded while one is multiplied.
+// The nr right-hand sides of a block alone are taken like the blocks of a group
+// (column k at i nr + k); its tiles are read once per application (NT: past the
+// caches).
+template <typename T, bool NT>
+__global__ __launch_bounds__(256, 2) void k_units_grp(const cplx_t<T> *__restrict__ tiles,
+                                                      const int4 *__restrict__ units,
+                                                      int64_t nunits, int nr,
+                                                      const cplx_t<T> *__restrict__ xloc,
+                                                      cplx_t<T> *__restrict__ part) {
+  using C = cplx_t<T>;
+  __shared__ C xs[4][kSeg * 32];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t per = gridDim.x / 8, wg = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+  const int64_t wv = wg * 4 + wave;
+  if (wv >= nunits) return;
+  const int lane = threadIdx.x & 63, ra = lane >> 3, cb = lane & 7;
+  const int4 d0 = units[3 * wv], d1 = units[3 * wv + 1], d2 = units[3 * wv + 2];
+  const int each = d2.x, gw = (d1.w >> 8) * nr;
+  const int64_t ent = (int64_t)(uint32_t)d0.x | ((int64_t)d0.y << 32);
+  part += (int64_t)d2.y * (nr - 1);   // slots of the block vectors before this group's
+  const bool two = d1.w & 1, off0 = d1.w & 2, off1 = d1.w & 4;
+  const bool upper = ra <= cb, strict = ra < cb;
+  const C *tp = tiles + ent;
+  C t0[16], t1[16], xJ[4];
+  const int ds = upper ? diag_slot(ra, cb) : 0;
+  const int s0 = off0 ? 64 : kDiagSlots, s1 = off1 ? 64 : kDiagSlots;
+  const C *p0 = tp + (off0 ? lane : ds), *p1 = tp + kTileFull + (off1 ? lane : ds);
+#pragma unroll
+  for (int k = 0; k < 16; ++k) t0[k] = NT ? ld_nt(p0 + k * s0) : p0[k * s0];
+  if (two) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) t1[k] = NT ? ld_nt(p1 + k * s1) : p1[k * s1];
+  }
+  const int nx = 32 * (1 + two);
+  const C *xi = xloc + (int64_t)d0.z * nr + min(lane, nx - 1) * gw;
+  const C *xj = xloc + (int64_t)d0.w * nr + 4 * cb * gw;
+  C v = xi[0];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) xJ[j] = xj[j * gw];
+  if (!off0) mask_lower(upper, t0);
+  if (two && !off1) mask_lower(upper, t1);
+  C *xw = xs[wave];
+#pragma unroll 1
+  for (int m = 0; m < gw; ++m) {
+    C w, cacc[4], xc[4];
+    w.x = lane < nx ? v.x : 0;
+    w.y = lane < nx ? v.y : 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    xw[lane] = w;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int mn = min(m + 1, gw - 1);
+    v = xi[mn];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      xc[j] = xJ[j];
+      xJ[j] = xj[j * gw + mn];
+      cacc[j] = czero<C>();
+    }
+    C *pm = part + (int64_t)m * each;
+    do_tile(t0, xc, xw, off0 || strict, ra, cb, cacc, pm + d1.x);
+    if (two) do_tile(t1, xc, xw + 32, off1 || strict, ra, cb, cacc, pm + d1.x + d1.y);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      cacc[j] = cadd(cacc[j], shfl_xor_c(cacc[j], 8));
+      cacc[j] = cadd(cacc[j], shfl_xor_c(cacc[j], 16));
+      cacc[j] = cadd(cacc[j], shfl_xor_c(cacc[j], 32));
+    }
+    if (ra < 4) pm[d1.z + 4 * cb + ra] = sel4(cacc[0], cacc[1], cacc[2], cacc[3], ra);
+  }
 }
 
 // One wave per (block, strip s, chunk of tile rows [Ia, Ib)).  The unit's
@@ -363,13 +447,132 @@ __global__ __launch_bounds__(256) void k_strips(const cplx_t<T> *__restrict__ ti
   }
 }
 
+// The strips of up to kStripBlocks equal blocks (a group's local vectors are
+// interleaved: row i of block m at i gw + m): each pair of tiles is loaded once
+// for all of them, from a cache except for the first group of its class, and
+// every block gets the arithmetic of k_strips in the same order, so the partials
+// are bit for bit the same.  Bound by the vector units: 128 multiply-adds per
+// tile, entry of a lane and block, about 600 cycles per block and tile against
+// 3660 for the tile's 8 KB at a SIMD's share of the HBM rate.  Four blocks (16
+// column sums and 16 x entries each) fill the 256 registers of two waves per SIMD.
+template <typename T>
+__global__ __launch_bounds__(256, 2) void k_strips_grp(const cplx_t<T> *__restrict__ tiles,
+                                                       const int4 *__restrict__ units,
+                                                       int64_t nunits,
+                                                       const cplx_t<T> *__restrict__ xloc,
+                                                       cplx_t<T> *__restrict__ part) {
+  using C = cplx_t<T>;
+  constexpr int G = kStripBlocks;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t per = gridDim.x / 8, wg = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+  const int64_t wv = wg * 4 + wave;
+  if (wv >= nunits) return;
+  const int lane = threadIdx.x & 63, ra = lane >> 3, cb = lane & 7;
+  const int4 d0 = units[3 * wv], d1 = units[3 * wv + 1];
+  const int each = units[3 * wv + 2].x;
+  const int64_t ent = (int64_t)(uint32_t)d0.x | ((int64_t)d0.y << 32);
+  const int cnt = d0.w & 0xff, gw = d0.w >> 8;
+  const int J0 = d1.x & 0xffff, nt = d1.x >> 16, J1 = J0 + 1;
+  const int Ia = d1.y & 0xffff, Ib = d1.y >> 16;
+  const bool two = J1 < nt;
+  const int ns = (nt + 1) >> 1, s = J0 >> 1;
+  const bool upper = ra <= cb, strict = ra < cb;
+  const int ds = upper ? diag_slot(ra, cb) : 0;
+  const C *t0 = tiles + ent;                                   // tile (0, J0)
+  const C *t1 = two ? t0 + (int64_t)kTileFull * J0 + kTileDiag : t0;   // tile (0, J1)
+  const C *xb = xloc + d0.z;
+  C xJ0[G][4], xJ1[G][4], c0[G][4], c1[G][4];
+#pragma unroll
+  for (int m = 0; m < G; ++m) {
+    const int mc = min(m, cnt - 1);   // blocks past cnt repeat the last one, unused
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      xJ0[m][j] = xb[(32 * J0 + 4 * cb + j) * gw + mc];
+      xJ1[m][j] = xb[(32 * (two ? J1 : J0) + 4 * cb + j) * gw + mc];
+      c0[m][j] = czero<C>();
+      c1[m][j] = czero<C>();
+    }
+  }
+#pragma unroll 1
+  for (int I = Ia; I < Ib; ++I) {
+    const bool fa = I < J0, fb = two && I < J1;
+    const bool ka = fa || (I == J0 && upper), kb = fb || (two && I == J1 && upper);
+    const C *pa = fa ? t0 + (int64_t)kTileFull * I + lane : t0 + (int64_t)kTileFull * J0 + ds;
+    const C *pb = fb ? t1 + (int64_t)kTileFull * I + lane
+                     : two ? t1 + (int64_t)kTileFull * J1 + ds : t0 + (int64_t)kTileFull * J0 + ds;
+    const int sa = fa ? 64 : kDiagSlots, sb = fb ? 64 : kDiagSlots;
+    C ta[16], tb[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) ta[k] = pa[k * sa];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) tb[k] = pb[k * sb];
+    mask_lower(ka, ta);
+    mask_lower(kb, tb);
+#pragma unroll
+    for (int m = 0; m < G; ++m) {
+      if (m >= cnt) break;
+      C xI[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) xI[i] = xb[(32 * I + 4 * ra + i) * gw + m];
+      C rs[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        C a = czero<C>();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a = cfma(ta[4 * i + j], xJ0[m][j], a);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a = cfma(tb[4 * i + j], xJ1[m][j], a);
+        rs[i] = a;
+      }
+      C xa[4], xbb[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        xa[i] = csel(fa || strict, xI[i], czero<C>());
+        xbb[i] = csel(fb || strict, xI[i], czero<C>());
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          c0[m][j] = cfmaconj(ta[4 * i + j], xa[i], c0[m][j]);
+          c1[m][j] = cfmaconj(tb[4 * i + j], xbb[i], c1[m][j]);
+        }
+      const C v = rowsum_scatter(rs, cb);
+      if (!(cb & 1))
+        part[d1.w + m * each + 32 * strip_row_slot(ns, I, s) + 4 * ra + (cb >> 1)] = v;
+    }
+  }
+  const int nc = (min(2 * s + 2, nt) + kChunk - 1) / kChunk;   // chunks of the strip
+#pragma unroll
+  for (int m = 0; m < G; ++m) {
+    if (m >= cnt) break;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      c0[m][j] = cadd(c0[m][j], shfl_xor_c(c0[m][j], 8));
+      c0[m][j] = cadd(c0[m][j], shfl_xor_c(c0[m][j], 16));
+      c0[m][j] = cadd(c0[m][j], shfl_xor_c(c0[m][j], 32));
+      c1[m][j] = cadd(c1[m][j], shfl_xor_c(c1[m][j], 8));
+      c1[m][j] = cadd(c1[m][j], shfl_xor_c(c1[m][j], 16));
+      c1[m][j] = cadd(c1[m][j], shfl_xor_c(c1[m][j], 32));
+    }
+    if (ra < 4) {
+      C *pc = part + d1.z + m * each + 4 * cb + ra;
+      pc[0] = sel4(c0[m][0], c0[m][1], c0[m][2], c0[m][3], ra);
+      if (two) pc[32 * nc] = sel4(c1[m][0], c1[m][1], c1[m][2], c1[m][3], ra);
+    }
+  }
+}
+
 // Half a wave per (block, tile row I): y_loc rows of I = column sums of the
 // segments of tile column I + row sums of tiles (I, J >= I).  The row's
 // descriptor (rowd, see HermSet::build) gives both partial bases and counts
 // with one load.  The slots are independent loads: eight are in flight per
 // lane (a row of a 24-tile block sums 25 slots), summed in a fixed order.
+// With nr right-hand sides, blockIdx.y is the column and rowb gives {first
+// slot of the block, slots of the block}.
 template <typename T>
-__global__ __launch_bounds__(256) void k_rows(const int4 *__restrict__ rowd, int64_t nrows,
+__global__ __launch_bounds__(256) void k_rows(const int4 *__restrict__ rowd,
+                                              const int2 *__restrict__ rowb, int64_t nrows, int nr,
                                               const cplx_t<T> *__restrict__ part,
                                               cplx_t<T> *__restrict__ yl) {
   using C = cplx_t<T>;
@@ -378,9 +581,10 @@ __global__ __launch_bounds__(256) void k_rows(const int4 *__restrict__ rowd, int
   if (hw >= nrows) return;
   const int r = threadIdx.x & 31;
   const int4 d = rowd[hw];
+  if (nr > 1) part += (int64_t)rowb[hw].x * (nr - 1) + (int64_t)rowb[hw].y * blockIdx.y;
   const C *cp = part + d.x + r;
   const C *rp = part + d.y + r;
-  const int nseg = d.z & 0xffff, tot = nseg + (d.z >> 16);
+  const int nseg = d.z & 0xfff, tot = nseg + (d.z >> 12 & 0xfff);
   C acc[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -403,7 +607,7 @@ __global__ __launch_bounds__(256) void k_rows(const int4 *__restrict__ rowd, int
   for (int w = U / 2; w >= 1; w /= 2)
 #pragma unroll
     for (int u = 0; u < w; ++u) acc[u] = cadd(acc[u], acc[u + w]);
-  yl[d.w + r] = acc[0];
+  yl[(int64_t)(d.w + r * (d.z >> 24)) * nr + blockIdx.y] = acc[0];
 }
 
 // With FWD the result of entry d is also written to every local row of the
@@ -469,19 +673,20 @@ __global__ __launch_bounds__(256) void k_pack(const int4 *__restrict__ tdesc, in
 
 void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t> &idx_concat,
                     int64_t nvec_, bool fp64, bool fp32, Budget *bud, hipStream_t s,
-                    const std::vector<int32_t> *cls) {
+                    const std::vector<int32_t> *cls, bool grouping) {
   nblk = (int)sizes.size();
   nvec = nvec_;
   n_h = sizes;
-  std::vector<int64_t> toff, ceoff, eoff(nblk), cpo(nblk), rpo(nblk), loff(nblk);
+  std::vector<int64_t> toff, ceoff, eoff(nblk), cpo(nblk), rpo(nblk), loff(nblk), idx0(nblk);
+  std::vector<std::vector<int32_t>> members;   // blocks of each class
   int64_t t = 0, p = 0, lo = 0, ii = 0;
   nent = 0;
   packed = 0;
   full = 0;
+  full_grouped = 0;
   std::vector<int4> un;
   std::vector<int2> rw;
   std::vector<int4> td;
-  std::vector<int32_t> gi;
   for (int b = 0; b < nblk; ++b) {
     const int n = sizes[b], nt = (n + 31) / 32;
     const int cl = cls ? (*cls)[b] : b;
@@ -491,25 +696,89 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
       ceoff.push_back(nent);
       t += (int64_t)nt * (nt + 1) / 2;
       nent += tile_entry(0, nt);
-      packed += (int64_t)n * (n + 1) / 2;
+      members.emplace_back();
     }
     eoff[b] = ceoff[cl];
-    cpo[b] = p;
-    p += colbase(nt);
-    rpo[b] = p;
-    p += (int64_t)nt * (nt + 1) / 2 * 32;
-    loff[b] = lo;
-    lo += (int64_t)nt * 32;
+    members[cl].push_back(b);
+    idx0[b] = ii;
     full += (int64_t)n * n;
-    for (int i = 0; i < 32 * nt; ++i) gi.push_back(i < n ? idx_concat[ii + i] : -1);
     ii += n;
-    for (int J = 0; J < nt; ++J) {
-      for (int seg = 0; seg * kSeg <= J; ++seg) un.push_back(make_int4(b, J, seg * kSeg, seg));
-      rw.push_back(make_int2(b, J));
-      for (int I = 0; first && I <= J; ++I) td.push_back(make_int4(b, I, J, 0));
-    }
+    for (int J = 0; first && J < nt; ++J)
+      for (int I = 0; I <= J; ++I) td.push_back(make_int4(b, I, J, 0));
   }
   if (ii != (int64_t)idx_concat.size()) throw DpgError(-1, "HermSet: index list size mismatch");
+  // groups: the members of a class in about equal parts of at most kMaxGroup
+  // (in block order, so that the columns of a group are mostly neighbours of
+  // one another), stored widest first.  A wave takes its blocks of a group one
+  // after the other, so the groups are no wider than leaves two waves per SIMD
+  // (2048) to run (8^3 order levels: solve 15.6 ms with each block alone, 21.2
+  // ms in groups of 32).
+  struct Part { std::vector<int32_t> m; HermGroup g; };
+  std::vector<Part> parts;
+  auto cut = [&](int most) {
+    parts.clear();
+    int64_t waves = 0;
+    for (size_t k = 0; k < members.size(); ++k) {
+      const int cnt = (int)members[k].size(), np = (cnt + most - 1) / most;
+      const int nt = (sizes[members[k][0]] + 31) / 32;
+      int64_t w = 0;
+      for (int J = 0; J < nt; ++J) w += J / kSeg + 1;
+      if (fp32) {
+        w = 0;
+        for (int st = 0; 2 * st < nt; ++st) w += strip_chunks(nt, st);
+      }
+      for (int q = 0; q < np; ++q) {
+        const int m0 = (int)((int64_t)cnt * q / np), m1 = (int)((int64_t)cnt * (q + 1) / np);
+        parts.push_back({{members[k].begin() + m0, members[k].begin() + m1},
+                         {ceoff[k], 0, m1 - m0, nt, 0}});
+        waves += w * (fp32 ? (m1 - m0 + kStripBlocks - 1) / kStripBlocks : 1);
+      }
+    }
+    return waves;
+  };
+  for (int most = grouping ? kMaxGroup : 1; cut(most) < 2048 && most > 1;) most /= 2;
+  std::stable_sort(parts.begin(), parts.end(),
+                   [](const Part &x, const Part &y) { return x.g.gw > y.g.gw; });
+  std::vector<HermGroup> gs;
+  std::vector<int2> gr;
+  std::fill(std::begin(nrow_w), std::end(nrow_w), 0);
+  std::vector<int32_t> alone, step(nblk, 1);   // blocks that are a group of their own
+  for (Part &q : parts) {
+    HermGroup &g = q.g;
+    if (lo + (int64_t)g.nt * 32 * g.gw >= (1LL << 31))
+      throw DpgError(-1, "HermSet: partial or local vectors beyond 32-bit offsets");
+    g.base = (int32_t)lo;
+    for (int m = 0; m < g.gw; ++m) {
+      loff[q.m[m]] = lo + m;
+      step[q.m[m]] = g.gw;
+    }
+    lo += (int64_t)g.nt * 32 * g.gw;
+    for (int I = 0; I < g.nt; ++I) gr.push_back(make_int2((int)gs.size(), I));
+    for (int w = 0; w <= g.gw; ++w) nrow_w[w] += g.nt;
+    if (g.gw == 1) alone.push_back(q.m[0]);
+    else full_grouped += (int64_t)g.gw * sizes[q.m[0]] * sizes[q.m[0]];
+    gs.push_back(g);
+  }
+  std::sort(alone.begin(), alone.end());
+  std::vector<int32_t> gi(lo, -1);
+  for (int b = 0; b < nblk; ++b)
+    for (int i = 0; i < sizes[b]; ++i) gi[loff[b] + (int64_t)i * step[b]] = idx_concat[idx0[b] + i];
+  for (const Part &q : parts)
+    for (int32_t b : q.m) {
+      const int nt = q.g.nt;
+      cpo[b] = p;
+      p += colbase(nt);
+      rpo[b] = p;
+      p += (int64_t)nt * (nt + 1) / 2 * 32;
+    }
+  for (int b = 0; b < nblk; ++b)
+    for (int J = 0; 32 * J < sizes[b]; ++J) rw.push_back(make_int2(b, J));
+  for (int32_t b : alone) {
+    const int n = sizes[b], nt = (n + 31) / 32;
+    packed += (int64_t)n * (n + 1) / 2;
+    for (int J = 0; J < nt; ++J)
+      for (int seg = 0; seg * kSeg <= J; ++seg) un.push_back(make_int4(b, J, seg * kSeg, seg));
+  }
   // units in block order (block, tile column, segment): the waves of
   // neighbouring workgroups stream neighbouring tiles (longest first, the
   // blocks mixed, was 1.3 % slower at 16^3, shuffled slower still)
@@ -517,6 +786,35 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
   npart = p;
   nloc = lo;
   nunits = (int64_t)un.size();
+  // of groups (group, tile column, segment): as below with the first block's
+  // offsets, flags | blocks << 8, and {slots of a block, first slot of the
+  // group, 0, 0}; the blocks that are a group of their own at the end
+  std::vector<int4> gud64;
+  gnunits64 = 0;
+  for (const Part &q : parts) {
+    if (!fp64) break;
+    const int nt = q.g.nt, b = q.m[0];
+    const int64_t each = colbase(nt) + (int64_t)nt * (nt + 1) / 2 * 32;
+    for (int J = 0; J < nt; ++J)
+      for (int I0 = 0; I0 <= J; I0 += kSeg) {
+        const int64_t tile = q.g.ent + tile_entry(I0, J);
+        const int64_t rd = I0 + 1 <= J ? row_slot(nt, I0 + 1, J) - row_slot(nt, I0, J) : 0;
+        const int flags = (I0 + 1 <= J ? 1 : 0) | (I0 < J ? 2 : 0) | (I0 + 1 < J ? 4 : 0);
+        gud64.push_back(make_int4((int)(uint32_t)(tile & 0xffffffff), (int)(tile >> 32),
+                                  (int)(loff[b] + (int64_t)32 * I0 * q.g.gw),
+                                  (int)(loff[b] + (int64_t)32 * J * q.g.gw)));
+        gud64.push_back(make_int4((int)(rpo[b] + row_slot(nt, I0, J)), (int)rd,
+                                  (int)(cpo[b] + colbase(J) + I0 / kSeg * 32), flags | q.g.gw << 8));
+        gud64.push_back(make_int4((int)each, (int)cpo[b], 0, 0));
+      }
+    if (q.g.gw > 1) gnunits64 = (int64_t)gud64.size() / 3;
+  }
+  gall64 = (int64_t)gud64.size() / 3;
+  std::vector<int2> rb;
+  for (const int2 &k : rw) {
+    const int b = k.x, nt = (sizes[b] + 31) / 32;
+    rb.push_back(make_int2((int)cpo[b], (int)(colbase(nt) + (int64_t)nt * (nt + 1) / 2 * 32)));
+  }
   if (npart >= (1LL << 31) || nloc >= (1LL << 31))
     throw DpgError(-1, "HermSet: partial or local vectors beyond 32-bit offsets");
   // unit descriptors: {entry offset of tile (I0, J) lo, hi, x offset of tile
@@ -541,36 +839,42 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
   for (size_t k = 0; k < rw.size(); ++k) {
     const int b = rw[k].x, I = rw[k].y, nt = (sizes[b] + 31) / 32;
     const int nseg = (I + kSeg) / kSeg, nrw = nt - I;
-    if (nseg > 0xffff || nrw > 0x7fff) throw DpgError(-1, "HermSet: block too large for row descriptors");
+    if (nt > 0xfff) throw DpgError(-1, "HermSet: block too large for row descriptors");
     rd[k] = make_int4((int)(cpo[b] + colbase(I)), (int)(rpo[b] + row_slot(nt, I, I)),
-                      nseg | (nrw << 16), (int)(loff[b] + 32 * I));
+                      nseg | nrw << 12 | step[b] << 24, (int)(loff[b] + (int64_t)32 * I * step[b]));
   }
   // FP32: units (block, strip, chunk), in that order: {entry offset of
   // tile (0, J0) lo, hi, x offset of the block, row-sum base of the block},
   // {J0 | nt << 16, Ia | Ib << 16, column-sum slot of J0, of J1 (0 without
-  // J1)}; rows: the column sums of tile column I (one slot per chunk of its
-  // strip) and the row sums of tile row I (one slot per strip s >= I / 2)
-  std::vector<int4> sud, srd;
+  // J1)}; of groups (up to four blocks, strip, chunk): {entry offset lo, hi, x
+  // offset of the first block, blocks | row step << 8}, {J0 | nt << 16, Ia |
+  // Ib << 16, column-sum slot of J0 of the first block, its row-sum base},
+  // {step of the slots from block to block, 0, 0, 0}; rows: the column sums of
+  // tile column I (one slot per chunk of its strip) and the row sums of tile
+  // row I (one slot per strip s >= I / 2)
+  std::vector<int4> sud, gud, srd;
   if (fp32) {
-    struct Unit { int4 d0, d1; };
-    std::vector<Unit> su;
     std::vector<int64_t> scpo(nblk), srpo(nblk);
-    std::vector<std::vector<int32_t>> cbase(nblk);
+    std::map<int, std::vector<int32_t>> cbase;   // by tile count
     int64_t sp = 0;
-    for (int b = 0; b < nblk; ++b) {
-      const int nt = (sizes[b] + 31) / 32;
-      if (nt > 0x7fff) throw DpgError(-1, "HermSet: block too large for strip descriptors");
-      std::vector<int32_t> &cbv = cbase[b];
-      cbv.assign(nt + 1, 0);
-      for (int J = 0; J < nt; ++J) cbv[J + 1] = cbv[J] + strip_chunks(nt, J / 2);
-      scpo[b] = sp;
-      sp += 32LL * cbv[nt];
-      srpo[b] = sp;
-      sp += 32 * strip_row_slots(nt);
+    for (const Part &q : parts) {
+      const int nt = q.g.nt;
+      if (nt > 0xfff) throw DpgError(-1, "HermSet: block too large for strip descriptors");
+      std::vector<int32_t> &cbv = cbase[nt];
+      if (cbv.empty()) {
+        cbv.assign(nt + 1, 0);
+        for (int J = 0; J < nt; ++J) cbv[J + 1] = cbv[J] + strip_chunks(nt, J / 2);
+      }
+      for (int32_t b : q.m) {
+        scpo[b] = sp;
+        sp += 32LL * cbv[nt];
+        srpo[b] = sp;
+        sp += 32 * strip_row_slots(nt);
+      }
     }
     snpart = sp;
     if (snpart >= (1LL << 31)) throw DpgError(-1, "HermSet: partials beyond 32-bit offsets");
-    for (int b = 0; b < nblk; ++b) {
+    for (int32_t b : alone) {
       const int nt = (sizes[b] + 31) / 32;
       for (int st = 0; 2 * st < nt; ++st) {
         const int J0 = 2 * st, J1 = J0 + 1, rws = strip_rows(nt, st);
@@ -578,29 +882,40 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
         const int64_t tile = eoff[b] + tile_entry(0, J0);
         for (int c = 0; c * kChunk < rws; ++c) {
           const int Ia = c * kChunk, Ib = std::min(rws, Ia + kChunk);
-          Unit u;
-          u.d0 = make_int4((int)(uint32_t)(tile & 0xffffffff), (int)(tile >> 32), (int)loff[b],
-                           (int)srpo[b]);
-          u.d1 = make_int4(J0 | (nt << 16), Ia | (Ib << 16),
-                           (int)(scpo[b] + 32LL * (cbase[b][J0] + c)),
-                           two ? (int)(scpo[b] + 32LL * (cbase[b][J1] + c)) : 0);
-          su.push_back(u);
+          sud.push_back(make_int4((int)(uint32_t)(tile & 0xffffffff), (int)(tile >> 32),
+                                  (int)loff[b], (int)srpo[b]));
+          sud.push_back(make_int4(J0 | (nt << 16), Ia | (Ib << 16),
+                                  (int)(scpo[b] + 32LL * (cbase[nt][J0] + c)),
+                                  two ? (int)(scpo[b] + 32LL * (cbase[nt][J1] + c)) : 0));
         }
       }
     }
-    snunits = (int64_t)su.size();
-    sud.resize(2 * su.size());
-    for (size_t k = 0; k < su.size(); ++k) {
-      sud[2 * k] = su[k].d0;
-      sud[2 * k + 1] = su[k].d1;
+    for (const Part &q : parts) {
+      if (q.g.gw == 1) continue;
+      const int nt = q.g.nt, np = (q.g.gw + kStripBlocks - 1) / kStripBlocks;
+      const int64_t each = 32LL * (cbase[nt][nt] + strip_row_slots(nt));
+      for (int st = 0; 2 * st < nt; ++st)
+        for (int c = 0; c * kChunk < strip_rows(nt, st); ++c)
+          for (int u = 0; u < np; ++u) {   // blocks m0 .. m1 - 1 of the group
+            const int m0 = q.g.gw * u / np, m1 = q.g.gw * (u + 1) / np, b = q.m[m0];
+            const int64_t tile = q.g.ent + tile_entry(0, 2 * st);
+            gud.push_back(make_int4((int)(uint32_t)(tile & 0xffffffff), (int)(tile >> 32),
+                                    (int)loff[b], (m1 - m0) | q.g.gw << 8));
+            gud.push_back(make_int4(2 * st | (nt << 16),
+                                    c * kChunk | std::min(strip_rows(nt, st), (c + 1) * kChunk) << 16,
+                                    (int)(scpo[b] + 32LL * (cbase[nt][2 * st] + c)), (int)srpo[b]));
+            gud.push_back(make_int4((int)each, 0, 0, 0));
+          }
     }
-    srd.resize(rw.size());
-    for (size_t k = 0; k < rw.size(); ++k) {
-      const int b = rw[k].x, I = rw[k].y, nt = (sizes[b] + 31) / 32, ns = (nt + 1) / 2;
+    snunits = (int64_t)sud.size() / 2;
+    gnunits = (int64_t)gud.size() / 3;
+    for (const int2 &k : rw) {
+      const int b = k.x, I = k.y, nt = (sizes[b] + 31) / 32, ns = (nt + 1) / 2;
       const int nseg = strip_chunks(nt, I / 2), nrw = ns - I / 2;
-      srd[k] = make_int4((int)(scpo[b] + 32LL * cbase[b][I]),
-                         (int)(srpo[b] + 32 * strip_row_slot(ns, I, I / 2)), nseg | (nrw << 16),
-                         (int)(loff[b] + 32 * I));
+      srd.push_back(make_int4((int)(scpo[b] + 32LL * cbase[nt][I]),
+                              (int)(srpo[b] + 32 * strip_row_slot(ns, I, I / 2)),
+                              nseg | nrw << 12 | step[b] << 24,
+                              (int)(loff[b] + (int64_t)32 * I * step[b])));
     }
   }
   tile_off_h = toff;
@@ -615,20 +930,37 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
   for (int64_t d = 0; d < nvec; ++d) cnt[d + 1] += cnt[d];
   std::vector<int32_t> ent(cnt[nvec]);
   std::vector<int32_t> fill(cnt.begin(), cnt.end() - 1);
-  for (int64_t k = 0; k < (int64_t)gi.size(); ++k)
-    if (gi[k] >= 0) ent[fill[gi[k]]++] = (int32_t)k;
-  bn.upload(sizes, bud, s);
-  ent_off.upload(eoff, bud, s);
-  cp_off.upload(cpo, bud, s);
-  rp_off.upload(rpo, bud, s);
-  loc_off.upload(loff, bud, s);
-  gidx.upload(gi, bud, s);
-  units.upload(ud, bud, s);
-  rows.upload(rw, bud, s);
-  rowd.upload(rd, bud, s);
-  tdesc.upload(td, bud, s);
-  red_ptr.upload(cnt, bud, s);
-  red_ent.upload(ent, bud, s);
+  for (int b = 0; b < nblk; ++b)   // in block order, whatever the groups
+    for (int i = 0; i < sizes[b]; ++i) {
+      const int64_t k = loff[b] + (int64_t)i * step[b];
+      ent[fill[gi[k]]++] = (int32_t)k;
+    }
+  // one upload for all lists (each from a multiple of 16 bytes)
+  std::vector<int4> all;
+  std::vector<std::pair<void **, size_t>> at;
+  auto add = [&](auto &dst, const auto &v) {
+    at.push_back({(void **)&dst.p, all.size()});
+    const size_t bytes = v.size() * sizeof(v[0]);
+    all.resize(all.size() + (bytes + 15) / 16);
+    if (bytes) std::memcpy(&all[at.back().second], v.data(), bytes);
+  };
+  add(bn, sizes);
+  add(ent_off, eoff);
+  add(grp, gs);
+  add(grow, gr);
+  add(gidx, gi);
+  add(units, ud);
+  add(gunits64, gud64);
+  add(rowd, rd);
+  add(rowb, rb);
+  add(tdesc, td);
+  add(red_ptr, cnt);
+  add(red_ent, ent);
+  add(sunits, sud);
+  add(gunits, gud);
+  add(srowd, srd);
+  lists.upload(all, bud, s);
+  for (auto &q : at) *q.first = lists.p + q.second;
   if (fp64) {
     t64.alloc(nent, bud);
     p64.alloc(npart, bud);
@@ -637,8 +969,6 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
     launch_zero(nloc, xl64.p, s);
   }
   if (fp32) {
-    sunits.upload(sud, bud, s);
-    srowd.upload(srd, bud, s);
     t32.alloc(nent, bud);
     p32.alloc(snpart, bud);
     xl32.alloc(nloc, bud);
@@ -691,7 +1021,7 @@ void herm_apply(HermSet &H, const cplx_t<T> *x, cplx_t<T> *y, const cplx_t<T> *r
     yl = H.yl32.p;
   }
   xl = local_x<T>(H);
-  if (!tiles || !part) throw DpgError(-6, "block set has no tiles of this precision");
+  if (!tiles) throw DpgError(-6, "block set has no tiles of this precision");
   cplx_t<T> *fxl = fwd ? local_x<T>(*fwd) : nullptr;
   if (fwd && (!fxl || fwd->nvec != H.nvec))
     throw DpgError(-1, "forwarded block set does not match this one");
@@ -701,20 +1031,37 @@ void herm_apply(HermSet &H, const cplx_t<T> *x, cplx_t<T> *y, const cplx_t<T> *r
                        H.gidx.p, x, xl);
     LAUNCH_OK();
   }
-  {
-    ProfScope ps(H.prof, sizeof(T) == 8 ? DPG_K_APPLY64 : DPG_K_APPLY32,
-                 (double)H.packed_entries() * sizeof(cplx_t<T>), s);
-    if constexpr (sizeof(T) == 8)
+  if constexpr (sizeof(T) == 8) {
+    if (H.gnunits64 > 0) {
+      ProfScope ps(H.prof, DPG_K_APPLYG64, 8.0 * (double)H.full_grouped, s);
+      hipLaunchKernelGGL((k_units_grp<T, false>), dim3(8 * cdiv(cdiv(H.gnunits64, 4), 8)),
+                         dim3(256), 0, s, tiles, H.gunits64.p, H.gnunits64, 1, xl, part);
+      LAUNCH_OK();
+    }
+    if (H.nunits > 0) {
+      ProfScope ps(H.prof, DPG_K_APPLY64, (double)H.packed_entries() * sizeof(cplx_t<T>), s);
       hipLaunchKernelGGL((k_units<T>), dim3(8 * cdiv(cdiv(H.nunits, 4), 8)), dim3(256), 0, s,
                          tiles, H.units.p, H.nunits, xl, part);
-    else
+      LAUNCH_OK();
+    }
+  } else {
+    if (H.gnunits > 0) {
+      ProfScope ps(H.prof, DPG_K_APPLYG32, 8.0 * (double)H.full_grouped, s);
+      hipLaunchKernelGGL((k_strips_grp<T>), dim3(8 * cdiv(cdiv(H.gnunits, 4), 8)), dim3(256), 0, s,
+                         tiles, H.gunits.p, H.gnunits, xl, part);
+      LAUNCH_OK();
+    }
+    if (H.snunits > 0) {
+      ProfScope ps(H.prof, DPG_K_APPLY32, (double)H.packed_entries() * sizeof(cplx_t<T>), s);
       hipLaunchKernelGGL((k_strips<T>), dim3(8 * cdiv(cdiv(H.snunits, 4), 8)), dim3(256), 0, s,
                          tiles, H.sunits.p, H.snunits, xl, part);
-    LAUNCH_OK();
+      LAUNCH_OK();
+    }
   }
   ProfScope ps(H.prof, DPG_K_REDUCE, 0.0, s);
   hipLaunchKernelGGL((k_rows<T>), dim3(cdiv(H.nrows, 8)), dim3(256), 0, s,
-                     sizeof(T) == 8 ? H.rowd.p : H.srowd.p, H.nrows, part, yl);
+                     sizeof(T) == 8 ? H.rowd.p : H.srowd.p, (const int2 *)nullptr, H.nrows, 1, part,
+                     yl);
   LAUNCH_OK();
   switch (mode) {
     case RED_SET: launch_scatter<T, RED_SET>(H, yl, r, y, theta, fwd, fxl, s); break;
@@ -722,6 +1069,21 @@ void herm_apply(HermSet &H, const cplx_t<T> *x, cplx_t<T> *y, const cplx_t<T> *r
     case RED_AXPY: launch_scatter<T, RED_AXPY>(H, yl, r, y, theta, fwd, fxl, s); break;
     default: launch_scatter<T, RED_SET_SCALED>(H, yl, r, y, theta, fwd, fxl, s);
   }
+  LAUNCH_OK();
+}
+
+void launch_units_cols(HermSet &H, const double2 *xl, double2 *part, double2 *yl, int nr,
+                       hipStream_t s) {
+  const dim3 g(8 * cdiv(cdiv(H.gall64, 4), 8));
+  {
+    ProfScope ps(H.prof, DPG_K_APPLYG64, 8.0 * (double)H.full * nr, s);
+    hipLaunchKernelGGL((k_units_grp<double, true>), g, dim3(256), 0, s, H.t64.p, H.gunits64.p,
+                       H.gall64, nr, xl, part);
+    LAUNCH_OK();
+  }
+  ProfScope ps(H.prof, DPG_K_REDUCE, 0.0, s);
+  hipLaunchKernelGGL((k_rows<double>), dim3(cdiv(H.nrows, 8), nr), dim3(256), 0, s, H.rowd.p,
+                     H.rowb.p, H.nrows, nr, part, yl);
   LAUNCH_OK();
 }
 

@@ -11,6 +11,14 @@
 // only the sub-blocks on and above its diagonal (36 of 64, the diagonal 4x4
 // sub-blocks whole): [k][slot] with 36 slots, 576 entries instead of 1024.
 //
+// Blocks that are the same matrix (a class) share one copy of its tiles and are
+// applied in groups of up to eight: their local vectors are the columns of a
+// matrix, and each tile is read once for the blocks of a group (four in FP32).
+// Every block gets the arithmetic it would get alone, in the same order: the
+// mixed-precision solutions move by 1e-9 and more with the rounding of the
+// preconditioner (products of the groups on the matrix cores were as fast but
+// moved them), so results do not depend on the grouping.
+//
 // Apply (four kernels, deterministic):
 //  1. gather:  x_loc[b] = R_b x, zero-padded to 32 nt_b entries;
 //  2. columns: FP64: one wave per (block, tile column J, segment of two tile
@@ -49,29 +57,65 @@ __host__ __device__ __forceinline__ int diag_slot(int ra, int cb) {
   return ra * 8 - ra * (ra - 1) / 2 + (cb - ra);
 }
 
+// Blocks of one class that are applied together: column m of a group of gw
+// blocks is the local vector of its member m, row i at (base + i gw + m) (times
+// the right-hand sides of a block vector, column k of a member at m nr + k).  A
+// group of one block is that block's contiguous local vector.
+constexpr int kMaxGroup = 8;
+struct HermGroup {
+  int64_t ent;               // first tile entry of the class
+  int32_t base, gw, nt, pad;
+};
+
+// Units of the matrix-core apply for nr right-hand sides: chunks of 32 columns;
+// chunk c covers the first cnt[c] units (units are sorted by group width).
+struct ChunkMap {
+  int32_t total = 0;
+  int32_t cnt[kMaxGroup] = {};
+};
+
+// A list inside HermSet::lists.
+template <typename T> struct DevList {
+  T *p = nullptr;
+};
+
 struct HermSet {
   int nblk = 0;
+  DevBuf<int4> lists;        // every list below, in one allocation
   int64_t nvec = 0;          // length of the target vector
+  // units, packed: of the blocks that are a group of their own
   int64_t ntiles = 0, npart = 0, nunits = 0, nrows = 0, nloc = 0, packed = 0;
   int64_t nent = 0;          // stored tile entries
   int64_t full = 0;          // sum of n_b^2 (entries of the full blocks)
   std::vector<int32_t> n_h;  // block sizes (host)
   std::vector<int64_t> tile_off_h;   // per class: first tile index
   std::vector<int64_t> ent_off_h;    // per block: first entry of its class
-  std::vector<int64_t> loc_off_h;                // per block: first row of its local vectors
-  DevBuf<int32_t> bn;
-  DevBuf<int64_t> ent_off, cp_off, rp_off, loc_off;
-  DevBuf<int32_t> gidx;      // [nloc] vector index of each padded local row, -1 = padding
-  DevBuf<int4> units;        // two int4 descriptors per (block, J, tile-row pair), block order
-  DevBuf<int2> rows;         // (block, I)
-  DevBuf<int4> rowd;         // per (block, I): column-partial base, row-partial base,
-                             // segment count | (row-partial count << 16), local offset
-  // the same for the FP32 apply by column pairs (strips); partials in p32
-  DevBuf<int4> sunits, srowd;
-  int64_t snunits = 0, snpart = 0;
-  DevBuf<int4> tdesc;        // (representative block, I, J, 0) per stored tile (packing)
-  DevBuf<int32_t> red_ptr;   // CSR over vector entries
-  DevBuf<int32_t> red_ent;   // offsets into the local vectors
+  std::vector<int64_t> loc_off_h;    // per block: row 0 of its local vector
+  DevList<int32_t> bn;
+  DevList<int64_t> ent_off;
+  // groups, widest first, and their tile rows (group, I); nrow_w[w]: how many of
+  // these belong to groups of at least w blocks
+  DevList<HermGroup> grp;
+  DevList<int2> grow;
+  int64_t nrow_w[kMaxGroup + 2] = {};
+  int64_t full_grouped = 0;  // sum of n_b^2 over the blocks in groups of two and more
+  DevList<int32_t> gidx;      // [nloc] vector index of each padded local row, -1 = padding
+  DevList<int4> units;        // two int4 descriptors per (block, J, tile-row pair), block order
+  DevList<int4> rowd;         // per (block, I): column-partial base, row-partial base,
+                             // segment count | row-partial count << 12 | row step of the
+                             // local vector << 24, local offset
+  // the same for the FP32 apply by column pairs (strips); partials in p32;
+  // sunits: blocks alone, gunits (three int4 each): up to four blocks of a group;
+  // rowd, srowd: the rows of every block
+  DevList<int4> sunits, gunits, srowd;
+  int64_t snunits = 0, gnunits = 0, snpart = 0;
+  DevList<int4> gunits64;     // three int4 per (group, J, tile-row pair), FP64; the first
+  int64_t gnunits64 = 0;     // gnunits64 of groups of two and more blocks, gall64 in all
+  int64_t gall64 = 0;
+  DevList<int2> rowb;         // per (block, I): first partial slot of the block, its slots
+  DevList<int4> tdesc;        // (representative block, I, J, 0) per stored tile (packing)
+  DevList<int32_t> red_ptr;   // CSR over vector entries
+  DevList<int32_t> red_ent;   // offsets into the local vectors
   DevBuf<double2> t64;       // tiles, FP64
   DevBuf<float2> t32;        // tiles, FP32 (mixed precision)
   DevBuf<double2> p64, xl64, yl64;   // partials and local vectors
@@ -79,16 +123,18 @@ struct HermSet {
   Prof *prof = nullptr;      // kernel timing of the owning context
   int64_t bytes_fp64() const { return nent * 16; }
   int64_t bytes_fp32() const { return nent * 8; }
-  // algorithmic entries: packed Hermitian n(n+1)/2 per block
+  // algorithmic entries of the blocks applied one by one: packed Hermitian
+  // n(n+1)/2 per block
   int64_t packed_entries() const { return packed; }
 
   // idx: per block the vector index of each local row (concatenated).  cls
   // (or null: every block its own): the class of each block; the blocks of a
   // class are the same matrix and share one copy of its tiles, packed from
-  // the class's first block.
+  // the class's first block; unless grouping is off, they are applied in
+  // groups.
   void build(const std::vector<int32_t> &sizes, const std::vector<int32_t> &idx_concat,
              int64_t nvec_, bool fp64, bool fp32, Budget *bud, hipStream_t s,
-             const std::vector<int32_t> *cls = nullptr);
+             const std::vector<int32_t> *cls = nullptr, bool grouping = true);
   // Fill the tiles from dense column-major sources: block b reads
   // src[src_off[b] + map(i) + map(j) * ld[b]] where map is the identity when
   // map_off[b] < 0, else map[map_off[b] + i].
@@ -107,5 +153,10 @@ struct HermSet {
 template <typename T>
 void herm_apply(HermSet &H, const cplx_t<T> *x, cplx_t<T> *y, const cplx_t<T> *r, int mode,
                 T theta, hipStream_t s, bool gathered = false, HermSet *fwd = nullptr);
+
+// yl = A xl for the nr interleaved columns of every block of a set without
+// groups, each tile read once for all of them (FP64; part: npart nr entries).
+void launch_units_cols(HermSet &H, const double2 *xl, double2 *part, double2 *yl, int nr,
+                       hipStream_t s);
 
 }  // namespace dpg
