@@ -279,7 +279,6 @@ void classify_levels(dpg_ctx *c) {
       });
     }
     const auto &pp = f.mc.patch_ptr;
-    const auto &slot = f.mc.patch_slot;
     build_classes(f.pc, (int)pp.size() - 1, [&](int v, std::array<int64_t, 8> &k) {
       const int vx = v % (Nc + 1), vy = (v / (Nc + 1)) % (Nc + 1), vz = v / ((Nc + 1) * (Nc + 1));
       for (int ch = 0; ch < 8; ++ch) {
@@ -288,9 +287,10 @@ void classify_levels(dpg_ctx *c) {
         k[ch] = in ? f.bc.of_h[i + Nc * (j + Nc * z)] : -1;
       }
     }, [&](int a, int b) {
-      return pp[a + 1] - pp[a] == pp[b + 1] - pp[b] &&
-             std::memcmp(&slot[8 * pp[a]], &slot[8 * pp[b]],
-                         (size_t)(pp[a + 1] - pp[a]) * 8 * sizeof(int32_t)) == 0;
+      // the members and their slots follow from the blocks around the vertex:
+      // the numbering is lexicographic in each family, so a translation keeps
+      // their order
+      return pp[a + 1] - pp[a] == pp[b + 1] - pp[b];
     });
   }
   std::vector<int32_t> all;   // one upload for every level
@@ -2231,7 +2231,6 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
       f.nel = f.N * f.N * f.N;
       f.num.build(f.N, f.q);
       f.edofs_h = element_dofs(f.num, f.el);
-      f.edofs.upload(f.edofs_h, &c->bud, s);
     }
     for (int l = 1; l <= c->L; ++l) {
       LevelData &f = c->lv[l];
@@ -2249,16 +2248,23 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
       f.nblk = f.mc.Nc * f.mc.Nc * f.mc.Nc;
     }
     classify_levels(c);
+    ListPack edofs0;
+    edofs0.add(c->lv[0].edofs, c->lv[0].edofs_h);
+    edofs0.upload(c->lv[0].lists, &c->bud, s);
     for (int l = 1; l <= c->L; ++l) {
       LevelData &f = c->lv[l];
+      ListPack lp;
+      std::vector<float> pv, ptv;
+      std::vector<int32_t> pidx;
+      lp.add(f.edofs, f.edofs_h);
       f.nBf = f.mc.nBf;
       f.nI = f.mc.nI;
       f.nM = f.mc.nM;
-      f.macroB.upload(f.mc.macro_B, &c->bud, s);
-      f.blkI.upload(f.mc.blkI, &c->bud, s);
+      lp.add(f.macroB, f.mc.macro_B);
+      lp.add(f.blkI, f.mc.blkI);
       std::vector<int32_t> bm(f.mc.blkB.size());
       for (size_t k = 0; k < bm.size(); ++k) bm[k] = f.mc.blkB[k] >= 0 ? f.mc.macro_of[f.mc.blkB[k]] : -1;
-      f.blkBm.upload(bm, &c->bud, s);
+      lp.add(f.blkBm, bm);
       // condensation reduction lists: (block, slot) holding each macro unknown
       std::vector<int32_t> cnt(f.nM + 1, 0), ent;
       for (size_t k = 0; k < bm.size(); ++k)
@@ -2268,20 +2274,21 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
       std::vector<int32_t> fill(cnt.begin(), cnt.end() - 1);
       for (size_t k = 0; k < bm.size(); ++k)
         if (bm[k] >= 0) ent[fill[bm[k]]++] = (int32_t)k;
-      f.cred_ptr.upload(cnt, &c->bud, s);
-      f.cred_ent.upload(ent, &c->bud, s);
-      f.patch_ptr.upload(f.mc.patch_ptr, &c->bud, s);
-      f.patch_slot.upload(f.mc.patch_slot, &c->bud, s);
-      f.Pptr.upload(f.P.ptr, &c->bud, s);
-      f.Pcol.upload(f.P.col, &c->bud, s);
-      f.Pval.upload(f.P.val, &c->bud, s);
-      f.Ptptr.upload(f.P.tptr, &c->bud, s);
-      f.Ptcol.upload(f.P.tcol, &c->bud, s);
-      f.Ptval.upload(f.P.tval, &c->bud, s);
+      lp.add(f.cred_ptr, cnt);
+      lp.add(f.cred_ent, ent);
+      lp.add(f.patch_ptr, f.mc.patch_ptr);
+      lp.add(f.patch_slot, f.mc.patch_slot);
+      lp.add(f.Pptr, f.P.ptr);
+      lp.add(f.Pcol, f.P.col);
+      lp.add(f.Pval, f.P.val);
+      lp.add(f.Ptptr, f.P.tptr);
+      lp.add(f.Ptcol, f.P.tcol);
+      lp.add(f.Ptval, f.P.tval);
       if (mixed) {
-        std::vector<float> pv(f.P.val.begin(), f.P.val.end()), ptv(f.P.tval.begin(), f.P.tval.end());
-        f.Pval32.upload(pv, &c->bud, s);
-        f.Ptval32.upload(ptv, &c->bud, s);
+        pv.assign(f.P.val.begin(), f.P.val.end());
+        ptv.assign(f.P.tval.begin(), f.P.tval.end());
+        lp.add(f.Pval32, pv);
+        lp.add(f.Ptval32, ptv);
       }
       // block sets
       std::vector<int32_t> msz(f.nblk), midx;
@@ -2295,11 +2302,11 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
       std::vector<int32_t> psz(np);
       for (int v = 0; v < np; ++v) psz[v] = (int32_t)(f.mc.patch_ptr[v + 1] - f.mc.patch_ptr[v]);
       if (c->opt.flags & DPG_RECOMPUTE_PATCHES) {   // no tiles: the inverses are recomputed
-        std::vector<int32_t> pidx((size_t)f.nblk * f.nBf, -1);   // slot -> packed position
+        pidx.assign((size_t)f.nblk * f.nBf, -1);   // slot -> packed position
         for (int b = 0; b < f.nblk; ++b)
           for (int64_t k = f.mc.blkB_ptr[b]; k < f.mc.blkB_ptr[b + 1]; ++k)
             pidx[(size_t)b * f.nBf + f.mc.blkB_present[k]] = (int32_t)(k - f.mc.blkB_ptr[b]);
-        f.mpidx.upload(pidx, &c->bud, s);
+        lp.add(f.mpidx, pidx);
         f.Sset.build(psz, f.mc.patch_idx, f.nM, false, false, &c->bud, s, &f.pc.of_h, false);
         f.Sset.xl64.alloc(f.Sset.nloc, &c->bud);
         f.Sset.yl64.alloc(f.Sset.nloc, &c->bud);
@@ -2308,6 +2315,8 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
       }
       f.Mset.prof = &c->prof;
       f.Sset.prof = &c->prof;
+      lp.upload(f.lists, &c->bud, s);
+      HIP_OK(hipStreamSynchronize(s));   // the lists built here are copied
       // work vectors
       const int64_t nc = c->lv[l - 1].num.n;
       if (mixed) {

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <cstring>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -115,6 +116,44 @@ template <typename T> struct DevBuf {
       HIP_OK(hipStreamSynchronize(s));
     }
     return h;
+  }
+};
+
+// Lists in one device allocation; the small ones are copied together (a hipMalloc
+// and a copy per list are most of the time of setting up a small mesh).
+template <typename T> struct DevList {
+  T *p = nullptr;
+};
+struct ListPack {
+  struct Item { void **dst; const void *src; size_t bytes; };
+  std::vector<Item> items;
+  std::vector<int4> small;
+  // v must stay unchanged until the copies on s have been waited for
+  template <typename T> void add(DevList<T> &dst, const std::vector<T> &v) {
+    items.push_back({(void **)&dst.p, v.data(), v.size() * sizeof(T)});
+  }
+  // buf must outlive the lists, this object and the added vectors the copies on s
+  void upload(DevBuf<int4> &buf, Budget *b, hipStream_t s) {
+    constexpr size_t kSmall = 65536;
+    auto slots = [](size_t bytes) { return (bytes + 15) / 16; };
+    size_t n = 0, n_small = 0;
+    for (const Item &q : items) {
+      n += slots(q.bytes);
+      if (q.bytes <= kSmall) n_small += slots(q.bytes);
+    }
+    buf.alloc((int64_t)n, b);
+    small.resize(n_small);
+    size_t at_small = 0, at = n_small;
+    for (const Item &q : items) {
+      const bool sm = q.bytes <= kSmall;
+      size_t &o = sm ? at_small : at;
+      *q.dst = buf.p + o;
+      if (sm && q.bytes) std::memcpy((void *)&small[o], q.src, q.bytes);
+      if (!sm) HIP_OK(hipMemcpyAsync(buf.p + o, q.src, q.bytes, hipMemcpyHostToDevice, s));
+      o += slots(q.bytes);
+    }
+    if (n_small)
+      HIP_OK(hipMemcpyAsync(buf.p, small.data(), n_small * 16, hipMemcpyHostToDevice, s));
   }
 };
 

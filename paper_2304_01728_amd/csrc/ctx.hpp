@@ -129,7 +129,8 @@ struct LevelData {
   ElementLayout el;
   Numbering num;
   std::vector<int32_t> edofs_h;
-  DevBuf<int32_t> edofs;
+  DevBuf<int4> lists;                // the index and value lists below
+  DevList<int32_t> edofs;
   Classes ec, bc, pc;                // of the elements, macro blocks and vertex patches
   DevBuf<double2> E;                 // element matrices [ec.n][n_tr^2]
   DevBuf<double> kappa, Zel;         // per element c^-2 and Z on a coarser mesh whose
@@ -143,18 +144,18 @@ struct LevelData {
   DevBuf<double2> Mfull;             // [bc.n][nBf^2] condensed blocks, full local layout
   DevBuf<double2> Tinv, WH;          // [bc.n][nI^2], [bc.n][nBf nI]
   DevBuf<float2> Tinv32, WH32;
-  DevBuf<int32_t> blkI, blkBm;       // [nblk][nI] canonical, [nblk][nBf] macro index / -1
-  DevBuf<int64_t> macroB;            // [nM] canonical index of each macro unknown
-  DevBuf<int32_t> cred_ptr, cred_ent;
-  DevBuf<int64_t> patch_ptr;
-  DevBuf<int32_t> patch_slot;
-  DevBuf<int32_t> mpidx;             // [nblk][nBf] packed position of each macro-block slot
+  DevList<int32_t> blkI, blkBm;       // [nblk][nI] canonical, [nblk][nBf] macro index / -1
+  DevList<int64_t> macroB;            // [nM] canonical index of each macro unknown
+  DevList<int32_t> cred_ptr, cred_ent;
+  DevList<int64_t> patch_ptr;
+  DevList<int32_t> patch_slot;
+  DevList<int32_t> mpidx;             // [nblk][nBf] packed position of each macro-block slot
                                      // (recomputed patch inverses)
   HermSet Mset, Sset;
-  DevBuf<int64_t> Pptr, Ptptr;
-  DevBuf<int32_t> Pcol, Ptcol;
-  DevBuf<double> Pval, Ptval;
-  DevBuf<float> Pval32, Ptval32;
+  DevList<int64_t> Pptr, Ptptr;
+  DevList<int32_t> Pcol, Ptcol;
+  DevList<double> Pval, Ptval;
+  DevList<float> Pval32, Ptval32;
   // V-cycle work vectors: r, x, res on this macro grid; rc, ec on the coarser
   // mesh's traces; c = per-block condensation contributions of this level.
   DevBuf<double2> r64, x64, res64, rc64, ec64, c64;

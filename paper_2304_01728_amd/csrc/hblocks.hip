@@ -1,6 +1,5 @@
 // Hermitian block sets: packing and apply kernels (see hblocks.hpp).
 #include <algorithm>
-#include <cstring>
 #include <map>
 
 #include "block.hpp"
@@ -563,41 +562,25 @@ __global__ __launch_bounds__(256, 2) void k_strips_grp(const cplx_t<T> *__restri
   }
 }
 
-// Half a wave per (block, tile row I): y_loc rows of I = column sums of the
-// segments of tile column I + row sums of tiles (I, J >= I).  The row's
-// descriptor (rowd, see HermSet::build) gives both partial bases and counts
-// with one load.  The slots are independent loads: eight are in flight per
-// lane (a row of a 24-tile block sums 25 slots), summed in a fixed order.
-// With nr right-hand sides, blockIdx.y is the column and rowb gives {first
-// slot of the block, slots of the block}.
-template <typename T>
-__global__ __launch_bounds__(256) void k_rows(const int4 *__restrict__ rowd,
-                                              const int2 *__restrict__ rowb, int64_t nrows, int nr,
-                                              const cplx_t<T> *__restrict__ part,
-                                              cplx_t<T> *__restrict__ yl) {
-  using C = cplx_t<T>;
+// Sum of the partial slots of row r of a tile row: the column sums of the
+// segments (or strip chunks) of its tile column, then the row sums of its tiles;
+// eight loads in flight per lane (a row of a 24-tile block sums 25 slots), summed
+// in a fixed order.
+template <typename C>
+__device__ __forceinline__ C row_total(const int4 d, int r, const C *__restrict__ part) {
   constexpr int U = 8;
-  const int64_t hw = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5;
-  if (hw >= nrows) return;
-  const int r = threadIdx.x & 31;
-  const int4 d = rowd[hw];
-  if (nr > 1) part += (int64_t)rowb[hw].x * (nr - 1) + (int64_t)rowb[hw].y * blockIdx.y;
   const C *cp = part + d.x + r;
   const C *rp = part + d.y + r;
   const int nseg = d.z & 0xfff, tot = nseg + (d.z >> 12 & 0xfff);
   C acc[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    acc[u].x = 0;
-    acc[u].y = 0;
-  }
+  for (int u = 0; u < U; ++u) acc[u] = czero<C>();
   for (int q0 = 0; q0 < tot; q0 += U) {
     C v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int q = q0 + u;
-      v[u].x = 0;
-      v[u].y = 0;
+      v[u] = czero<C>();
       if (q < tot) v[u] = q < nseg ? cp[q * 32] : rp[(q - nseg) * 32];
     }
 #pragma unroll
@@ -607,7 +590,23 @@ __global__ __launch_bounds__(256) void k_rows(const int4 *__restrict__ rowd,
   for (int w = U / 2; w >= 1; w /= 2)
 #pragma unroll
     for (int u = 0; u < w; ++u) acc[u] = cadd(acc[u], acc[u + w]);
-  yl[(int64_t)(d.w + r * (d.z >> 24)) * nr + blockIdx.y] = acc[0];
+  return acc[0];
+}
+
+// Half a wave per (block, tile row I) and column blockIdx.y of the local vectors
+// of nr right-hand sides; rowb gives {first slot of the block, slots of the block}
+// (read for nr > 1).
+template <typename T>
+__global__ __launch_bounds__(256) void k_rows(const int4 *__restrict__ rowd,
+                                              const int2 *__restrict__ rowb, int64_t nrows, int nr,
+                                              const cplx_t<T> *__restrict__ part,
+                                              cplx_t<T> *__restrict__ yl) {
+  const int64_t hw = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5;
+  if (hw >= nrows) return;
+  const int r = threadIdx.x & 31;
+  const int4 d = rowd[hw];
+  if (nr > 1) part += (int64_t)rowb[hw].x * (nr - 1) + (int64_t)rowb[hw].y * blockIdx.y;
+  yl[(int64_t)(d.w + r * (d.z >> 24)) * nr + blockIdx.y] = row_total(d, r, part);
 }
 
 // With FWD the result of entry d is also written to every local row of the
@@ -637,6 +636,72 @@ __global__ __launch_bounds__(256) void k_scatter(int64_t nvec, const int32_t *__
   y[d] = out;
   if (FWD)
     for (int32_t k = fwd_ptr[d]; k < fwd_ptr[d + 1]; ++k) fwd_xl[fwd_ent[k]] = out;
+}
+
+// One column: eight lanes per vector entry d, one for each block that holds it
+// (its list: tile row 32 + row of the entry in the block, in block order; longer
+// lists take more rounds), each sums its row's partials, and the sums are added
+// in list order, 0 + first + second + ..., in the group's first lane, which
+// applies the epilogue.  The row sums never go to memory and one launch is
+// saved; the partials are read in shorter runs (eight rows of a slot instead of
+// 32), which costs more once they exceed the 256 MB Infinity Cache (kFusedBytes).
+// Solves with k_rows and k_scatter / with this: 8^3, order levels, 15.3 / 12.1 ms;
+// 4^3, p = 2, 1.69 / 1.52; 16^3, p = 3 (118 MB of FP64 partials) 25.9 / 25.5; 24^3,
+// p = 4 mixed (400 MB) 108.7 / 113.1.
+constexpr int64_t kFusedBytes = 192 << 20;
+template <int K, typename C> __device__ __forceinline__ C add_lane(C acc, C v, int cnt) {
+  const C o = dpp_c<0x100 | K>(v);   // row_shl: lane i reads lane i + K of its 16
+  return csel(K < cnt, cadd(acc, o), acc);
+}
+template <typename T, int MODE, bool FWD>
+__global__ __launch_bounds__(256) void k_rows_scatter(int64_t nvec,
+                                                      const int32_t *__restrict__ red_ptr,
+                                                      const int32_t *__restrict__ red_row,
+                                                      const int4 *__restrict__ rowd,
+                                                      const cplx_t<T> *__restrict__ part,
+                                                      const cplx_t<T> *__restrict__ r,
+                                                      cplx_t<T> *__restrict__ y, T theta,
+                                                      const int32_t *__restrict__ fwd_ptr,
+                                                      const int32_t *__restrict__ fwd_ent,
+                                                      cplx_t<T> *__restrict__ fwd_xl) {
+  using C = cplx_t<T>;
+  const int64_t d = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 3;
+  const int j = threadIdx.x & 7;
+  if (d >= nvec) return;   // whole groups of eight
+  const int32_t p0 = red_ptr[d];
+  int cnt = red_ptr[d + 1] - p0;
+  C rd, yd;
+  if (MODE == RED_RESID) rd = r[d];
+  if (MODE == RED_AXPY) yd = y[d];
+  C acc = czero<C>();
+  for (int32_t q = p0;; q += 8, cnt -= 8) {
+    C v = czero<C>();
+    if (j < cnt) {
+      const int32_t e = red_row[q + j];
+      v = row_total(rowd[e >> 5], e & 31, part);
+    }
+    acc = csel(0 < cnt, cadd(acc, v), acc);
+    acc = add_lane<1>(acc, v, cnt);
+    acc = add_lane<2>(acc, v, cnt);
+    acc = add_lane<3>(acc, v, cnt);
+    acc = add_lane<4>(acc, v, cnt);
+    acc = add_lane<5>(acc, v, cnt);
+    acc = add_lane<6>(acc, v, cnt);
+    acc = add_lane<7>(acc, v, cnt);
+    if (cnt <= 8) break;
+  }
+  C out;
+  if (MODE == RED_SET) out = acc;
+  else if (MODE == RED_RESID) out = csub(rd, acc);
+  else if (MODE == RED_AXPY) out = cadd(yd, cscale(acc, theta));
+  else out = cscale(acc, theta);
+  if (j == 0) y[d] = out;
+  if (FWD) {
+    const int src = threadIdx.x & 0x38;   // the group's first lane
+    out.x = __shfl(out.x, src, 64);
+    out.y = __shfl(out.y, src, 64);
+    for (int32_t k = fwd_ptr[d] + j; k < fwd_ptr[d + 1]; k += 8) fwd_xl[fwd_ent[k]] = out;
+  }
 }
 
 __global__ __launch_bounds__(256) void k_pack(const int4 *__restrict__ tdesc, int64_t tile0,
@@ -776,7 +841,7 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
   for (int32_t b : alone) {
     const int n = sizes[b], nt = (n + 31) / 32;
     packed += (int64_t)n * (n + 1) / 2;
-    for (int J = 0; J < nt; ++J)
+    for (int J = 0; fp64 && J < nt; ++J)
       for (int seg = 0; seg * kSeg <= J; ++seg) un.push_back(make_int4(b, J, seg * kSeg, seg));
   }
   // units in block order (block, tile column, segment): the waves of
@@ -812,10 +877,11 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
   gall64 = (int64_t)gud64.size() / 3;
   std::vector<int2> rb;
   for (const int2 &k : rw) {
+    if (!fp64) break;
     const int b = k.x, nt = (sizes[b] + 31) / 32;
     rb.push_back(make_int2((int)cpo[b], (int)(colbase(nt) + (int64_t)nt * (nt + 1) / 2 * 32)));
   }
-  if (npart >= (1LL << 31) || nloc >= (1LL << 31))
+  if ((fp64 && npart >= (1LL << 31)) || nloc >= (1LL << 31))
     throw DpgError(-1, "HermSet: partial or local vectors beyond 32-bit offsets");
   // unit descriptors: {entry offset of tile (I0, J) lo, hi, x offset of tile
   // row I0, of tile column J}, {row-partial slot of (I0, J), step to the slot of (I0 + 1, J),
@@ -835,8 +901,8 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
     ud[2 * k + 1] = make_int4((int)r0, (int)rd, (int)cs, flags);
   }
   nrows = (int64_t)rw.size();
-  std::vector<int4> rd(rw.size());
-  for (size_t k = 0; k < rw.size(); ++k) {
+  std::vector<int4> rd(fp64 ? rw.size() : 0);
+  for (size_t k = 0; k < rd.size(); ++k) {
     const int b = rw[k].x, I = rw[k].y, nt = (sizes[b] + 31) / 32;
     const int nseg = (I + kSeg) / kSeg, nrw = nt - I;
     if (nt > 0xfff) throw DpgError(-1, "HermSet: block too large for row descriptors");
@@ -923,27 +989,25 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
   loc_off_h = loff;
   // reduction lists: for every vector entry, the local rows holding it
   std::vector<int32_t> cnt(nvec + 1, 0);
-  for (int32_t v : gi) {
-    if (v >= nvec) throw DpgError(-1, "HermSet: index out of range");
-    if (v >= 0) cnt[v + 1]++;
+  for (int32_t v : idx_concat) {
+    if (v < 0 || v >= nvec) throw DpgError(-1, "HermSet: index out of range");
+    cnt[v + 1]++;
   }
   for (int64_t d = 0; d < nvec; ++d) cnt[d + 1] += cnt[d];
-  std::vector<int32_t> ent(cnt[nvec]);
+  std::vector<int32_t> ent(cnt[nvec]), erow(cnt[nvec]);
   std::vector<int32_t> fill(cnt.begin(), cnt.end() - 1);
-  for (int b = 0; b < nblk; ++b)   // in block order, whatever the groups
+  if (32 * (int64_t)rw.size() >= (1LL << 31))
+    throw DpgError(-1, "HermSet: partial or local vectors beyond 32-bit offsets");
+  for (int b = 0, row0 = 0; b < nblk; ++b) {   // in block order, whatever the groups
     for (int i = 0; i < sizes[b]; ++i) {
-      const int64_t k = loff[b] + (int64_t)i * step[b];
-      ent[fill[gi[k]]++] = (int32_t)k;
+      const int32_t f = fill[idx_concat[idx0[b] + i]]++;
+      ent[f] = (int32_t)(loff[b] + (int64_t)i * step[b]);
+      erow[f] = 32 * row0 + i;   // rows of rw: tile row I of block b is row0 + I
     }
-  // one upload for all lists (each from a multiple of 16 bytes)
-  std::vector<int4> all;
-  std::vector<std::pair<void **, size_t>> at;
-  auto add = [&](auto &dst, const auto &v) {
-    at.push_back({(void **)&dst.p, all.size()});
-    const size_t bytes = v.size() * sizeof(v[0]);
-    all.resize(all.size() + (bytes + 15) / 16);
-    if (bytes) std::memcpy(&all[at.back().second], v.data(), bytes);
-  };
+    row0 += (sizes[b] + 31) / 32;
+  }
+  ListPack all;
+  auto add = [&](auto &dst, const auto &v) { all.add(dst, v); };
   add(bn, sizes);
   add(ent_off, eoff);
   add(grp, gs);
@@ -956,23 +1020,23 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
   add(tdesc, td);
   add(red_ptr, cnt);
   add(red_ent, ent);
+  add(red_row, erow);
   add(sunits, sud);
   add(gunits, gud);
   add(srowd, srd);
-  lists.upload(all, bud, s);
-  for (auto &q : at) *q.first = lists.p + q.second;
+  all.upload(lists, bud, s);
   if (fp64) {
     t64.alloc(nent, bud);
     p64.alloc(npart, bud);
+    if (npart * 16 > kFusedBytes) yl64.alloc(nloc, bud);
     xl64.alloc(nloc, bud);
-    yl64.alloc(nloc, bud);
     launch_zero(nloc, xl64.p, s);
   }
   if (fp32) {
     t32.alloc(nent, bud);
     p32.alloc(snpart, bud);
+    if (snpart * 8 > kFusedBytes) yl32.alloc(nloc, bud);
     xl32.alloc(nloc, bud);
-    yl32.alloc(nloc, bud);
     launch_zero(nloc, xl32.p, s);
   }
   HIP_OK(hipStreamSynchronize(s));
@@ -990,15 +1054,28 @@ void HermSet::pack(const double2 *src, const int64_t *src_off_dev, const int32_t
 }
 
 template <typename T, int MODE>
-void launch_scatter(const HermSet &H, const cplx_t<T> *yl, const cplx_t<T> *r, cplx_t<T> *y,
-                    T theta, HermSet *fwd, cplx_t<T> *fxl, hipStream_t s) {
-  const dim3 g(cdiv(H.nvec, 256));
+void launch_reduce(const HermSet &H, const cplx_t<T> *part, cplx_t<T> *yl, const cplx_t<T> *r,
+                   cplx_t<T> *y, T theta, HermSet *fwd, cplx_t<T> *fxl, hipStream_t s) {
+  const dim3 g(cdiv(H.nvec, yl ? 256 : 32));
+  const int4 *rowd = sizeof(T) == 8 ? H.rowd.p : H.srowd.p;
+  if (yl) {
+    hipLaunchKernelGGL((k_rows<T>), dim3(cdiv(H.nrows, 8)), dim3(256), 0, s, rowd,
+                       (const int2 *)nullptr, H.nrows, 1, part, yl);
+    LAUNCH_OK();
+    if (fwd)
+      hipLaunchKernelGGL((k_scatter<T, MODE, true>), g, dim3(256), 0, s, H.nvec, H.red_ptr.p,
+                         H.red_ent.p, yl, r, y, theta, fwd->red_ptr.p, fwd->red_ent.p, fxl);
+    else
+      hipLaunchKernelGGL((k_scatter<T, MODE, false>), g, dim3(256), 0, s, H.nvec, H.red_ptr.p,
+                         H.red_ent.p, yl, r, y, theta, nullptr, nullptr, nullptr);
+    return;
+  }
   if (fwd)
-    hipLaunchKernelGGL((k_scatter<T, MODE, true>), g, dim3(256), 0, s, H.nvec, H.red_ptr.p,
-                       H.red_ent.p, yl, r, y, theta, fwd->red_ptr.p, fwd->red_ent.p, fxl);
+    hipLaunchKernelGGL((k_rows_scatter<T, MODE, true>), g, dim3(256), 0, s, H.nvec, H.red_ptr.p,
+                       H.red_row.p, rowd, part, r, y, theta, fwd->red_ptr.p, fwd->red_ent.p, fxl);
   else
-    hipLaunchKernelGGL((k_scatter<T, MODE, false>), g, dim3(256), 0, s, H.nvec, H.red_ptr.p,
-                       H.red_ent.p, yl, r, y, theta, nullptr, nullptr, nullptr);
+    hipLaunchKernelGGL((k_rows_scatter<T, MODE, false>), g, dim3(256), 0, s, H.nvec, H.red_ptr.p,
+                       H.red_row.p, rowd, part, r, y, theta, nullptr, nullptr, nullptr);
 }
 
 template <typename T> cplx_t<T> *local_x(HermSet &H) {
@@ -1059,15 +1136,11 @@ void herm_apply(HermSet &H, const cplx_t<T> *x, cplx_t<T> *y, const cplx_t<T> *r
     }
   }
   ProfScope ps(H.prof, DPG_K_REDUCE, 0.0, s);
-  hipLaunchKernelGGL((k_rows<T>), dim3(cdiv(H.nrows, 8)), dim3(256), 0, s,
-                     sizeof(T) == 8 ? H.rowd.p : H.srowd.p, (const int2 *)nullptr, H.nrows, 1, part,
-                     yl);
-  LAUNCH_OK();
   switch (mode) {
-    case RED_SET: launch_scatter<T, RED_SET>(H, yl, r, y, theta, fwd, fxl, s); break;
-    case RED_RESID: launch_scatter<T, RED_RESID>(H, yl, r, y, theta, fwd, fxl, s); break;
-    case RED_AXPY: launch_scatter<T, RED_AXPY>(H, yl, r, y, theta, fwd, fxl, s); break;
-    default: launch_scatter<T, RED_SET_SCALED>(H, yl, r, y, theta, fwd, fxl, s);
+    case RED_SET: launch_reduce<T, RED_SET>(H, part, yl, r, y, theta, fwd, fxl, s); break;
+    case RED_RESID: launch_reduce<T, RED_RESID>(H, part, yl, r, y, theta, fwd, fxl, s); break;
+    case RED_AXPY: launch_reduce<T, RED_AXPY>(H, part, yl, r, y, theta, fwd, fxl, s); break;
+    default: launch_reduce<T, RED_SET_SCALED>(H, part, yl, r, y, theta, fwd, fxl, s);
   }
   LAUNCH_OK();
 }

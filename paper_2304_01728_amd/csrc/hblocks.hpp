@@ -19,7 +19,7 @@
 // preconditioner (products of the groups on the matrix cores were as fast but
 // moved them), so results do not depend on the grouping.
 //
-// Apply (four kernels, deterministic):
+// Apply (three kernels, deterministic):
 //  1. gather:  x_loc[b] = R_b x, zero-padded to 32 nt_b entries;
 //  2. columns: FP64: one wave per (block, tile column J, segment of two tile
 //     rows) loads both tiles before any arithmetic, writes A_IJ x_J (row
@@ -28,13 +28,13 @@
 //     FP32: one wave per (block, pair of tile columns J0, J1, chunk of tile
 //     rows) writes A_I,J0 x_J0 + A_I,J1 x_J1 per row I (one 32-vector per
 //     two tiles) and the column sums of both columns over the chunk;
-//  3. rows:    half a wave per (block, tile row I) adds the column partials
-//     of column I and the row partials of row I (contiguous) into y_loc[b];
-//  4. scatter: one thread per vector entry adds y_loc of every block holding
-//     it, in a fixed order, and applies the epilogue; it can also write the
-//     result into the local vector of the set applied next (the smoother
-//     after a residual, the residual after a smoother), whose gather is
-//     then left out.
+//  3. rows and scatter: eight lanes per vector entry, one per block holding it,
+//     add the column partials of its column and the row partials of its row
+//     (contiguous); the blocks' sums are added in a fixed order and the
+//     epilogue applied (large sets: the rows first, into y_loc, then the sums
+//     of these); the result can also be written into the local vector
+//     of the set applied next (the smoother after a residual, the residual
+//     after a smoother), whose gather is then left out.
 #pragma once
 #include "common.hpp"
 
@@ -74,11 +74,6 @@ struct ChunkMap {
   int32_t cnt[kMaxGroup] = {};
 };
 
-// A list inside HermSet::lists.
-template <typename T> struct DevList {
-  T *p = nullptr;
-};
-
 struct HermSet {
   int nblk = 0;
   DevBuf<int4> lists;        // every list below, in one allocation
@@ -116,10 +111,11 @@ struct HermSet {
   DevList<int4> tdesc;        // (representative block, I, J, 0) per stored tile (packing)
   DevList<int32_t> red_ptr;   // CSR over vector entries
   DevList<int32_t> red_ent;   // offsets into the local vectors
+  DevList<int32_t> red_row;   // the same rows as 32 (tile row in rowd) + row in it
   DevBuf<double2> t64;       // tiles, FP64
   DevBuf<float2> t32;        // tiles, FP32 (mixed precision)
-  DevBuf<double2> p64, xl64, yl64;   // partials and local vectors
-  DevBuf<float2> p32, xl32, yl32;
+  DevBuf<double2> p64, xl64, yl64;   // partials and local vectors (yl: large sets, and
+  DevBuf<float2> p32, xl32, yl32;    // with recomputed patches)
   Prof *prof = nullptr;      // kernel timing of the owning context
   int64_t bytes_fp64() const { return nent * 16; }
   int64_t bytes_fp32() const { return nent * 8; }
