@@ -1,11 +1,18 @@
 // Batched dense complex-FP64 kernels: Cholesky, forward solve, GEMM.
 //
 // The rank-k updates share one tile routine: a workgroup of 256 threads
-// stages 64x16 slices of op(A) and 16x64 slices of op(B) in LDS and its four
+// stages 64x8 slices of op(A) and 8x64 slices of op(B) in LDS and its four
 // waves accumulate the 64x64 complex output tile on the FP64 matrix cores
 // (v_mfma_f64_16x16x4f64), three real products per complex one.  The tile
-// kernels run two waves per SIMD: the three accumulator sets and the
-// prefetched slice take 184-192 registers, which at three waves (168) spilled.  The FP64 matrix and vector peaks of MI355X are
+// kernels run three waves per SIMD (150-160 registers of 168): 128-wide updates
+// spend a third of a tile's time on its first slice and its C entries, which the
+// other workgroups of a compute unit fill.  Batches of 88 items of order 1000,
+// slices of 16 at two waves / of 8 at three: Cholesky 3.32 / 3.04 ms, forward
+// solve 6.69 / 6.18, inverse factor 2.96 / 2.74, C = A^H B 9.38 / 9.20 (77
+// TFLOP/s; 98 at the matrix cores' FP64 rate).  Keeping a tile in registers over
+// all updates (left-looking Cholesky, whole forward solves of a column panel per
+// workgroup) was slower, 3.62 and 3.53 ms for Cholesky and inverse factor: too few
+// workgroups of too different length.  The FP64 matrix and vector peaks of MI355X are
 // equal (78.6 TFLOP/s); the matrix cores win because they reuse each operand
 // sixteen times inside the instruction, where vector FMAs would need one LDS
 // read per two complex multiply-adds.
@@ -26,14 +33,14 @@
 namespace dpg {
 namespace {
 
-constexpr int TM = 64, TN = 64, TK = 16, NT = 256, NB = 64, NBO = 128;
+constexpr int TM = 64, TN = 64, TK = 8, NT = 256, NB = 64, NBO = 128;
 // entries of a k-slice of op(A) (and of op(B)) per thread
 constexpr int QS = TM * TK / NT;
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 struct GemmSmem {
-  double2 As[TM][TK + 1];
-  double2 Bs[TK][TN + 1];
+  double2 As[2][TM][TK + 1];
+  double2 Bs[2][TK][TN + 2];
 };
 
 template <int OP> __device__ inline double2 ld_op(const double2 *X, int ldx, int r, int c) {
@@ -114,7 +121,7 @@ __device__ __forceinline__ unsigned load_slice(int m, int n, int k, int k0, int 
 
 template <int OPA, int OPB>
 __device__ __forceinline__ void store_slice(const double2 ra[QS], const double2 rb[QS], unsigned ok,
-                                            GemmSmem &sm) {
+                                            GemmSmem &sm, int u) {
   const int tid = threadIdx.x;
 #pragma unroll
   for (int q = 0; q < QS; ++q) {
@@ -122,7 +129,7 @@ __device__ __forceinline__ void store_slice(const double2 ra[QS], const double2 
     int rr, kk;
     if (OPA == OP_N) { rr = e % TM; kk = e / TM; } else { kk = e % TK; rr = e / TK; }
     const double2 v = OPA == OP_C ? cconj(ra[q]) : ra[q];
-    sm.As[rr][kk] = ((ok >> q) & 1) ? v : mk(0.0, 0.0);
+    sm.As[u][rr][kk] = ((ok >> q) & 1) ? v : mk(0.0, 0.0);
   }
 #pragma unroll
   for (int q = 0; q < QS; ++q) {
@@ -130,9 +137,15 @@ __device__ __forceinline__ void store_slice(const double2 ra[QS], const double2 
     int kk, cc;
     if (OPB == OP_N) { kk = e % TK; cc = e / TK; } else { cc = e % TN; kk = e / TN; }
     const double2 v = OPB == OP_C ? cconj(rb[q]) : rb[q];
-    sm.Bs[kk][cc] = ((ok >> (QS + q)) & 1) ? v : mk(0.0, 0.0);
+    sm.Bs[u][kk][cc] = ((ok >> (QS + q)) & 1) ? v : mk(0.0, 0.0);
   }
 }
+
+// Zeros that a tile's 16x16 blocks skip, slice by slice: op(A) one lower triangular
+// 64-wide block (nothing right of a row's diagonal entry), op(B) one upper triangular
+// one (nothing below a column's), or op(B) lower triangular from row k_begin on
+// (nothing above a column's).
+enum { TRI_NONE = 0, TRI_A = 1, TRI_B = 2, TRI_LOW_B = 3 };
 
 // C[r0:r0+64, c0:c0+64] (clipped to m x n) <- alpha op(A) op(B) + beta C with
 // inner indices k_begin..k-1.  lower_only leaves entries above the diagonal
@@ -143,12 +156,14 @@ template <int OPA, int OPB>
 __device__ __forceinline__ void gemm_tile(int m, int n, int k, int k_begin, int r0, int c0, double2 alpha,
                           const double2 *A, int lda, const double2 *B, int ldb, double2 beta,
                           double2 *C, int ldc, bool lower_only, GemmSmem &sm,
-                          bool mirror = false) {
+                          bool mirror = false, int tri = TRI_NONE) {
   const int tid = threadIdx.x;
   // FP64 matrix cores: v_mfma_f64_16x16x4f64 computes D(16x16) += A(16x4) B(4x16)
   // with A[i][k] in lane i + 16k, B[k][j] in lane j + 16k and D[i][j] in
-  // lane j + 16 (i % 4), element i / 4.  Wave w owns the 32x32 sub-tile at
-  // (32 (w / 2), 32 (w % 2)) as 2x2 blocks.  A complex product takes three
+  // lane j + 16 (i % 4), element i / 4.  Wave w owns the block rows w / 2 and
+  // 3 - w / 2 and the block columns w % 2 and 3 - w % 2 of the tile's 4x4 blocks
+  // (outer ones paired with inner ones, so that the blocks that a triangle leaves
+  // out are spread over the four SIMDs).  A complex product takes three
   // real MFMAs (the three-multiplication form): P1 = sum a_re b_re,
   // P2 = sum a_im b_im, P3 = sum (a_re + a_im)(b_re + b_im); then
   // re = P1 - P2 and im = P3 - P1 - P2.  The real part is as accurate as with
@@ -158,7 +173,8 @@ __device__ __forceinline__ void gemm_tile(int m, int n, int k, int k_begin, int 
   // three products are issued term by term so that two updates of one
   // accumulator are never adjacent.
   const int lane = tid & 63, wave = tid >> 6;
-  const int wr = 32 * (wave >> 1), wc = 32 * (wave & 1);
+  const int wr = 16 * (wave >> 1), wc = 16 * (wave & 1);
+  const int br[2] = {wr, 48 - wr}, bc[2] = {wc, 48 - wc};   // rows / columns of the blocks
   const int li = lane & 15, lk = lane >> 4;
   v4d acc_p1[2][2], acc_p2[2][2], acc_p3[2][2];
 #pragma unroll
@@ -172,29 +188,28 @@ __device__ __forceinline__ void gemm_tile(int m, int n, int k, int k_begin, int 
   // 16x16 blocks whose results are never stored take no matrix-core work:
   // those outside m x n (the ragged last tile row or column of sizes such as
   // 451 = 7 x 64 + 3) and, with lower_only, those strictly above the
-  // diagonal.  The mask is uniform over the wave; a wave with every block
-  // active runs the unguarded loop.
+  // diagonal.  The mask is uniform over the wave.
   unsigned act = 0;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int br = r0 + wr + 16 * i, bc = c0 + wc + 16 * j;
-      const bool on = br < m && bc < n && !(lower_only && bc > br + 15);
+      const bool on = r0 + br[i] < m && c0 + bc[j] < n &&
+                      !(lower_only && c0 + bc[j] > r0 + br[i] + 15);
       act |= (unsigned)on << (2 * i + j);
     }
   act = __builtin_amdgcn_readfirstlane(act);
   // The next k-slice is fetched into registers while the current one is
-  // multiplied from LDS, so global latency hides behind the matrix cores.
-  auto mma_slice = [&](auto guarded) {
-    constexpr bool G = decltype(guarded)::value;
+  // multiplied from LDS, so global latency hides behind the matrix cores; two
+  // LDS buffers, so that one barrier per slice is enough.
+  auto mma_slice = [&](unsigned act, int u) {
 #pragma unroll
     for (int ks = 0; ks < TK; ks += 4) {
       double2 a[2], b[2];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = sm.As[wr + 16 * i + li][ks + lk];
+      for (int i = 0; i < 2; ++i) a[i] = sm.As[u][br[i] + li][ks + lk];
 #pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = sm.Bs[ks + lk][wc + 16 * j + li];
+      for (int j = 0; j < 2; ++j) b[j] = sm.Bs[u][ks + lk][bc[j] + li];
       double sa[2], sb[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) sa[i] = a[i].x + a[i].y;
@@ -204,32 +219,43 @@ __device__ __forceinline__ void gemm_tile(int m, int n, int k, int k_begin, int 
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          if (!G || (act >> (2 * i + j) & 1))
+          if (act >> (2 * i + j) & 1)
             acc_p1[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].x, acc_p1[i][j], 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          if (!G || (act >> (2 * i + j) & 1))
+          if (act >> (2 * i + j) & 1)
             acc_p2[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, b[j].y, acc_p2[i][j], 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          if (!G || (act >> (2 * i + j) & 1))
+          if (act >> (2 * i + j) & 1)
             acc_p3[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(sa[i], sb[j], acc_p3[i][j], 0, 0, 0);
     }
   };
   double2 ra[QS], rb[QS];
   unsigned ok = 0;
   if (k_begin < k) ok = load_slice<OPA, OPB>(m, n, k, k_begin, r0, c0, A, lda, B, ldb, ra, rb);
+  int u = 0;
 #pragma unroll 1
   for (int k0 = k_begin; k0 < k; k0 += TK) {
-    store_slice<OPA, OPB>(ra, rb, ok, sm);
+    store_slice<OPA, OPB>(ra, rb, ok, sm, u);
     __syncthreads();
     if (k0 + TK < k) ok = load_slice<OPA, OPB>(m, n, k, k0 + TK, r0, c0, A, lda, B, ldb, ra, rb);
-    if (act) mma_slice(std::true_type{});
-    __syncthreads();
+    unsigned on = act;
+    if (tri != TRI_NONE) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (tri == TRI_A && k0 > br[i] + 15) on &= ~(3u << (2 * i));
+        if (tri == TRI_B && k0 > bc[i] + 15) on &= ~(5u << i);
+        if (tri == TRI_LOW_B && k0 + TK <= k_begin + bc[i]) on &= ~(5u << i);
+      }
+      on = __builtin_amdgcn_readfirstlane(on);
+    }
+    if (on) mma_slice(on, u);
+    u ^= 1;
   }
   // The C entries of a row block (eight per lane) are loaded together, from
   // the nearest entry inside m x n where outside (the value is then unused),
@@ -243,7 +269,7 @@ __device__ __forceinline__ void gemm_tile(int m, int n, int k, int k_begin, int 
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int r = r0 + wr + 16 * i + lk + 4 * e, c = c0 + wc + 16 * j + li;
+          const int r = r0 + br[i] + lk + 4 * e, c = c0 + bc[j] + li;
           cv[j][e] = C[min(r, m - 1) + (int64_t)min(c, n - 1) * ldc];
         }
     }
@@ -251,7 +277,7 @@ __device__ __forceinline__ void gemm_tile(int m, int n, int k, int k_begin, int 
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int r = r0 + wr + 16 * i + lk + 4 * e, c = c0 + wc + 16 * j + li;
+        const int r = r0 + br[i] + lk + 4 * e, c = c0 + bc[j] + li;
         if (r < m && c < n && (!lower_only || c <= r)) {
           const double p1 = acc_p1[i][j][e], p2 = acc_p2[i][j][e];
           double2 v = cmul(alpha, mk(p1 - p2, acc_p3[i][j][e] - p1 - p2));
@@ -650,7 +676,7 @@ __global__ __launch_bounds__(NTB, 2) void k_potrf_diag(double2 *base, const Potr
 
 // Panel below the diagonal block: X = A_panel L_kk^-H as a product with the
 // stored inverse, one 64-row tile per workgroup, in place.
-__global__ __launch_bounds__(NT, 2) void k_potrf_panel(double2 *base, const PotrfItem *items,
+__global__ __launch_bounds__(NT, 3) void k_potrf_panel(double2 *base, const PotrfItem *items,
                                                     const int *info, int k0, int kend,
                                                     const double2 *work, int wslots) {
   __shared__ GemmSmem sm;
@@ -665,12 +691,12 @@ __global__ __launch_bounds__(NT, 2) void k_potrf_panel(double2 *base, const Potr
   double2 *P = base + it.a + (k0 + kb) + (int64_t)k0 * lda;
   const double2 *W = work + ((int64_t)by * wslots + k0 / NB) * NB * NB;
   gemm_tile<OP_N, OP_C>(m, kb, kb, 0, r0, 0, mk(1.0, 0.0), P, lda, W, NB, mk(0.0, 0.0), P, lda,
-                        false, sm);
+                        false, sm, false, TRI_B);
 }
 
 // Update C[r, c] -= sum_{k in [k_lo, k_hi)} A[r, k] conj(A[c, k]) for
 // c in [c_lo, c_hi), r >= c (lower triangle only).
-__global__ __launch_bounds__(NT, 2) void k_potrf_update(double2 *base, const PotrfItem *items,
+__global__ __launch_bounds__(NT, 3) void k_potrf_update(double2 *base, const PotrfItem *items,
                                                      const int *info, int k_lo, int k_hi,
                                                      int c_lo, int c_hi, int tiles_c) {
   // tiles_c > 0: grid of tiles_c tile columns; tiles_c = 0: the lower
@@ -716,7 +742,7 @@ __global__ __launch_bounds__(NTD) void k_trsm_inv(const double2 *lbase, const Tr
 
 // Rows [k0, k0+kb) of B: X_k = L_kk^-1 B_k, one 64-column tile per workgroup,
 // in place.
-__global__ __launch_bounds__(NT, 2) void k_trsm_solve(double2 *bbase, const TrsmItem *items, int k0,
+__global__ __launch_bounds__(NT, 3) void k_trsm_solve(double2 *bbase, const TrsmItem *items, int k0,
                                                    int kend, int tri, const double2 *work,
                                                    int wslots) {
   __shared__ GemmSmem sm;
@@ -731,12 +757,12 @@ __global__ __launch_bounds__(NT, 2) void k_trsm_solve(double2 *bbase, const Trsm
   double2 *Bk = bbase + it.b + k0;
   const double2 *W = work + ((int64_t)by * wslots + k0 / NB) * NB * NB;
   gemm_tile<OP_N, OP_N>(kb, ncols, kb, 0, 0, c0, mk(1.0, 0.0), W, NB, Bk, it.ldb, mk(0.0, 0.0),
-                        Bk, it.ldb, false, sm);
+                        Bk, it.ldb, false, sm, false, TRI_A);
 }
 
 // B[r, c] -= sum_{k in [k_lo, k_hi)} L[r, k] X[k, c] for r in [r_lo, r_hi),
 // one 64x64 tile per workgroup.
-__global__ __launch_bounds__(NT, 2) void k_trsm_update(const double2 *lbase, double2 *bbase,
+__global__ __launch_bounds__(NT, 3) void k_trsm_update(const double2 *lbase, double2 *bbase,
                                                     const TrsmItem *items, int k_lo, int k_hi,
                                                     int r_lo, int r_hi, int tri, int tiles_c) {
   __shared__ GemmSmem sm;
@@ -751,7 +777,9 @@ __global__ __launch_bounds__(NT, 2) void k_trsm_update(const double2 *lbase, dou
   if (ti * TM >= m || tj * TN >= ncols) return;
   const double2 *L = lbase + it.l;
   double2 *B = bbase + it.b;
-  gemm_tile<OP_N, OP_N>(m, ncols, kw, 0, ti * TM, tj * TN, mk(-1.0, 0.0),
+  // with the identity right-hand side, rows above column tile tj are zero in it
+  const int kz = tri ? max(0, tj * TN - k_lo) : 0;
+  gemm_tile<OP_N, OP_N>(m, ncols, kw, kz, ti * TM, tj * TN, mk(-1.0, 0.0),
                         L + r_lo + (int64_t)k_lo * it.ldl, it.ldl, B + k_lo, it.ldb,
                         mk(1.0, 0.0), B + r_lo, it.ldb, false, sm);
 }
@@ -759,7 +787,7 @@ __global__ __launch_bounds__(NT, 2) void k_trsm_update(const double2 *lbase, dou
 // ---- GEMM ----------------------------------------------------------------------------
 
 template <int OPA, int OPB>
-__global__ __launch_bounds__(NT, 2) void k_gemm(double2 alpha, const double2 *abase,
+__global__ __launch_bounds__(NT, 3) void k_gemm(double2 alpha, const double2 *abase,
                                              const double2 *bbase, double2 beta, double2 *cbase,
                                              const GemmItem *items, int tiles_n, int mode) {
   __shared__ GemmSmem sm;
@@ -781,7 +809,9 @@ __global__ __launch_bounds__(NT, 2) void k_gemm(double2 alpha, const double2 *ab
     kb = c0;   // X lower triangular: rows below max(r0, c0) = c0 only
   const bool mirror = (mode == GEMM_HERM || mode == GEMM_HERM_LOWTRI) && tm < tn;
   gemm_tile<OPA, OPB>(it.m, it.n, it.k, kb, r0, c0, alpha, abase + it.a, it.lda, bbase + it.b,
-                      it.ldb, beta, cbase + it.c, it.ldc, false, sm, mirror);
+                      it.ldb, beta, cbase + it.c, it.ldc, false, sm, mirror,
+                      mode == GEMM_UPPER_LOWTRI || mode == GEMM_HERM_LOWTRI ? TRI_LOW_B
+                                                                                      : TRI_NONE);
 }
 
 template <int OPA>
