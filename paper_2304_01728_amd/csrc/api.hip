@@ -1076,6 +1076,28 @@ void build_macro_level(dpg_ctx *c, int l) {
 // parts 50.8 ms, three 50.4, four 49.5.
 constexpr int kPatchParts = 4;
 
+// Little patch work (sum of n^3 over the finest level's patches, or over their
+// classes) leaves the time to the chain of diagonal-block steps of the largest
+// patch, and four parts run that chain once per level and stream, one level after
+// the other.  Each level is then one part, consecutive levels on different extra
+// streams, and the main stream has none.  Hierarchy in four parts / in one per level,
+// ms: equal elements, 16^3, p = 3 (1.5e10) 16.3 / 12.6, 24^3, p = 2 (1.1e9) 6.0 / 3.1;
+// all patches different, 16^3, p = 2 (1.2e10) 7.8 / 6.4, 12^3, p = 3 (6e10) 22.4 / 19.6,
+// 16^3, p = 3 (1.7e11) 43.1 / 42.3, 12^3, p = 4 (4e11) 97 / 103, 24^3, p = 3 (6e11)
+// 128 / 134.  The workspaces are then whole levels', so under a memory budget the
+// four parts stay.
+constexpr double kNarrowWork = 2.5e11;
+
+double patch_work(const LevelData &f) {
+  double tot = 0.0;
+  for (int v = 0; v < f.pc.n; ++v) {
+    const int w = f.pc.rep_h[v];
+    const double n = f.mc.patch_ptr[w + 1] - f.mc.patch_ptr[w];
+    tot += n * n * n;
+  }
+  return tot;
+}
+
 void plan_patches(dpg_ctx *c, int l) {
   LevelData &f = c->lv[l];
   PatchPlan &P = f.pp;
@@ -1099,7 +1121,9 @@ void plan_patches(dpg_ctx *c, int l) {
   // and workspaces of 0.5 GB.
   const bool rec = c->opt.flags & DPG_RECOMPUTE_PATCHES;
   const int64_t ws = std::max<int64_t>((rec ? 500000000LL : 3000000000LL) / 16, maxent);
-  const int NP = rec ? 1 : kPatchParts;
+  const bool narrow = !rec && bd->limit <= 0 && patch_work(c->lv[c->L]) <= kNarrowWork;
+  const int NP = rec || narrow ? 1 : kPatchParts;
+  const int part0 = narrow ? (c->L - l) % (kPatchParts - 1) : 0;
   double tot = 0.0;
   for (int v = 0; v < np; ++v) tot += (double)nv[v] * nv[v] * nv[v];
   std::vector<int> vcut(NP + 1, np);
@@ -1122,9 +1146,9 @@ void plan_patches(dpg_ctx *c, int l) {
     for (int v = 0; v < npatch; ++v) members[f.pc.of_h[v]].push_back(v);
   int maxcnt[4] = {0, 0, 0, 0};
   int64_t maxuse[4] = {0, 0, 0, 0};   // largest batch footprint of each part (entries)
-  for (int half = 0; half < NP; ++half) {
-    int v0 = vcut[half];
-    const int vend = vcut[half + 1];
+  for (int half = part0; half < part0 + NP; ++half) {
+    int v0 = vcut[half - part0];
+    const int vend = vcut[half - part0 + 1];
     while (v0 < vend) {
       int cnt = 0;
       int64_t used = 0;
@@ -1193,7 +1217,7 @@ void plan_patches(dpg_ctx *c, int l) {
   P.ld_all.upload(ld_all, bd, s);
   P.info.ensure(np, bd);
   if (rec) grow(c->ptmp, f.Sset.nloc, bd);
-  for (int h = 0; h < NP; ++h) {
+  for (int h = part0; h < part0 + NP; ++h) {
     if (!maxcnt[h]) continue;
     if (c->pS[h].n < maxuse[h]) c->pS[h].alloc(maxuse[h], bd);
     if (c->pX[h].n < maxuse[h]) c->pX[h].alloc(maxuse[h], bd);
