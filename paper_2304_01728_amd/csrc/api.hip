@@ -12,11 +12,11 @@
 using namespace dpg;
 
 // Scratch of dpg_solve_noalloc: the reduction partials (2 kDotBlocks doubles)
-// and the eight CG scalars of the column being solved.  Each GPU the library
+// and the CG scalars of the column being solved.  Each GPU the library
 // runs on holds one copy until the process ends.  Host code never uses this
 // name as an address: dpg_setup looks up the device address once per device
 // (scratch_device_ptr) and the kernels receive that pointer.
-constexpr int kScratchDoubles = 2 * kDotBlocks + 8;
+constexpr int kScratchDoubles = 2 * kDotBlocks + kScalars;
 static __device__ __align__(256) double scratch[kScratchDoubles];
 
 namespace {
@@ -1476,12 +1476,13 @@ void smooth_apply(dpg_ctx *c, int l, const cplx_t<T> *x, cplx_t<T> *y, int mode,
 // macro unknowns are the level's traces, in order): a copy.
 template <typename T>
 void condense_level(const LevelData &g, const cplx_t<T> *WH, const cplx_t<T> *full, cplx_t<T> *cc,
-                    cplx_t<T> *out, int nr, hipStream_t s) {
+                    cplx_t<T> *out, int nr, hipStream_t s, LocalRows<T> fwd = {}) {
   if (g.order) {
     HIP_OK(hipMemcpyAsync(out, full, g.nM * nr * sizeof(cplx_t<T>), hipMemcpyDeviceToDevice, s));
   } else if (nr == 1) {
     launch_condense_local<T>(WH, g.bc.of, g.nI, g.nBf, g.blkI.p, g.nblk, full, cc, s);
-    launch_condense_reduce<T>(g.nM, g.macroB.p, g.cred_ptr.p, g.cred_ent.p, full, cc, out, s);
+    launch_condense_reduce<T>(g.nM, g.macroB.p, g.cred_ptr.p, g.cred_ent.p, full, cc, out,
+                              fwd, s);
   } else {
     launch_condense_blk<T>(WH, g.bc.of, g.nI, g.nBf, g.blkI.p, g.nblk, g.nM, g.macroB.p,
                            g.cred_ptr.p, g.cred_ent.p, full, cc, out, nr, s);
@@ -1505,21 +1506,42 @@ void expand_level(const LevelData &g, const cplx_t<T> *WH, const cplx_t<T> *Ti,
   }
 }
 
-template <typename T> void vcycle(dpg_ctx *c, int l) {
+// The rows of H's local vector, for a kernel that writes the vector they come from.
+template <typename T> LocalRows<T> rows_of(const HermSet &H) {
+  if constexpr (sizeof(T) == 8) return {H.red_ptr.p, H.red_ent.p, H.xl64.p};
+  else return {H.red_ptr.p, H.red_ent.p, H.xl32.p};
+}
+
+// Does the smoother of precision T take local vectors that other kernels wrote?
+// (Not with recomputed patches, which gather for themselves.)
+template <typename T> bool forwards(const dpg_ctx *c) {
+  return sizeof(T) == 4 || !(c->opt.flags & DPG_RECOMPUTE_PATCHES);
+}
+
+// Whose local vector the V-cycle of level l reads its right-hand side from.
+template <typename T> LocalRows<T> vcycle_rows(const dpg_ctx *c, const LevelData &f) {
+  if (!forwards<T>(c) || c->opt.nu_pre == 0) return {};
+  return rows_of<T>(f.Sset);
+}
+
+// x <- V_l(r).  rows: vcycle_rows already hold r.
+//
+// Every kernel that writes a vector forwards it to the block set that is applied to
+// it next (smoother and residual to each other, restriction to the coarse level,
+// prolongation to the first post-smoothing residual), so no application gathers.
+template <typename T>
+void vcycle(dpg_ctx *c, int l, const cplx_t<T> *r, cplx_t<T> *x, bool rows) {
   using B = LB<T>;
   LevelData &f = c->lv[l];
   const hipStream_t s = c->stream;
   const T th = (T)c->opt.theta;
-  auto r = B::r(f), x = B::x(f), res = B::res(f), rc = B::rc(f), ec = B::ec(f);
-  // With stored patch inverses every smoother application forwards the new x
-  // to the residual's block set and every residual forwards r - Mx to the
-  // smoother's (the scatter writes their local vectors), so neither gathers.
-  const bool fw = sizeof(T) == 4 || !(c->opt.flags & DPG_RECOMPUTE_PATCHES);
+  auto res = B::res(f), rc = B::rc(f), ec = B::ec(f);
+  const bool fw = forwards<T>(c);
   HermSet *toM = fw ? &f.Mset : nullptr, *toS = fw ? &f.Sset : nullptr;
   if (c->opt.nu_pre == 0) launch_zero(f.nM, x, s);
   for (int k = 0; k < c->opt.nu_pre; ++k) {
     if (k == 0) {
-      smooth_apply<T>(c, l, r, x, RED_SET_SCALED, th, false, toM);
+      smooth_apply<T>(c, l, r, x, RED_SET_SCALED, th, rows && fw, toM);
     } else {
       herm_apply<T>(f.Mset, x, res, r, RED_RESID, (T)0, s, fw, toS);
       smooth_apply<T>(c, l, res, x, RED_AXPY, th, fw, toM);
@@ -1527,27 +1549,33 @@ template <typename T> void vcycle(dpg_ctx *c, int l) {
   }
   herm_apply<T>(f.Mset, x, res, r, RED_RESID, (T)0, s, fw && c->opt.nu_pre > 0);
   LevelData &g = c->lv[l - 1];
+  const bool low = l - 1 == 0;
   {
     PROF(DPG_K_TRANSFER, 0);
-    launch_csr<T>(g.num.n, f.Ptptr.p, f.Ptcol.p, B::Ptv(f), res, rc, 0, s);
+    launch_csr<T>(g.num.n, f.Ptptr.p, f.Ptcol.p, B::Ptv(f), res, rc, 0,
+                  low ? rows_of<T>(c->T0set) : g.order ? vcycle_rows<T>(c, g) : LocalRows<T>{}, s);
   }
-  if (l - 1 == 0) {
-    herm_apply<T>(c->T0set, rc, ec, nullptr, RED_SET, (T)1, s);
+  if (low) {
+    herm_apply<T>(c->T0set, rc, ec, nullptr, RED_SET, (T)1, s, true);
+  } else if (g.order) {   // the level's unknowns are its traces: nothing to condense
+    vcycle<T>(c, l - 1, rc, ec, true);
   } else {
     {
       PROF(DPG_K_CONDENSE, 0);
-      condense_level<T>(g, B::WH(g), rc, B::cc(g), B::r(g), 1, s);
+      condense_level<T>(g, B::WH(g), rc, B::cc(g), B::r(g), 1, s, vcycle_rows<T>(c, g));
     }
-    vcycle<T>(c, l - 1);
+    vcycle<T>(c, l - 1, B::r(g), B::x(g), true);
     PROF(DPG_K_EXPAND, 0);
     expand_level<T>(g, B::WH(g), B::Ti(g), rc, B::x(g), ec, 1, s);
   }
+  const bool post = fw && c->opt.nu_post > 0;
   {
     PROF(DPG_K_TRANSFER, 0);
-    launch_csr<T>(f.nM, f.Pptr.p, f.Pcol.p, B::Pv(f), ec, x, 1, s);
+    launch_csr<T>(f.nM, f.Pptr.p, f.Pcol.p, B::Pv(f), ec, x, 1,
+                  post ? rows_of<T>(f.Mset) : LocalRows<T>{}, s);
   }
   for (int k = 0; k < c->opt.nu_post; ++k) {
-    herm_apply<T>(f.Mset, x, res, r, RED_RESID, (T)0, s, fw && k > 0, toS);
+    herm_apply<T>(f.Mset, x, res, r, RED_RESID, (T)0, s, fw, toS);
     smooth_apply<T>(c, l, res, x, RED_AXPY, th, fw, k + 1 < c->opt.nu_post ? toM : nullptr);
   }
 }
@@ -1558,12 +1586,10 @@ void precondition(dpg_ctx *c, const double2 *r, double2 *z) {
   const hipStream_t s = c->stream;
   if (c->opt.precision == DPG_MIXED) {
     launch_to32(top.nM, r, top.r32.p, s);
-    vcycle<float>(c, c->L);
+    vcycle<float>(c, c->L, top.r32.p, top.x32.p, false);
     launch_to64(top.nM, top.x32.p, z, s);
   } else {
-    HIP_OK(hipMemcpyAsync(top.r64.p, r, top.nM * 16, hipMemcpyDeviceToDevice, s));
-    vcycle<double>(c, c->L);
-    HIP_OK(hipMemcpyAsync(z, top.x64.p, top.nM * 16, hipMemcpyDeviceToDevice, s));
+    vcycle<double>(c, c->L, r, z, false);
   }
 }
 
@@ -1593,7 +1619,7 @@ template <class F> hipGraphExec_t capture(hipStream_t s, F &&f) {
 
 // PCG on the finest macro grid for one trace right-hand side s (device);
 // full trace solution into xout (device).  Returns DPG_OK / ENOCONV.
-// partial (2 kDotBlocks doubles) and sc (8 doubles) hold the reduction
+// partial (2 kDotBlocks doubles) and sc (kScalars doubles) hold the reduction
 // partials and the CG scalars; graphs: replay the iteration as HIP graphs
 // (instantiated per call) instead of launching every kernel.
 int solve_one(dpg_ctx *c, const double2 *sv, double tol, double2 *xout, int32_t *iters,
@@ -1602,7 +1628,7 @@ int solve_one(dpg_ctx *c, const double2 *sv, double tol, double2 *xout, int32_t 
   const hipStream_t s = c->stream;
   const int64_t nM = top.nM;
   condense_level<double>(top, top.WH.p, sv, top.c64.p, c->b.p, 1, s);
-  launch_zero(4, reinterpret_cast<double2 *>(sc), s);   // the 8 scalars
+  launch_zero(kScalars / 2, reinterpret_cast<double2 *>(sc), s);
   dot_re(nM, c->b.p, c->b.p, partial, sc + 5, s);
   launch_zero(nM, c->x.p, s);
   HIP_OK(hipMemcpyAsync(c->r.p, c->b.p, nM * 16, hipMemcpyDeviceToDevice, s));
@@ -1615,25 +1641,31 @@ int solve_one(dpg_ctx *c, const double2 *sv, double tol, double2 *xout, int32_t 
   if (bb > 0.0) {
     double2 *z = c->z.p, *zo = c->zo.p;
     precondition(c, c->r.p, z);
-    dot_re(nM, c->r.p, z, partial, sc + 0, s);
-    HIP_OK(hipMemcpyAsync(c->pv.p, z, nM * 16, hipMemcpyDeviceToDevice, s));
+    dot_re(nM, c->r.p, z, partial, sc + 8, s);
+    const bool mixed = c->opt.precision == DPG_MIXED;
+    const LocalRows<double> pM = rows_of<double>(top.Mset);
+    const LocalRows<double> rS = mixed ? LocalRows<double>{} : vcycle_rows<double>(c, top);
+    const LocalRows<float> rS32 = mixed ? vcycle_rows<float>(c, top) : LocalRows<float>{};
+    cg_first_direction(nM, z, c->pv.p, pM, s);
     rr = 1.0;
     // One iteration is two fixed launch sequences around the host's
     // convergence check: (A) matvec, alpha, x and r; (B) V-cycle, beta, p.
     // Without per-kernel profiling they are captured once per solve as HIP
     // graphs and replayed (B in two versions: z and z_old swap every
-    // iteration), which removes the launch gaps between the ~105 kernels.
+    // iteration), which removes the launch gaps between the kernels.  The vectors
+    // of an iteration reach the local vectors of the block sets that are applied to
+    // them, and FP32, inside the kernels that write them.
     auto part_a = [&]() {
-      herm_apply<double>(top.Mset, c->pv.p, c->q.p, nullptr, RED_SET, 1.0, s);
+      herm_apply<double>(top.Mset, c->pv.p, c->q.p, nullptr, RED_SET, 1.0, s, true);
       PROF(DPG_K_CG, 0);
-      cg_alpha(nM, c->pv.p, c->q.p, partial, sc, s);
-      cg_update_xr(nM, c->x.p, c->r.p, c->pv.p, c->q.p, partial, sc, s);
+      cg_step(nM, c->x.p, c->r.p, c->pv.p, c->q.p, mixed ? top.r32.p : nullptr, rS, rS32, partial,
+              sc, s);
     };
     auto part_b = [&](double2 *zn, double2 *zp) {
-      precondition(c, c->r.p, zn);
+      if (mixed) vcycle<float>(c, c->L, top.r32.p, top.x32.p, true);
+      else vcycle<double>(c, c->L, c->r.p, zn, true);
       PROF(DPG_K_CG, 0);
-      cg_beta(nM, c->r.p, zn, zp, partial, sc, s);
-      cg_update_p(nM, c->pv.p, zn, sc, s);
+      cg_direction(nM, c->r.p, mixed ? top.x32.p : nullptr, zn, zp, c->pv.p, pM, partial, sc, s);
     };
     GraphSet gs;
     graphs = graphs && !c->prof.on;
@@ -2407,7 +2439,7 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
     c->xfull.alloc(nT, &c->bud);
     c->sB.alloc(nT, &c->bud);
     c->partial.alloc(2 * kDotBlocks, &c->bud);
-    c->sc.alloc(8, &c->bud);
+    c->sc.alloc(kScalars, &c->bud);
     HIP_OK(hipHostMalloc((void **)&c->host_sc, 8 * sizeof(double), 0));
     // (the bytes without sharing decide, so that what can be recovered does
     // not depend on the medium)
@@ -2637,7 +2669,7 @@ int dpg_solve_noalloc(dpg_ctx *c, const double *rhs, int nrhs, double tol, doubl
       throw DpgError(DPG_ESTATE, "kernel profiling creates events: switch it off for this call");
     // The scratch holds the reductions of one column; columns are solved one
     // after the other, so every size the context accepts fits.
-    static_assert(2 * kDotBlocks + 8 <= kScratchDoubles, "solve scratch too small");
+    static_assert(2 * kDotBlocks + kScalars <= kScratchDoubles, "solve scratch too small");
     double *sp = scratch_device_ptr(c->device, false);
     if (!sp) throw DpgError(DPG_ESTATE, "solve scratch not set up on this device");
     auto t0 = clk::now();

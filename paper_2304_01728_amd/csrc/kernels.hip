@@ -1,6 +1,8 @@
 // Hierarchy-setup and solve-phase kernels (see kernels.hpp).
 #include "kernels.hpp"
 
+#include <algorithm>
+
 #include "hblocks.hpp"
 
 namespace dpg {
@@ -242,18 +244,27 @@ __global__ __launch_bounds__(256) void k_assemble_dense(const double2 *__restric
 // ---- solve phase --------------------------------------------------------------------
 
 template <typename T>
+__device__ __forceinline__ void forward(const LocalRows<T> &f, int64_t d, cplx_t<T> v) {
+  if (!f.ptr) return;
+  for (int32_t k = f.ptr[d]; k < f.ptr[d + 1]; ++k) f.xl[f.ent[k]] = v;
+}
+
+template <typename T>
 __global__ __launch_bounds__(256) void k_csr(int64_t nrows, const int64_t *__restrict__ ptr,
                                              const int32_t *__restrict__ col,
                                              const T *__restrict__ val,
                                              const cplx_t<T> *__restrict__ x,
-                                             cplx_t<T> *__restrict__ y, int add) {
+                                             cplx_t<T> *__restrict__ y, int add,
+                                             LocalRows<T> fwd) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= nrows) return;
   cplx_t<T> acc;
   acc.x = 0;
   acc.y = 0;
   for (int64_t k = ptr[i]; k < ptr[i + 1]; ++k) acc = cadd(acc, cscale(x[col[k]], val[k]));
-  y[i] = add ? cadd(y[i], acc) : acc;
+  const cplx_t<T> v = add ? cadd(y[i], acc) : acc;
+  y[i] = v;
+  forward(fwd, i, v);
 }
 
 // One workgroup per (block, 64 boundary slots): wave w sums the interior
@@ -300,12 +311,14 @@ __global__ __launch_bounds__(256) void k_condense_reduce(int64_t nM,
                                                          const int32_t *__restrict__ red_ent,
                                                          const cplx_t<T> *__restrict__ rc,
                                                          const cplx_t<T> *__restrict__ c,
-                                                         cplx_t<T> *__restrict__ rB) {
+                                                         cplx_t<T> *__restrict__ rB,
+                                                         LocalRows<T> fwd) {
   const int64_t m = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (m >= nM) return;
   cplx_t<T> acc = rc[macro_B[m]];
   for (int32_t k = red_ptr[m]; k < red_ptr[m + 1]; ++k) acc = csub(acc, c[red_ent[k]]);
   rB[m] = acc;
+  forward(fwd, m, acc);
 }
 
 template <typename C> __device__ inline C wave_sum(C v) {
@@ -526,12 +539,20 @@ __global__ __launch_bounds__(256) void k_dot_partial(int64_t n, const double2 *_
 }
 
 __global__ __launch_bounds__(256) void k_dot2_partial(int64_t n, const double2 *__restrict__ r,
-                                                      const double2 *__restrict__ z,
+                                                      const float2 *__restrict__ z32,
+                                                      double2 *__restrict__ z,
                                                       const double2 *__restrict__ zo,
                                                       double *__restrict__ partial) {
   double s = 0.0, t = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    s += r[i].x * z[i].x + r[i].y * z[i].y;
+    double2 v;
+    if (z32) {
+      v = mk((double)z32[i].x, (double)z32[i].y);
+      z[i] = v;
+    } else {
+      v = z[i];
+    }
+    s += r[i].x * v.x + r[i].y * v.y;
     t += r[i].x * zo[i].x + r[i].y * zo[i].y;
   }
   s = block_sum(s);
@@ -548,54 +569,72 @@ __device__ inline double sum_partials(const double *partial) {
   return block_sum(s);
 }
 
-// mode 0: dst = sum; 1: pq / alpha; 2: ||r||^2; 3: beta
-__global__ __launch_bounds__(256) void k_final(const double *__restrict__ partial, double *dst,
-                                               double *sc, int mode) {
+__global__ __launch_bounds__(256) void k_final(const double *__restrict__ partial, double *dst) {
   const double s = sum_partials(partial);
-  double t = 0.0;
-  if (mode == 3) t = sum_partials(partial + kDotBlocks);
-  if (threadIdx.x != 0) return;
-  if (mode == 0) {
-    *dst = s;
-  } else if (mode == 1) {
-    sc[1] = s;
-    if (!(s > 0.0) || !isfinite(s)) sc[6] = 1.0;
-    sc[2] = sc[0] / s;
-  } else if (mode == 2) {
-    sc[4] = s;
-  } else {
-    // flexible (Polak-Ribiere) beta = Re(r^H (z - z_old)) / Re(r_old^H z_old)
-    sc[3] = (s - t) / sc[0];
-    sc[7] = t;
-    sc[0] = s;
-    if (!isfinite(sc[3])) sc[6] = 1.0;
-  }
+  if (threadIdx.x == 0) *dst = s;
 }
 
-__global__ __launch_bounds__(256) void k_update_xr(int64_t n, double2 *__restrict__ x,
-                                                   double2 *__restrict__ r,
-                                                   const double2 *__restrict__ p,
-                                                   const double2 *__restrict__ q,
-                                                   double *__restrict__ partial,
-                                                   const double *__restrict__ sc) {
-  const double a = sc[2];
+// Bound by the launch on small problems (2.3 us of a 4 us gap at 4^3) and by the
+// five vectors it streams on large ones; every workgroup adds the 512 partial sums
+// of p^H q itself, which costs less than the launch between two kernels.  partial:
+// those sums, then the sums of ||r||^2 written here.
+__global__ __launch_bounds__(256) void k_cg_step(int64_t n, double2 *__restrict__ x,
+                                                 double2 *__restrict__ r,
+                                                 const double2 *__restrict__ p,
+                                                 const double2 *__restrict__ q,
+                                                 float2 *__restrict__ r32,
+                                                 LocalRows<double> fwd64, LocalRows<float> fwd32,
+                                                 double *__restrict__ partial,
+                                                 double *__restrict__ sc) {
+  const double pq = sum_partials(partial), rz = sc[8], a = rz / pq;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    sc[0] = rz;
+    sc[1] = pq;
+    sc[2] = a;
+    if (!(pq > 0.0) || !isfinite(pq)) sc[6] = 1.0;
+  }
   double s = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
     x[i] = mk(x[i].x + a * p[i].x, x[i].y + a * p[i].y);
     const double2 ri = mk(r[i].x - a * q[i].x, r[i].y - a * q[i].y);
     r[i] = ri;
     s += ri.x * ri.x + ri.y * ri.y;
+    if (r32) {
+      const float2 v = mkf((float)ri.x, (float)ri.y);
+      r32[i] = v;
+      forward(fwd32, i, v);
+    } else {
+      forward(fwd64, i, ri);
+    }
   }
   s = block_sum(s);
-  if (threadIdx.x == 0) partial[blockIdx.x] = s;
+  if (threadIdx.x == 0) partial[kDotBlocks + blockIdx.x] = s;
 }
 
-__global__ __launch_bounds__(256) void k_update_p(int64_t n, double2 *__restrict__ p,
-                                                  const double2 *__restrict__ z,
-                                                  const double *__restrict__ sc) {
-  const double b = sc[3];
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = mk(z[i].x + b * p[i].x, z[i].y + b * p[i].y);
+// sums: the kDotBlocks sums of r^H z and r^H z_old, and the flexible (Polak-Ribiere)
+// beta = Re(r^H (z - z_old)) / Re(r_old^H z_old) of them, in every workgroup; null:
+// p = z.
+__global__ __launch_bounds__(256) void k_cg_direction(int64_t n, double2 *__restrict__ p,
+                                                      const double2 *__restrict__ z,
+                                                      const double *__restrict__ sums,
+                                                      LocalRows<double> fwd,
+                                                      double *__restrict__ sc) {
+  double b = 0.0;
+  if (sums) {
+    const double s = sum_partials(sums), t = sum_partials(sums + kDotBlocks);
+    b = (s - t) / sc[0];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      sc[3] = b;
+      sc[7] = t;
+      sc[8] = s;
+      if (!isfinite(b)) sc[6] = 1.0;
+    }
+  }
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const double2 v = sums ? mk(z[i].x + b * p[i].x, z[i].y + b * p[i].y) : z[i];
+    p[i] = v;
+    forward(fwd, i, v);
+  }
 }
 
 }  // namespace
@@ -669,10 +708,10 @@ void launch_assemble_dense(const double2 *E, int n_tr, const int32_t *ecls, cons
 
 template <typename T>
 void launch_csr(int64_t nrows, const int64_t *ptr, const int32_t *col, const T *val,
-                const cplx_t<T> *x, cplx_t<T> *y, int add, hipStream_t s) {
+                const cplx_t<T> *x, cplx_t<T> *y, int add, LocalRows<T> fwd, hipStream_t s) {
   if (nrows <= 0) return;
   hipLaunchKernelGGL((k_csr<T>), dim3(cdiv(nrows, 256)), dim3(256), 0, s, nrows, ptr, col, val, x,
-                     y, add);
+                     y, add, fwd);
   LAUNCH_OK();
 }
 
@@ -689,9 +728,9 @@ void launch_condense_local(const cplx_t<T> *WH, const int32_t *bcls, int nI, int
 template <typename T>
 void launch_condense_reduce(int64_t nM, const int64_t *macro_B, const int32_t *red_ptr,
                             const int32_t *red_ent, const cplx_t<T> *rc, const cplx_t<T> *c,
-                            cplx_t<T> *rB, hipStream_t s) {
+                            cplx_t<T> *rB, LocalRows<T> fwd, hipStream_t s) {
   hipLaunchKernelGGL((k_condense_reduce<T>), dim3(cdiv(nM, 256)), dim3(256), 0, s, nM, macro_B,
-                     red_ptr, red_ent, rc, c, rB);
+                     red_ptr, red_ent, rc, c, rB, fwd);
   LAUNCH_OK();
 }
 
@@ -765,40 +804,43 @@ void launch_to64(int64_t n, const float2 *a, double2 *b, hipStream_t s) {
 void dot_re(int64_t n, const double2 *a, const double2 *b, double *partial, double *dst,
             hipStream_t s) {
   hipLaunchKernelGGL(k_dot_partial, dim3(kDotBlocks), dim3(256), 0, s, n, a, b, partial);
-  hipLaunchKernelGGL(k_final, dim3(1), dim3(256), 0, s, partial, dst, (double *)nullptr, 0);
+  hipLaunchKernelGGL(k_final, dim3(1), dim3(256), 0, s, partial, dst);
   LAUNCH_OK();
 }
 
-void cg_alpha(int64_t n, const double2 *p, const double2 *q, double *partial, double *sc,
-              hipStream_t s) {
+void cg_step(int64_t n, double2 *x, double2 *r, const double2 *p, const double2 *q, float2 *r32,
+             LocalRows<double> fwd64, LocalRows<float> fwd32, double *partial, double *sc,
+             hipStream_t s) {
   hipLaunchKernelGGL(k_dot_partial, dim3(kDotBlocks), dim3(256), 0, s, n, p, q, partial);
-  hipLaunchKernelGGL(k_final, dim3(1), dim3(256), 0, s, partial, (double *)nullptr, sc, 1);
+  hipLaunchKernelGGL(k_cg_step, dim3(kDotBlocks), dim3(256), 0, s, n, x, r, p, q, r32, fwd64,
+                     fwd32, partial, sc);
+  hipLaunchKernelGGL(k_final, dim3(1), dim3(256), 0, s, partial + kDotBlocks, sc + 4);
   LAUNCH_OK();
 }
 
-void cg_update_xr(int64_t n, double2 *x, double2 *r, const double2 *p, const double2 *q,
-                  double *partial, double *sc, hipStream_t s) {
-  hipLaunchKernelGGL(k_update_xr, dim3(kDotBlocks), dim3(256), 0, s, n, x, r, p, q, partial, sc);
-  hipLaunchKernelGGL(k_final, dim3(1), dim3(256), 0, s, partial, (double *)nullptr, sc, 2);
+// at most this many workgroups add the partial sums of a direction
+constexpr int64_t kDirBlocks = 2048;
+
+void cg_direction(int64_t n, const double2 *r, const float2 *z32, double2 *z, const double2 *zold,
+                  double2 *p, LocalRows<double> fwd, double *partial, double *sc, hipStream_t s) {
+  hipLaunchKernelGGL(k_dot2_partial, dim3(kDotBlocks), dim3(256), 0, s, n, r, z32, z, zold,
+                     partial);
+  hipLaunchKernelGGL(k_cg_direction, dim3(std::min<int64_t>(cdiv(n, 256), kDirBlocks)), dim3(256),
+                     0, s, n, p, z, partial, fwd, sc);
   LAUNCH_OK();
 }
 
-void cg_beta(int64_t n, const double2 *r, const double2 *z, const double2 *zold, double *partial,
-             double *sc, hipStream_t s) {
-  hipLaunchKernelGGL(k_dot2_partial, dim3(kDotBlocks), dim3(256), 0, s, n, r, z, zold, partial);
-  hipLaunchKernelGGL(k_final, dim3(1), dim3(256), 0, s, partial, (double *)nullptr, sc, 3);
-  LAUNCH_OK();
-}
-
-void cg_update_p(int64_t n, double2 *p, const double2 *z, const double *sc, hipStream_t s) {
-  hipLaunchKernelGGL(k_update_p, dim3(cdiv(n, 256)), dim3(256), 0, s, n, p, z, sc);
+void cg_first_direction(int64_t n, const double2 *z, double2 *p, LocalRows<double> fwd,
+                        hipStream_t s) {
+  hipLaunchKernelGGL(k_cg_direction, dim3(std::min<int64_t>(cdiv(n, 256), kDirBlocks)), dim3(256),
+                     0, s, n, p, z, (const double *)nullptr, fwd, (double *)nullptr);
   LAUNCH_OK();
 }
 
 template void launch_csr<double>(int64_t, const int64_t *, const int32_t *, const double *,
-                                 const double2 *, double2 *, int, hipStream_t);
+                                 const double2 *, double2 *, int, LocalRows<double>, hipStream_t);
 template void launch_csr<float>(int64_t, const int64_t *, const int32_t *, const float *,
-                                const float2 *, float2 *, int, hipStream_t);
+                                const float2 *, float2 *, int, LocalRows<float>, hipStream_t);
 template void launch_condense_local<double>(const double2 *, const int32_t *, int, int,
                                             const int32_t *, int, const double2 *, double2 *,
                                             hipStream_t);
@@ -807,10 +849,10 @@ template void launch_condense_local<float>(const float2 *, const int32_t *, int,
                                            hipStream_t);
 template void launch_condense_reduce<double>(int64_t, const int64_t *, const int32_t *,
                                              const int32_t *, const double2 *, const double2 *,
-                                             double2 *, hipStream_t);
+                                             double2 *, LocalRows<double>, hipStream_t);
 template void launch_condense_reduce<float>(int64_t, const int64_t *, const int32_t *,
                                             const int32_t *, const float2 *, const float2 *,
-                                            float2 *, hipStream_t);
+                                            float2 *, LocalRows<float>, hipStream_t);
 template void launch_expand<double>(const double2 *, const double2 *, const int32_t *, int, int,
                                     const int32_t *, const int32_t *, int, const double2 *,
                                     const double2 *, int64_t, const int64_t *, double2 *,

@@ -53,10 +53,19 @@ void launch_assemble_dense(const double2 *E, int n_tr, const int32_t *ecls, cons
 
 // ---- solve phase ---------------------------------------------------------------
 
+// Where a kernel that writes a vector also puts the rows of a block set's local
+// vectors: entry d goes to xl[ent[k]], k in [ptr[d], ptr[d + 1]) (ptr null:
+// nowhere).  The set's next application then gathers nothing, which saves one
+// launch, about 4 us, per application.
+template <typename T> struct LocalRows {
+  const int32_t *ptr = nullptr, *ent = nullptr;
+  cplx_t<T> *xl = nullptr;
+};
+
 // y[i] = sum_k val[k] x[col[k]] over CSR rows (mode 0: set, 1: add).
 template <typename T>
 void launch_csr(int64_t nrows, const int64_t *ptr, const int32_t *col, const T *val,
-                const cplx_t<T> *x, cplx_t<T> *y, int add, hipStream_t s);
+                const cplx_t<T> *x, cplx_t<T> *y, int add, LocalRows<T> fwd, hipStream_t s);
 
 // Macro condensation of a trace vector rc through the blocks of one level.
 // Per class of equal blocks: WH = (T_II^-1 T_IB)^H (nBf x nI), Tinv =
@@ -70,7 +79,7 @@ void launch_condense_local(const cplx_t<T> *WH, const int32_t *bcls, int nI, int
 template <typename T>
 void launch_condense_reduce(int64_t nM, const int64_t *macro_B, const int32_t *red_ptr,
                             const int32_t *red_ent, const cplx_t<T> *rc, const cplx_t<T> *c,
-                            cplx_t<T> *rB, hipStream_t s);
+                            cplx_t<T> *rB, LocalRows<T> fwd, hipStream_t s);
 // ec[macro_B[m]] = eB[m]; ec[I_b] = Tinv_b rc[I_b] - WH_b^H eB_b.
 template <typename T>
 void launch_expand(const cplx_t<T> *WH, const cplx_t<T> *Tinv, const int32_t *bcls, int nI,
@@ -120,17 +129,26 @@ void launch_to32(int64_t n, const double2 *a, float2 *b, hipStream_t s);
 void launch_to64(int64_t n, const float2 *a, double2 *b, hipStream_t s);
 
 // ---- CG vector algebra (FP64) ---------------------------------------------------
-// Device scalars: sc[0] = rz, sc[1] = pq, sc[2] = alpha, sc[3] = beta,
-// sc[4] = ||r||^2, sc[5] = ||b||^2, sc[6] = breakdown flag, sc[7] = r^H z_old.
-constexpr int kDotBlocks = 512;
+// Device scalars: sc[0] = rz of the iteration before, sc[1] = pq, sc[2] = alpha,
+// sc[3] = beta, sc[4] = ||r||^2, sc[5] = ||b||^2, sc[6] = breakdown flag,
+// sc[7] = r^H z_old, sc[8] = rz.  The dot products leave kDotBlocks partial sums
+// each; the kernel that needs the sum adds them in every workgroup, in the order
+// of dot_re, instead of a launch of its own in between (workgroup 0 stores it).  A
+// kernel never writes a scalar that it reads, which is why rz has two.
+constexpr int kDotBlocks = 512, kScalars = 16;
 void dot_re(int64_t n, const double2 *a, const double2 *b, double *partial, double *dst,
             hipStream_t s);                                  // dst = Re(a^H b)
-void cg_alpha(int64_t n, const double2 *p, const double2 *q, double *partial, double *sc,
-              hipStream_t s);                                // pq, alpha = rz / pq
-void cg_update_xr(int64_t n, double2 *x, double2 *r, const double2 *p, const double2 *q,
-                  double *partial, double *sc, hipStream_t s);  // x += a p, r -= a q, ||r||^2
-void cg_beta(int64_t n, const double2 *r, const double2 *z, const double2 *zold, double *partial,
-             double *sc, hipStream_t s);                     // beta (flexible), rz <- r^H z
-void cg_update_p(int64_t n, double2 *p, const double2 *z, const double *sc, hipStream_t s);
+// pq, alpha = rz / pq; x += alpha p, r -= alpha q, ||r||^2.  r32 (or null) receives
+// the new r in FP32; its (else r's) rows go to fwd32 (fwd64).
+void cg_step(int64_t n, double2 *x, double2 *r, const double2 *p, const double2 *q, float2 *r32,
+             LocalRows<double> fwd64, LocalRows<float> fwd32, double *partial, double *sc,
+             hipStream_t s);
+// beta (flexible), rz <- r^H z; p <- z + beta p, whose rows go to fwd.  With z32
+// (else null), z is that vector's FP64 copy, written here.
+void cg_direction(int64_t n, const double2 *r, const float2 *z32, double2 *z, const double2 *zold,
+                  double2 *p, LocalRows<double> fwd, double *partial, double *sc, hipStream_t s);
+// p = z, with the same rows
+void cg_first_direction(int64_t n, const double2 *z, double2 *p, LocalRows<double> fwd,
+                        hipStream_t s);
 
 }  // namespace dpg
