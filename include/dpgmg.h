@@ -261,7 +261,7 @@ int dpg_batch_close(dpg_ctx *ctx);
  * it), but the call allocates nothing: no hipMalloc or hipFree, no HIP graph
  * instantiation (every kernel is launched directly on the context's stream),
  * no library routine that allocates.  The CG reduction partials and scalars
- * live in a static device array of the library (8,256 bytes per GPU, held
+ * live in a static device array of the library (8,320 bytes per GPU, held
  * until the process ends) instead of the context's buffers; the vectors are
  * the ones dpg_setup allocated.  Every size the context accepts fits, since
  * the array holds one column's reductions.  All calls on one GPU share that

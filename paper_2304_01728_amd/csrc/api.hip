@@ -1617,23 +1617,49 @@ template <class F> hipGraphExec_t capture(hipStream_t s, F &&f) {
   return e;
 }
 
+// Host: wait for report number n of the solve on the context's stream, and
+// read it: ||b||^2, ||r||^2, pq, the breakdown flag.
+std::array<double, 4> wait_report(dpg_ctx *c, double n) {
+  double *w = c->host_report;
+  auto there = [&]() {
+    double v;
+    __atomic_load(&w[4], &v, __ATOMIC_ACQUIRE);
+    return v == n;
+  };
+  const auto t0 = clk::now();
+  for (uint32_t k = 1; !there(); ++k) {
+    __builtin_ia32_pause();
+    if ((k & 1023) == 0 && ms_since(t0) > 20.0) {   // a long iteration, or a failed one
+      HIP_OK(hipStreamSynchronize(c->stream));
+      if (!there()) throw DpgError(DPG_EDEVICE, "the solve's kernels left no report");
+    }
+  }
+  return {w[0], w[1], w[2], w[3]};
+}
+
+// The V-cycle of the next iteration is queued before this one's residual is
+// known while the residual is expected to stay this far above the tolerance (the
+// reduction of the iteration before, again): the GPU then never waits for the host.
+// Wrongly queued it would be a V-cycle for nothing; its results are not used.
+constexpr double kAhead = 10.0;
+
 // PCG on the finest macro grid for one trace right-hand side s (device);
-// full trace solution into xout (device).  Returns DPG_OK / ENOCONV.
-// partial (2 kDotBlocks doubles) and sc (kScalars doubles) hold the reduction
-// partials and the CG scalars; graphs: replay the iteration as HIP graphs
-// (instantiated per call) instead of launching every kernel.
+// full trace solution into xout (device), on the context's stream when the call
+// returns.  Returns DPG_OK / ENOCONV.  partial (2 kDotBlocks doubles) and sc
+// (kScalars doubles) hold the reduction partials and the CG scalars.
 int solve_one(dpg_ctx *c, const double2 *sv, double tol, double2 *xout, int32_t *iters,
-              double *relres, double *partial, double *sc, bool graphs) {
+              double *relres, double *partial, double *sc) {
   LevelData &top = c->lv[c->L];
   const hipStream_t s = c->stream;
   const int64_t nM = top.nM;
+  double *report = c->host_report;
+  report[4] = 0.0;
   condense_level<double>(top, top.WH.p, sv, top.c64.p, c->b.p, 1, s);
   launch_zero(kScalars / 2, reinterpret_cast<double2 *>(sc), s);
-  dot_re(nM, c->b.p, c->b.p, partial, sc + 5, s);
+  cg_start(nM, c->b.p, partial, sc, c->dev_report, s);
   launch_zero(nM, c->x.p, s);
   HIP_OK(hipMemcpyAsync(c->r.p, c->b.p, nM * 16, hipMemcpyDeviceToDevice, s));
-  read_sc(c, sc);
-  const double bb = c->host_sc[5];
+  const double bb = wait_report(c, 1.0)[0];
   int it = 0;
   double rr = 0.0;
   int status = DPG_OK;
@@ -1648,51 +1674,46 @@ int solve_one(dpg_ctx *c, const double2 *sv, double tol, double2 *xout, int32_t 
     const LocalRows<float> rS32 = mixed ? vcycle_rows<float>(c, top) : LocalRows<float>{};
     cg_first_direction(nM, z, c->pv.p, pM, s);
     rr = 1.0;
-    // One iteration is two fixed launch sequences around the host's
-    // convergence check: (A) matvec, alpha, x and r; (B) V-cycle, beta, p.
-    // Without per-kernel profiling they are captured once per solve as HIP
-    // graphs and replayed (B in two versions: z and z_old swap every
-    // iteration), which removes the launch gaps between the kernels.  The vectors
-    // of an iteration reach the local vectors of the block sets that are applied to
-    // them, and FP32, inside the kernels that write them.
+    // One iteration is two launch sequences around the host's convergence
+    // check: (A) matvec, alpha, x and r; (B) V-cycle, beta, p.  The vectors of
+    // an iteration reach the local vectors of the block sets that are applied
+    // to them, and FP32, inside the kernels that write them.  The launches are
+    // not captured as HIP graphs: while the GPU never waits for the host (kAhead),
+    // replayed graphs save nothing (4.5 us from kernel to kernel both ways), and
+    // capturing them cost 0.2 to 0.6 ms a solve.
     auto part_a = [&]() {
       herm_apply<double>(top.Mset, c->pv.p, c->q.p, nullptr, RED_SET, 1.0, s, true);
       PROF(DPG_K_CG, 0);
       cg_step(nM, c->x.p, c->r.p, c->pv.p, c->q.p, mixed ? top.r32.p : nullptr, rS, rS32, partial,
-              sc, s);
+              sc, c->dev_report, s);
     };
-    auto part_b = [&](double2 *zn, double2 *zp) {
-      if (mixed) vcycle<float>(c, c->L, top.r32.p, top.x32.p, true);
-      else vcycle<double>(c, c->L, c->r.p, zn, true);
-      PROF(DPG_K_CG, 0);
-      cg_direction(nM, c->r.p, mixed ? top.x32.p : nullptr, zn, zp, c->pv.p, pM, partial, sc, s);
-    };
-    GraphSet gs;
-    graphs = graphs && !c->prof.on;
-    if (graphs) {
-      gs.a = capture(s, part_a);
-      gs.b[0] = capture(s, [&]() { part_b(c->zo.p, c->z.p); });   // odd iterations
-      gs.b[1] = capture(s, [&]() { part_b(c->z.p, c->zo.p); });   // even iterations
-    }
-    while (it < c->opt.maxit) {
-      if (graphs) HIP_OK(hipGraphLaunch(gs.a, s));
-      else part_a();
-      ++it;
-      read_sc(c, sc);
-      if (c->host_sc[6] != 0.0)
-        throw DpgError(DPG_EBREAKDOWN, "CG breakdown at iteration " + std::to_string(it) +
-                                           " (p^H M p = " + std::to_string(c->host_sc[1]) + ")");
-      rr = std::sqrt(c->host_sc[4] / bb);
-      if (!std::isfinite(rr)) throw DpgError(DPG_EBREAKDOWN, "residual is not finite");
-      if (rr <= tol) break;
+    auto part_b = [&]() {
       std::swap(z, zo);
-      if (graphs) HIP_OK(hipGraphLaunch(gs.b[it & 1 ? 0 : 1], s));
-      else part_b(z, zo);
+      if (mixed) vcycle<float>(c, c->L, top.r32.p, top.x32.p, true);
+      else vcycle<double>(c, c->L, c->r.p, z, true);
+      PROF(DPG_K_CG, 0);
+      cg_direction(nM, c->r.p, mixed ? top.x32.p : nullptr, z, zo, c->pv.p, pM, partial, sc, s);
+    };
+    double last = 0.1;   // residual reduction of the iteration before
+    while (it < c->opt.maxit) {
+      part_a();
+      ++it;
+      const bool ahead = it < c->opt.maxit && rr * std::min(last, 1.0) > kAhead * tol;
+      if (ahead) part_b();
+      const std::array<double, 4> rep = wait_report(c, it + 1.0);
+      if (rep[3] != 0.0)
+        throw DpgError(DPG_EBREAKDOWN, "CG breakdown at iteration " + std::to_string(it) +
+                                           " (p^H M p = " + std::to_string(rep[2]) + ")");
+      const double now = std::sqrt(rep[1] / bb);
+      if (!std::isfinite(now)) throw DpgError(DPG_EBREAKDOWN, "residual is not finite");
+      last = now / rr;
+      rr = now;
+      if (rr <= tol) break;
+      if (!ahead) part_b();
     }
     if (rr > tol) status = DPG_ENOCONV;
   }
   expand_level<double>(top, top.WH.p, top.Tinv.p, sv, c->x.p, xout, 1, s);
-  HIP_OK(hipStreamSynchronize(s));
   if (iters) *iters = it;
   if (relres) *relres = rr;
   return status;
@@ -1701,8 +1722,7 @@ int solve_one(dpg_ctx *c, const double2 *sv, double tol, double2 *xout, int32_t 
 // Columns solved one after the other (solve_one), rhs / x_out staged through
 // the context's trace vectors when they are host memory.
 int solve_columns(dpg_ctx *c, const double *rhs, int nrhs, double tol, double *x_out,
-                  int32_t *iters_out, double *relres_out, double *partial, double *sc,
-                  bool graphs) {
+                  int32_t *iters_out, double *relres_out, double *partial, double *sc) {
   const int64_t nT = c->lv[c->L].num.n;
   const bool dev = c->opt.flags & DPG_DEVICE_PTRS;
   int status = DPG_OK;
@@ -1717,15 +1737,14 @@ int solve_columns(dpg_ctx *c, const double *rhs, int nrhs, double tol, double *x
     }
     int32_t it = 0;
     double rr = 0;
-    const int st = solve_one(c, sv, tol, c->xfull.p, &it, &rr, partial, sc, graphs);
+    const int st = solve_one(c, sv, tol, c->xfull.p, &it, &rr, partial, sc);
     if (st != DPG_OK) status = st;
     if (iters_out) iters_out[k] = it;
     if (relres_out) relres_out[k] = rr;
-    if (x_out) {
+    if (x_out)
       HIP_OK(hipMemcpyAsync(x_out + 2 * nT * k, c->xfull.p, nT * 16,
                             dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, c->stream));
-      HIP_OK(hipStreamSynchronize(c->stream));
-    }
+    HIP_OK(hipStreamSynchronize(c->stream));
   }
   return status;
 }
@@ -2441,6 +2460,9 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
     c->partial.alloc(2 * kDotBlocks, &c->bud);
     c->sc.alloc(kScalars, &c->bud);
     HIP_OK(hipHostMalloc((void **)&c->host_sc, 8 * sizeof(double), 0));
+    HIP_OK(hipHostMalloc((void **)&c->host_report, kReportWords * sizeof(double),
+                         hipHostMallocMapped | hipHostMallocCoherent));
+    HIP_OK(hipHostGetDevicePointer((void **)&c->dev_report, c->host_report, 0));
     // (the bytes without sharing decide, so that what can be recovered does
     // not depend on the medium)
     const int64_t rec_bytes = 16LL * top.nel * ((int64_t)c->n_field * c->n_field +
@@ -2649,7 +2671,7 @@ int dpg_solve(dpg_ctx *c, const double *rhs, int nrhs, double tol, double *x_out
       }
     } else {
       status = solve_columns(c, rhs, nrhs, tol, x_out, iters_out, relres_out, c->partial.p,
-                             c->sc.p, true);
+                             c->sc.p);
     }
     c->prof.flush();
     c->ms[3] = ms_since(t0);
@@ -2674,8 +2696,7 @@ int dpg_solve_noalloc(dpg_ctx *c, const double *rhs, int nrhs, double tol, doubl
     if (!sp) throw DpgError(DPG_ESTATE, "solve scratch not set up on this device");
     auto t0 = clk::now();
     const int status =
-        solve_columns(c, rhs, nrhs, tol, x_out, iters_out, relres_out, sp, sp + 2 * kDotBlocks,
-                      false);
+        solve_columns(c, rhs, nrhs, tol, x_out, iters_out, relres_out, sp, sp + 2 * kDotBlocks);
     c->ms[3] = ms_since(t0);
     if (status == DPG_ENOCONV) c->err = "maximum number of iterations reached";
     return status;
@@ -3025,6 +3046,7 @@ void dpg_destroy(dpg_ctx *c) {
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   batch_close(c);
   if (c->host_sc) (void)hipHostFree(c->host_sc);
+  if (c->host_report) (void)hipHostFree(c->host_report);
   if (c->aux) {
     (void)hipStreamSynchronize(c->aux);
     (void)hipStreamDestroy(c->aux);

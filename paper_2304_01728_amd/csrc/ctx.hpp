@@ -258,6 +258,7 @@ struct dpg_ctx {
   dpg::DevBuf<double2> b, x, r, z, zo, pv, q, xfull, sB;
   dpg::DevBuf<double> partial, sc;
   double *host_sc = nullptr;         // pinned
+  double *host_report = nullptr, *dev_report = nullptr;   // pinned, and its device address
   // block PCG (interleaved [n][nr] vectors), allocated at the first block solve
   int bcap = 0;
   dpg::HermBlockBufs T0b;

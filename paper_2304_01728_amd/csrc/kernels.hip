@@ -574,6 +574,24 @@ __global__ __launch_bounds__(256) void k_final(const double *__restrict__ partia
   if (threadIdx.x == 0) *dst = s;
 }
 
+// *dst = the sum, and the report of the scalars to the host.  The host polls the
+// report's last word: 5-8 us after the sum is there, where a copy launch and a stream
+// synchronisation take about 25.
+__global__ __launch_bounds__(256) void k_report(const double *__restrict__ partial, double *dst,
+                                                double *sc, double *report) {
+  const double s = sum_partials(partial);
+  if (threadIdx.x != 0) return;
+  *dst = s;
+  const double n = sc[9] + 1.0;
+  sc[9] = n;
+  report[0] = dst == sc + 5 ? s : sc[5];
+  report[1] = dst == sc + 4 ? s : sc[4];
+  report[2] = sc[1];
+  report[3] = sc[6];
+  __threadfence_system();
+  __hip_atomic_store(&report[4], n, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Bound by the launch on small problems (2.3 us of a 4 us gap at 4^3) and by the
 // five vectors it streams on large ones; every workgroup adds the 512 partial sums
 // of p^H q itself, which costs less than the launch between two kernels.  partial:
@@ -808,13 +826,20 @@ void dot_re(int64_t n, const double2 *a, const double2 *b, double *partial, doub
   LAUNCH_OK();
 }
 
+void cg_start(int64_t n, const double2 *b, double *partial, double *sc, double *report,
+              hipStream_t s) {
+  hipLaunchKernelGGL(k_dot_partial, dim3(kDotBlocks), dim3(256), 0, s, n, b, b, partial);
+  hipLaunchKernelGGL(k_report, dim3(1), dim3(256), 0, s, partial, sc + 5, sc, report);
+  LAUNCH_OK();
+}
+
 void cg_step(int64_t n, double2 *x, double2 *r, const double2 *p, const double2 *q, float2 *r32,
              LocalRows<double> fwd64, LocalRows<float> fwd32, double *partial, double *sc,
-             hipStream_t s) {
+             double *report, hipStream_t s) {
   hipLaunchKernelGGL(k_dot_partial, dim3(kDotBlocks), dim3(256), 0, s, n, p, q, partial);
   hipLaunchKernelGGL(k_cg_step, dim3(kDotBlocks), dim3(256), 0, s, n, x, r, p, q, r32, fwd64,
                      fwd32, partial, sc);
-  hipLaunchKernelGGL(k_final, dim3(1), dim3(256), 0, s, partial + kDotBlocks, sc + 4);
+  hipLaunchKernelGGL(k_report, dim3(1), dim3(256), 0, s, partial + kDotBlocks, sc + 4, sc, report);
   LAUNCH_OK();
 }
 

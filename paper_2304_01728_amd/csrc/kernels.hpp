@@ -136,13 +136,20 @@ void launch_to64(int64_t n, const float2 *a, double2 *b, hipStream_t s);
 // of dot_re, instead of a launch of its own in between (workgroup 0 stores it).  A
 // kernel never writes a scalar that it reads, which is why rz has two.
 constexpr int kDotBlocks = 512, kScalars = 16;
+// The scalars that the host decides by: report[0..3] = ||b||^2, ||r||^2, pq, the
+// breakdown flag, and report[4] the number of reports since sc was zeroed (counted in
+// sc[9]), written last.  report: pinned host memory, device address.
+constexpr int kReportWords = 8;
 void dot_re(int64_t n, const double2 *a, const double2 *b, double *partial, double *dst,
             hipStream_t s);                                  // dst = Re(a^H b)
-// pq, alpha = rz / pq; x += alpha p, r -= alpha q, ||r||^2.  r32 (or null) receives
+// ||b||^2, reported
+void cg_start(int64_t n, const double2 *b, double *partial, double *sc, double *report,
+              hipStream_t s);
+// pq, alpha = rz / pq; x += alpha p, r -= alpha q, ||r||^2, reported.  r32 (or null) receives
 // the new r in FP32; its (else r's) rows go to fwd32 (fwd64).
 void cg_step(int64_t n, double2 *x, double2 *r, const double2 *p, const double2 *q, float2 *r32,
              LocalRows<double> fwd64, LocalRows<float> fwd32, double *partial, double *sc,
-             hipStream_t s);
+             double *report, hipStream_t s);
 // beta (flexible), rz <- r^H z; p <- z + beta p, whose rows go to fwd.  With z32
 // (else null), z is that vector's FP64 copy, written here.
 void cg_direction(int64_t n, const double2 *r, const float2 *z32, double2 *z, const double2 *zold,
