@@ -470,34 +470,43 @@ __global__ __launch_bounds__(256) void k_csr_blk(int64_t nrows, int nr,
   y[e] = add ? cadd(y[e], acc) : acc;
 }
 
-// c_b[sl, k] = sum_i WH_b[sl, i] rc[I_b(i), k] for the KC columns of blockIdx.y.
+// c_b[sl, k] = sum_i WH_b[sl, i] rc[I_b(i), k] for the KC columns of blockIdx.y and
+// the 64 boundary slots of blockIdx.z, one per lane.  Bound by latency: a level has
+// few blocks, and a lane's sum is one chain over the interior, so the slots of a
+// block are spread over workgroups of one wave whose LDS holds only the interior
+// values (WH is read once per KC columns, from a cache after the first).  Whole
+// blocks in workgroups of 256 with 64 KB of LDS took 91 us for 64 blocks of order
+// 169 + 434 and 8 columns in FP32, now 40 (216 blocks, 32 columns 168 / 111; 1728
+// blocks, 32 columns in FP64 1840 / 1380).
 template <typename T>
-__global__ __launch_bounds__(256) void k_condense_local_blk(const cplx_t<T> *__restrict__ WH,
-                                                            const int32_t *__restrict__ bcls,
-                                                            int nI, int nBf,
-                                                            const int32_t *__restrict__ blkI,
-                                                            const cplx_t<T> *__restrict__ rc,
-                                                            cplx_t<T> *__restrict__ c, int nr) {
+__global__ __launch_bounds__(64) void k_condense_local_blk(const cplx_t<T> *__restrict__ WH,
+                                                           const int32_t *__restrict__ bcls,
+                                                           int nI, int nBf,
+                                                           const int32_t *__restrict__ blkI,
+                                                           const cplx_t<T> *__restrict__ rc,
+                                                           cplx_t<T> *__restrict__ c, int nr) {
   using C = cplx_t<T>;
-  __shared__ C rI[kBMaxI][KC];
+  extern __shared__ __align__(16) char smem[];
+  C(*rI)[KC] = reinterpret_cast<C(*)[KC]>(smem);
   const int b = blockIdx.x, k0 = blockIdx.y * KC, kc = min(KC, nr - k0);
-  for (int e = threadIdx.x; e < nI * KC; e += 256) {
+  for (int e = threadIdx.x; e < nI * KC; e += 64) {
     const int i = e / KC, k = e % KC;
     rI[i][k] = k < kc ? rc[(int64_t)blkI[(int64_t)b * nI + i] * nr + k0 + k] : czero<C>();
   }
   __syncthreads();
-  const C *W = WH + (int64_t)bcls[b] * nBf * nI;
-  for (int sl = threadIdx.x; sl < nBf; sl += 256) {
-    C acc[KC];
+  const int sl = blockIdx.z * 64 + threadIdx.x;
+  if (sl >= nBf) return;
+  const C *W = WH + (int64_t)bcls[b] * nBf * nI + sl;
+  C acc[KC];
 #pragma unroll
-    for (int k = 0; k < KC; ++k) acc[k] = czero<C>();
-    for (int i = 0; i < nI; ++i) {
-      const C wv = W[sl + (int64_t)i * nBf];
+  for (int k = 0; k < KC; ++k) acc[k] = czero<C>();
+#pragma unroll 8
+  for (int i = 0; i < nI; ++i) {
+    const C wv = W[(int64_t)i * nBf];
 #pragma unroll
-      for (int k = 0; k < KC; ++k) acc[k] = cfma(wv, rI[i][k], acc[k]);
-    }
-    for (int k = 0; k < kc; ++k) c[((int64_t)b * nBf + sl) * nr + k0 + k] = acc[k];
+    for (int k = 0; k < KC; ++k) acc[k] = cfma(wv, rI[i][k], acc[k]);
   }
+  for (int k = 0; k < kc; ++k) c[((int64_t)b * nBf + sl) * nr + k0 + k] = acc[k];
 }
 
 template <typename T>
@@ -536,7 +545,12 @@ __global__ __launch_bounds__(256) void k_scatter_macro_blk(int64_t nM, int nr,
 }
 
 // ec[I_b(i), k] = sum_j conj(Tinv[j, i]) rc[I_b(j), k] - sum_sl conj(WH[sl, i]) eB_b[sl, k],
-// one wave per interior unknown i, KC columns per workgroup.
+// one wave per interior unknown i at a time, KC columns (blockIdx.y) and the rows of
+// blockIdx.z per workgroup.  A coarse level has few blocks, so their rows are spread
+// over workgroups until the chip is full: 64 blocks of order 169 + 434, 8 columns in
+// FP32, 239 us with all rows in one workgroup, now 36; 27 blocks, 3 columns in FP64
+// 253 / 34.  (Four rows per wave at a time, which reads the LDS values once for all,
+// needed twice the registers: 216 blocks, 32 columns 551 us, 266 so.)
 template <typename T>
 __global__ __launch_bounds__(256) void k_expand_blk(const cplx_t<T> *__restrict__ WH,
                                                     const cplx_t<T> *__restrict__ Tinv,
@@ -545,7 +559,7 @@ __global__ __launch_bounds__(256) void k_expand_blk(const cplx_t<T> *__restrict_
                                                     const int32_t *__restrict__ blkBm,
                                                     const cplx_t<T> *__restrict__ rc,
                                                     const cplx_t<T> *__restrict__ eB,
-                                                    cplx_t<T> *__restrict__ ec, int nr) {
+                                                    cplx_t<T> *__restrict__ ec, int nr, int rows) {
   using C = cplx_t<T>;
   extern __shared__ __align__(16) char smem[];
   C(*eBs)[KC] = reinterpret_cast<C(*)[KC]>(smem);
@@ -564,7 +578,8 @@ __global__ __launch_bounds__(256) void k_expand_blk(const cplx_t<T> *__restrict_
   const C *W = WH + (int64_t)bcls[b] * nBf * nI;
   const C *Ti = Tinv + (int64_t)bcls[b] * nI * nI;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int i = wave; i < nI; i += 4) {
+  const int r1 = min(nI, ((int)blockIdx.z + 1) * rows);
+  for (int i = blockIdx.z * rows + wave; i < r1; i += 4) {
     C acc[KC];
 #pragma unroll
     for (int k = 0; k < KC; ++k) acc[k] = czero<C>();
@@ -641,6 +656,7 @@ __global__ __launch_bounds__(256) void k_coldot(int64_t n, int nr, const double2
   const bool on = t < rpb * nr;
   double s = 0.0, u = 0.0;
   if (on)
+#pragma unroll 4
     for (int64_t i = (int64_t)blockIdx.x * rpb + t / nr; i < n; i += (int64_t)gridDim.x * rpb) {
       const double2 x = a[i * nr + k], y = bv[i * nr + k];
       s += x.x * y.x + x.y * y.y;
@@ -664,17 +680,40 @@ __global__ __launch_bounds__(256) void k_coldot(int64_t n, int nr, const double2
 }
 
 // Column reductions and the scalar updates of the CG step (mode: 0 store the
-// dot in slot q, 1 alpha, 2 ||r||^2, 3 flexible beta).
-__global__ __launch_bounds__(64) void k_colfinal(const double *__restrict__ partial, int nr,
-                                                 double *__restrict__ sc,
-                                                 const int *__restrict__ act, int mode, int q) {
+// dot in slot q, 1 alpha, 2 ||r||^2, 3 flexible beta).  One column's partials are
+// added in order by one lane; they come through LDS, kFinRows at a time, so that the
+// chain waits for LDS and not for memory (15 us, now 7).
+constexpr int kFinRows = 64;
+__global__ __launch_bounds__(256) void k_colfinal(const double *__restrict__ partial, int nr,
+                                                  double *__restrict__ sc,
+                                                  const int *__restrict__ act, int mode, int q) {
+  __shared__ double sh[2][kFinRows][kMaxCols];
   const int k = threadIdx.x;
-  if (k >= nr) return;
   double s = 0.0, u = 0.0;
-  for (int j = 0; j < kColDotBlocks; ++j) {
-    s += partial[(int64_t)j * kMaxCols + k];
-    u += partial[(int64_t)(kColDotBlocks + j) * kMaxCols + k];
+  for (int j0 = 0; j0 < kColDotBlocks; j0 += kFinRows) {
+    double v[kFinRows * kMaxCols / 256], w[kFinRows * kMaxCols / 256];
+#pragma unroll
+    for (int e = 0; e < kFinRows * kMaxCols / 256; ++e) {
+      const int64_t at = (int64_t)j0 * kMaxCols + e * 256 + threadIdx.x;
+      v[e] = partial[at];
+      w[e] = mode == 3 ? partial[(int64_t)kColDotBlocks * kMaxCols + at] : 0.0;
+    }
+    if (j0) __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kFinRows * kMaxCols / 256; ++e) {
+      (&sh[0][0][0])[e * 256 + threadIdx.x] = v[e];
+      (&sh[1][0][0])[e * 256 + threadIdx.x] = w[e];
+    }
+    __syncthreads();
+    if (k < nr) {
+#pragma unroll 16
+      for (int j = 0; j < kFinRows; ++j) {
+        s += sh[0][j][k];
+        u += sh[1][j][k];
+      }
+    }
   }
+  if (k >= nr) return;
   double *S = sc;
   const bool on = act ? act[k] != 0 : true;
   if (mode == 0) {
@@ -903,13 +942,16 @@ void launch_condense_blk(const cplx_t<T> *WH, const int32_t *bcls, int nI, int n
                          const int32_t *red_ent, const cplx_t<T> *rc, cplx_t<T> *c,
                          cplx_t<T> *rB, int nr, hipStream_t s) {
   if (nI > kBMaxI) throw DpgError(-1, "macro block too large");
-  hipLaunchKernelGGL((k_condense_local_blk<T>), dim3(nblk, cdiv(nr, KC)), dim3(256), 0, s, WH,
-                     bcls, nI, nBf, blkI, rc, c, nr);
+  // 64 KB of LDS at most: kBMaxI interior unknowns in FP64
+  hipLaunchKernelGGL((k_condense_local_blk<T>), dim3(nblk, cdiv(nr, KC), cdiv(nBf, 64)), dim3(64),
+                     sizeof(cplx_t<T>) * KC * nI, s, WH, bcls, nI, nBf, blkI, rc, c, nr);
   LAUNCH_OK();
   hipLaunchKernelGGL((k_condense_reduce_blk<T>), dim3(cdiv(nM * nr, 256)), dim3(256), 0, s, nM, nr,
                      macro_B, red_ptr, red_ent, rc, c, rB);
   LAUNCH_OK();
 }
+
+constexpr int64_t kExpandWgs = 2048;
 
 template <typename T>
 void launch_expand_blk(const cplx_t<T> *WH, const cplx_t<T> *Tinv, const int32_t *bcls, int nI,
@@ -927,8 +969,12 @@ void launch_expand_blk(const cplx_t<T> *WH, const cplx_t<T> *Tinv, const int32_t
   hipLaunchKernelGGL((k_scatter_macro_blk<T>), dim3(cdiv(nM * nr, 256)), dim3(256), 0, s, nM, nr,
                      macro_B, eB, ec);
   LAUNCH_OK();
-  hipLaunchKernelGGL((k_expand_blk<T>), dim3(nblk, cdiv(nr, KC)), dim3(256), lds, s, WH, Tinv,
-                     bcls, nI, nBf, blkI, blkBm, rc, eB, ec, nr);
+  // rows of a workgroup, in sixteens: workgroups enough to fill the chip eight deep
+  // (27 blocks, 32 columns: 65 us at four deep, 51 at eight)
+  const int64_t wgs = (int64_t)nblk * cdiv(nr, KC), want = cdiv(kExpandWgs, wgs);
+  const int rows = (int)std::max<int64_t>(16, 16 * cdiv(cdiv(nI, 16), want));
+  hipLaunchKernelGGL((k_expand_blk<T>), dim3(nblk, cdiv(nr, KC), cdiv(nI, rows)), dim3(256), lds, s,
+                     WH, Tinv, bcls, nI, nBf, blkI, blkBm, rc, eB, ec, nr, rows);
   LAUNCH_OK();
 }
 
@@ -967,7 +1013,7 @@ void cgb_dot(int64_t n, int nr, const double2 *a, const double2 *b, double *part
              int q, hipStream_t s) {
   hipLaunchKernelGGL(k_coldot, dim3(kColDotBlocks), dim3(256), 0, s, n, nr, a, b,
                      (const double2 *)nullptr, partial);
-  hipLaunchKernelGGL(k_colfinal, dim3(1), dim3(64), 0, s, partial, nr, sc, (const int *)nullptr, 0,
+  hipLaunchKernelGGL(k_colfinal, dim3(1), dim3(256), 0, s, partial, nr, sc, (const int *)nullptr, 0,
                      q);
   LAUNCH_OK();
 }
@@ -976,7 +1022,7 @@ void cgb_alpha(int64_t n, int nr, const double2 *p, const double2 *qv, double *p
                double *sc, const int *act, hipStream_t s) {
   hipLaunchKernelGGL(k_coldot, dim3(kColDotBlocks), dim3(256), 0, s, n, nr, p, qv,
                      (const double2 *)nullptr, partial);
-  hipLaunchKernelGGL(k_colfinal, dim3(1), dim3(64), 0, s, partial, nr, sc, act, 1, 0);
+  hipLaunchKernelGGL(k_colfinal, dim3(1), dim3(256), 0, s, partial, nr, sc, act, 1, 0);
   LAUNCH_OK();
 }
 
@@ -984,7 +1030,7 @@ void cgb_update_xr(int64_t n, int nr, double2 *x, double2 *r, const double2 *p, 
                    double *partial, double *sc, hipStream_t s) {
   hipLaunchKernelGGL(k_update_xr_blk, dim3(kColDotBlocks), dim3(256), 0, s, n, nr, x, r, p, qv,
                      partial, sc);
-  hipLaunchKernelGGL(k_colfinal, dim3(1), dim3(64), 0, s, partial, nr, sc, (const int *)nullptr, 2,
+  hipLaunchKernelGGL(k_colfinal, dim3(1), dim3(256), 0, s, partial, nr, sc, (const int *)nullptr, 2,
                      0);
   LAUNCH_OK();
 }
@@ -992,7 +1038,7 @@ void cgb_update_xr(int64_t n, int nr, double2 *x, double2 *r, const double2 *p, 
 void cgb_beta(int64_t n, int nr, const double2 *r, const double2 *z, const double2 *zold,
               double *partial, double *sc, const int *act, hipStream_t s) {
   hipLaunchKernelGGL(k_coldot, dim3(kColDotBlocks), dim3(256), 0, s, n, nr, r, z, zold, partial);
-  hipLaunchKernelGGL(k_colfinal, dim3(1), dim3(64), 0, s, partial, nr, sc, act, 3, 0);
+  hipLaunchKernelGGL(k_colfinal, dim3(1), dim3(256), 0, s, partial, nr, sc, act, 3, 0);
   LAUNCH_OK();
 }
 
