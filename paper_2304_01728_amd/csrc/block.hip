@@ -70,6 +70,20 @@ __device__ __forceinline__ RowUnit row_unit(const int2 *__restrict__ rows, const
   return u;
 }
 
+typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+
+// Raw buffer over n entries at p (wave-uniform); reads past them give zero.  Under
+// 2 GB: the tiles of the largest block (order 4459 at p = 7) are 80 MB.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const float2 *p, int64_t n) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float2 *>(p), 0, (int)(n * sizeof(float2)),
+                                           0x00020000);
+}
+// The entry at byte offset vo (per lane) + so (wave-uniform).
+__device__ __forceinline__ float2 buffer_at(__amdgpu_buffer_rsrc_t r, int vo, int so) {
+  const v2u v = __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0);
+  return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+}
+
 // FP32.  Y_I accumulates three real products per tile (the
 // three-multiplication complex product: a quarter fewer matrix-core
 // operations, and an imaginary part formed as p3 - p1 - p2, which in FP32
@@ -101,22 +115,29 @@ __device__ __forceinline__ void rows32(const RowUnit &u, const float2 *__restric
   // a diagonal tile stores the sub-blocks a <= q only (slot diag_slot(a, q))
   const bool dup = a <= q;
   const int dsl = dup ? diag_slot(a, q) : 0;
-  const float2 *xb = xl + u.base + ncl + (int64_t)kk * u.ld;
-  const int64_t xs = (int64_t)(64 / NC) * u.ld;   // step of a lane's X entries
+  // tiles and X through buffer descriptors: a load is the lane's offset, fixed, and a
+  // scalar one, so that no vector instruction forms addresses
+  const auto rt = buffer_of(tiles + u.ent, tile_entry(0, nt));
+  const auto rx = buffer_of(xl + u.base, (int64_t)(32 * nt - 1) * u.ld + u.nc);
+  const int xo = (ncl + kk * u.ld) * (int)sizeof(float2);
+  const int xs = 64 / NC * u.ld * (int)sizeof(float2);   // step of a lane's X entries
+  // Where the lane's entries (4a + i, 4q + j) go: row m of column c at
+  // 32 c + (m ^ 2 (c / 4 % 8)).  As A_IJ they are rows 4a + i of columns 4q + j,
+  // entry i of a column at up[i / 2] + i % 2 + 32 j; transposed, rows 4q + j of
+  // columns 4a + i, at lo[j / 2] + j % 2 + 32 i.
+  float2 *const up[2] = {buf + 128 * q + 4 * (a ^ (q >> 1)) + 2 * (q & 1),
+                         buf + 128 * q + 4 * (a ^ (q >> 1)) + 2 - 2 * (q & 1)};
+  float2 *const lo[2] = {buf + 128 * a + 4 * (q ^ (a >> 1)) + 2 * (a & 1),
+                         buf + 128 * a + 4 * (q ^ (a >> 1)) + 2 - 2 * (a & 1)};
+  float2 *const away = buf + 32 * 32;   // for lanes of a diagonal tile without an entry
   float2 t[16], x[NX];
   auto load_tile = [&](int J) {
-    // (wave-uniform branch, constant strides: immediate load offsets); lanes
-    // below the diagonal of a diagonal tile read slot 0 (in range), their
-    // values are not staged
-    if (J != I) {
-      const float2 *tp = tiles + u.ent + (J > I ? tile_entry(I, J) : tile_entry(J, I)) + lane;
+    // lanes below the diagonal of a diagonal tile read slot 0 (in range)
+    const int e = (int)(J > I ? tile_entry(I, J) : tile_entry(J, I)) * (int)sizeof(float2);
+    const int step = (J != I ? 64 : kDiagSlots) * (int)sizeof(float2);
+    const int vo = (J != I ? lane : dsl) * (int)sizeof(float2);
 #pragma unroll
-      for (int k = 0; k < 16; ++k) t[k] = tp[k * 64];
-    } else {
-      const float2 *tp = tiles + u.ent + tile_entry(I, I) + dsl;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) t[k] = tp[k * kDiagSlots];
-    }
+    for (int k = 0; k < 16; ++k) t[k] = buffer_at(rt, vo, e + k * step);
   };
   // three real products (Gauss): p1 = Re A Re X, p2 = Im A Im X,
   // p3 = (Re A + Im A)(Re X + Im X); Re Y = p1 - p2, Im Y = p3 - p1 - p2
@@ -135,35 +156,37 @@ __device__ __forceinline__ void rows32(const RowUnit &u, const float2 *__restric
   }
   load_tile(0);
 #pragma unroll
-  for (int s = 0; s < NX; ++s) x[s] = xb[s * xs];
+  for (int s = 0; s < NX; ++s) x[s] = buffer_at(rx, xo, s * xs);
 #pragma unroll 1
   for (int J = 0; J < nt; ++J) {
-    const bool up = J >= I;
     // the lane holds stored entries (4a + i, 4q + j) at 4i + j; A_IJ is the
-    // stored tile (J >= I) or the conjugate transpose of tile (J, I)
-    if (J != I) {
-      const float sg = up ? 1.f : -1.f;
+    // stored tile (J > I), the conjugate transpose of tile (J, I), or both
+    // triangles of the diagonal tile, whose lanes a <= q hold something.
+    // (Separate code and fixed addresses for each: choosing row, column and sign
+    // per entry took eight vector instructions an entry, and vector instructions
+    // take matrix-core time here.  With those and the load addresses gone, about
+    // 200 to 50 a tile, and no path on which a load is waited for late, 32 columns
+    // of 24^3, p = 3: 282 to 240 ms in this kernel, 123 to 144 TFLOP/s.)
+    auto stage_up = [&](float2 *u0, float2 *u1) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int c = up ? 4 * q + j : 4 * a + i;
-          const int m = up ? 4 * a + i : 4 * q + j;
-          const float2 v = t[4 * i + j];
-          buf[c * 32 + (m ^ (2 * ((c >> 2) & 7)))] = make_float2(v.x, sg * v.y);
-        }
+        for (int j = 0; j < 4; ++j) (i >> 1 ? u1 : u0)[(i & 1) + 32 * j] = t[4 * i + j];
+    };
+    auto stage_lo = [&](float2 *l0, float2 *l1) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          (j >> 1 ? l1 : l0)[(j & 1) + 32 * i] = make_float2(t[4 * i + j].x, -t[4 * i + j].y);
+    };
+    if (J > I) {
+      stage_up(up[0], up[1]);
+    } else if (J < I) {
+      stage_lo(lo[0], lo[1]);
     } else {
-      // diagonal tile: lanes a <= q write their sub-block, lanes a < q also
-      // its conjugate transpose below the diagonal
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int c = 4 * q + j, m = 4 * a + i;
-          const float2 v = t[4 * i + j];
-          if (dup) buf[c * 32 + (m ^ (2 * ((c >> 2) & 7)))] = v;
-          if (a < q) buf[m * 32 + (c ^ (2 * ((m >> 2) & 7)))] = make_float2(v.x, -v.y);
-        }
+      stage_up(dup ? up[0] : away, dup ? up[1] : away);
+      stage_lo(a < q ? lo[0] : away, a < q ? lo[1] : away);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -171,7 +194,7 @@ __device__ __forceinline__ void rows32(const RowUnit &u, const float2 *__restric
     const int Jn = min(J + 1, nt - 1);   // the loads after the last tile repeat it
     load_tile(Jn);
     __builtin_amdgcn_sched_barrier(0);
-    const float2 *xn = xb + (int64_t)32 * Jn * u.ld;
+    const int xn = 32 * Jn * u.ld * (int)sizeof(float2);
     if constexpr (NC == 32) {
       float2 av = buf[kk * 32 + n];
 #pragma unroll
@@ -181,7 +204,7 @@ __device__ __forceinline__ void rows32(const RowUnit &u, const float2 *__restric
         p1 = __builtin_amdgcn_mfma_f32_32x32x2f32(ac.x, x[s].x, p1, 0, 0, 0);
         p2 = __builtin_amdgcn_mfma_f32_32x32x2f32(ac.y, x[s].y, p2, 0, 0, 0);
         p3 = __builtin_amdgcn_mfma_f32_32x32x2f32(ac.x + ac.y, x[s].x + x[s].y, p3, 0, 0, 0);
-        x[s] = xn[s * xs];
+        x[s] = buffer_at(rx, xo, xn + s * xs);
         __builtin_amdgcn_sched_barrier(0);
       }
     } else {
@@ -203,7 +226,7 @@ __device__ __forceinline__ void rows32(const RowUnit &u, const float2 *__restric
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb)
           q3[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ac[rb].x + ac[rb].y, xsum, q3[rb], 0, 0, 0);
-        x[s] = xn[s * xs];
+        x[s] = buffer_at(rx, xo, xn + s * xs);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -231,7 +254,7 @@ __global__ __launch_bounds__(64, 3) void k_rows_mfma(const float2 *__restrict__ 
                                                      const HermGroup *__restrict__ grp,
                                                      const float2 *__restrict__ xl,
                                                      float2 *__restrict__ yl, int nr) {
-  __shared__ float2 buf[32 * 32];
+  __shared__ float2 buf[32 * 32 + 128];   // the tile, and entries that nobody reads
   const RowUnit u = row_unit(rows, cm, grp, nr);
   if (!u.on) return;
   if (u.nc <= 16) rows32<16>(u, tiles, xl, yl, buf);
