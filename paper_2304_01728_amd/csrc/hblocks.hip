@@ -16,23 +16,10 @@ template <typename C> __device__ __forceinline__ C czero() {
   return r;
 }
 
-template <typename C> __device__ inline C shfl_xor_c(C v, int m) {
-  C r;
-  r.x = __shfl_xor(v.x, m, 64);
-  r.y = __shfl_xor(v.y, m, 64);
-  return r;
-}
-
-template <typename C> __device__ inline C sel4(C v0, C v1, C v2, C v3, int i) {
-  C r;
-  r.x = i == 0 ? v0.x : i == 1 ? v1.x : i == 2 ? v2.x : v3.x;
-  r.y = i == 0 ? v0.y : i == 1 ? v1.y : i == 2 ? v2.y : v3.y;
-  return r;
-}
-
 // Cross-lane moves inside rows of 16 lanes (DPP): quad_perm [1,0,3,2],
-// quad_perm [2,3,0,1] and the mirror inside each group of 8 lanes.
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141;
+// quad_perm [2,3,0,1], the mirror inside each group of 8 lanes, and the rotation
+// by 8 lanes.
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor8 = 0x128;
 
 template <int CTRL> __device__ __forceinline__ float dpp(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
@@ -71,6 +58,53 @@ template <typename C> __device__ __forceinline__ C rowsum_scatter(const C rs[4],
   C k = csel(b1, k1, k0);
   k = cadd(k, dpp_c<kDppXor2>(csel(b1, k0, k1)));
   return cadd(k, dpp_c<kDppXor1>(k));
+}
+
+// The dwords of a pair (p, q) with their rows of 16 lanes (halves of 32) exchanged:
+// the sum of the two results is p over both rows of a pair in the even row, q in the
+// odd one.
+template <int ROW> __device__ __forceinline__ void swap_rows(uint32_t &p, uint32_t &q) {
+  if constexpr (ROW == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(p, q, false, false);
+    p = r[0];
+    q = r[1];
+  } else {
+    const auto r = __builtin_amdgcn_permlane32_swap(p, q, false, false);
+    p = r[0];
+    q = r[1];
+  }
+}
+template <int ROW> __device__ __forceinline__ float swap_sum(float p, float q) {
+  uint32_t a = __float_as_uint(p), b = __float_as_uint(q);
+  swap_rows<ROW>(a, b);
+  return __uint_as_float(a) + __uint_as_float(b);
+}
+template <int ROW> __device__ __forceinline__ double swap_sum(double p, double q) {
+  uint32_t al = __double2loint(p), ah = __double2hiint(p), bl = __double2loint(q),
+           bh = __double2hiint(q);
+  swap_rows<ROW>(al, bl);
+  swap_rows<ROW>(ah, bh);
+  return __hiloint2double(ah, al) + __hiloint2double(bh, bl);
+}
+
+// Sums of four column values over the lanes ra = 0..7 (8, 16, 32 lanes apart, in
+// that order): lane ra returns that of column col_of(ra).  Each exchange halves the
+// values a lane carries on, and stays in the vector unit (DPP, row swaps).  Four sums
+// one by one through LDS permutations, 12 exchanges instead of 4: solves at 16^3,
+// p = 3 24.6 / 23.6 ms, 24^3, p = 4 mixed 108.1 / 104.8.
+__device__ __forceinline__ int col_of(int ra) { return 2 * (ra & 1) + (ra >> 1 & 1); }
+template <typename C> __device__ __forceinline__ C colsum_scatter(const C v[4], int ra) {
+  const bool odd = ra & 1;
+  C k0 = csel(odd, v[2], v[0]), k1 = csel(odd, v[3], v[1]);
+  const C s0 = csel(odd, v[0], v[2]), s1 = csel(odd, v[1], v[3]);
+  k0 = cadd(k0, dpp_c<kDppRor8>(s0));
+  k1 = cadd(k1, dpp_c<kDppRor8>(s1));
+  C k;
+  k.x = swap_sum<16>(k0.x, k1.x);
+  k.y = swap_sum<16>(k0.y, k1.y);
+  k.x = swap_sum<32>(k.x, k.x);
+  k.y = swap_sum<32>(k.y, k.y);
+  return k;
 }
 
 // Tile entries are read once per application: non-temporal loads keep them
@@ -252,13 +286,8 @@ __global__ __launch_bounds__(256) void k_units(const cplx_t<T> *__restrict__ til
   if (two && !off1) mask_lower(upper, t1);
   do_tile(t0, xJ, xw, off0 || strict, ra, cb, cacc, part + d1.x);
   if (two) do_tile(t1, xJ, xw + 32, off1 || strict, ra, cb, cacc, part + d1.x + d1.y);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    cacc[j] = cadd(cacc[j], shfl_xor_c(cacc[j], 8));
-    cacc[j] = cadd(cacc[j], shfl_xor_c(cacc[j], 16));
-    cacc[j] = cadd(cacc[j], shfl_xor_c(cacc[j], 32));
-  }
-  if (ra < 4) part[d1.z + 4 * cb + ra] = sel4(cacc[0], cacc[1], cacc[2], cacc[3], ra);
+  const C cs = colsum_scatter(cacc, ra);
+  if (ra < 4) part[d1.z + 4 * cb + col_of(ra)] = cs;
 }
 
 // The units of a group's blocks (a group's local vectors are interleaved: row i
@@ -332,13 +361,8 @@ __global__ __launch_bounds__(256, 2) void k_units_grp(const cplx_t<T> *__restric
     C *pm = part + (int64_t)m * each;
     do_tile(t0, xc, xw, off0 || strict, ra, cb, cacc, pm + d1.x);
     if (two) do_tile(t1, xc, xw + 32, off1 || strict, ra, cb, cacc, pm + d1.x + d1.y);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      cacc[j] = cadd(cacc[j], shfl_xor_c(cacc[j], 8));
-      cacc[j] = cadd(cacc[j], shfl_xor_c(cacc[j], 16));
-      cacc[j] = cadd(cacc[j], shfl_xor_c(cacc[j], 32));
-    }
-    if (ra < 4) pm[d1.z + 4 * cb + ra] = sel4(cacc[0], cacc[1], cacc[2], cacc[3], ra);
+    const C cs = colsum_scatter(cacc, ra);
+    if (ra < 4) pm[d1.z + 4 * cb + col_of(ra)] = cs;
   }
 }
 
@@ -431,18 +455,10 @@ __global__ __launch_bounds__(256) void k_strips(const cplx_t<T> *__restrict__ ti
     const C v = rowsum_scatter(rs, cb);
     if (!(cb & 1)) rp[32 * strip_row_slot(ns, I, s) + 4 * ra + (cb >> 1)] = v;
   }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    c0[j] = cadd(c0[j], shfl_xor_c(c0[j], 8));
-    c0[j] = cadd(c0[j], shfl_xor_c(c0[j], 16));
-    c0[j] = cadd(c0[j], shfl_xor_c(c0[j], 32));
-    c1[j] = cadd(c1[j], shfl_xor_c(c1[j], 8));
-    c1[j] = cadd(c1[j], shfl_xor_c(c1[j], 16));
-    c1[j] = cadd(c1[j], shfl_xor_c(c1[j], 32));
-  }
+  const C s0 = colsum_scatter(c0, ra), s1 = colsum_scatter(c1, ra);
   if (ra < 4) {
-    part[d1.z + 4 * cb + ra] = sel4(c0[0], c0[1], c0[2], c0[3], ra);
-    if (two) part[d1.w + 4 * cb + ra] = sel4(c1[0], c1[1], c1[2], c1[3], ra);
+    part[d1.z + 4 * cb + col_of(ra)] = s0;
+    if (two) part[d1.w + 4 * cb + col_of(ra)] = s1;
   }
 }
 
@@ -545,19 +561,11 @@ __global__ __launch_bounds__(256, 2) void k_strips_grp(const cplx_t<T> *__restri
 #pragma unroll
   for (int m = 0; m < G; ++m) {
     if (m >= cnt) break;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      c0[m][j] = cadd(c0[m][j], shfl_xor_c(c0[m][j], 8));
-      c0[m][j] = cadd(c0[m][j], shfl_xor_c(c0[m][j], 16));
-      c0[m][j] = cadd(c0[m][j], shfl_xor_c(c0[m][j], 32));
-      c1[m][j] = cadd(c1[m][j], shfl_xor_c(c1[m][j], 8));
-      c1[m][j] = cadd(c1[m][j], shfl_xor_c(c1[m][j], 16));
-      c1[m][j] = cadd(c1[m][j], shfl_xor_c(c1[m][j], 32));
-    }
+    const C s0 = colsum_scatter(c0[m], ra), s1 = colsum_scatter(c1[m], ra);
     if (ra < 4) {
-      C *pc = part + d1.z + m * each + 4 * cb + ra;
-      pc[0] = sel4(c0[m][0], c0[m][1], c0[m][2], c0[m][3], ra);
-      if (two) pc[32 * nc] = sel4(c1[m][0], c1[m][1], c1[m][2], c1[m][3], ra);
+      C *pc = part + d1.z + m * each + 4 * cb + col_of(ra);
+      pc[0] = s0;
+      if (two) pc[32 * nc] = s1;
     }
   }
 }
