@@ -466,10 +466,12 @@ __global__ __launch_bounds__(256) void k_strips(const cplx_t<T> *__restrict__ ti
 // interleaved: row i of block m at i gw + m): each pair of tiles is loaded once
 // for all of them, from a cache except for the first group of its class, and
 // every block gets the arithmetic of k_strips in the same order, so the partials
-// are bit for bit the same.  Bound by the vector units: 128 multiply-adds per
-// tile, entry of a lane and block, about 600 cycles per block and tile against
-// 3660 for the tile's 8 KB at a SIMD's share of the HBM rate.  Four blocks (16
-// column sums and 16 x entries each) fill the 256 registers of two waves per SIMD.
+// are bit for bit the same.  Half of the time is vector work (some 300 instructions
+// per pair of tiles and block, 256 of them the products, 1200 cycles of 2440 at the
+// 34 TFLOP/s of 24^3, p = 4); two waves per SIMD do not hide all of the wait for the
+// tiles, and four blocks (16 column sums and 16 x entries each) fill their 256
+// registers.  The next tile row's x comes through LDS, loaded a row ahead (one load
+// per block and row, waited for at its use, 68.6 -> 66.5 ms of a solve).
 template <typename T>
 __global__ __launch_bounds__(256, 2) void k_strips_grp(const cplx_t<T> *__restrict__ tiles,
                                                        const int4 *__restrict__ units,
@@ -477,7 +479,8 @@ __global__ __launch_bounds__(256, 2) void k_strips_grp(const cplx_t<T> *__restri
                                                        const cplx_t<T> *__restrict__ xloc,
                                                        cplx_t<T> *__restrict__ part) {
   using C = cplx_t<T>;
-  constexpr int G = kStripBlocks;
+  constexpr int G = kStripBlocks, XR = 32 * G + 2 * 8;   // x of a tile row, padded per four rows
+  __shared__ C xs[4][XR];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t per = gridDim.x / 8, wg = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
   const int64_t wv = wg * 4 + wave;
@@ -508,8 +511,28 @@ __global__ __launch_bounds__(256, 2) void k_strips_grp(const cplx_t<T> *__restri
       c1[m][j] = czero<C>();
     }
   }
+  // x of the blocks' next tile row: entries lane and lane + 64 of (row, block)
+  C *const xw = xs[wave];
+  C xn[2];
+  auto load_x = [&](int I) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int e = lane + 64 * h;
+      xn[h] = xb[(32 * I + e / G) * gw + min(e % G, cnt - 1)];
+    }
+  };
+  static_assert(32 * G == 128, "two x entries per lane");
+  load_x(Ia);
 #pragma unroll 1
   for (int I = Ia; I < Ib; ++I) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int e = lane + 64 * h;
+      xw[e + 2 * (e / (4 * G))] = xn[h];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     const bool fa = I < J0, fb = two && I < J1;
     const bool ka = fa || (I == J0 && upper), kb = fb || (two && I == J1 && upper);
     const C *pa = fa ? t0 + (int64_t)kTileFull * I + lane : t0 + (int64_t)kTileFull * J0 + ds;
@@ -521,6 +544,7 @@ __global__ __launch_bounds__(256, 2) void k_strips_grp(const cplx_t<T> *__restri
     for (int k = 0; k < 16; ++k) ta[k] = pa[k * sa];
 #pragma unroll
     for (int k = 0; k < 16; ++k) tb[k] = pb[k * sb];
+    load_x(min(I + 1, Ib - 1));
     mask_lower(ka, ta);
     mask_lower(kb, tb);
 #pragma unroll
@@ -528,7 +552,7 @@ __global__ __launch_bounds__(256, 2) void k_strips_grp(const cplx_t<T> *__restri
       if (m >= cnt) break;
       C xI[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) xI[i] = xb[(32 * I + 4 * ra + i) * gw + m];
+      for (int i = 0; i < 4; ++i) xI[i] = xw[(4 * G + 2) * ra + G * i + m];
       C rs[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -862,14 +886,30 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
   // of groups (group, tile column, segment): as below with the first block's
   // offsets, flags | blocks << 8, and {slots of a block, first slot of the
   // group, 0, 0}; the blocks that are a group of their own at the end
+  //
+  // The units of all groups of a class that read the same tiles follow one another,
+  // so that the tiles come from memory once per class and not once per group (a
+  // class of order 1399 is 8 MB in FP32, twice an L2): 16^3, p = 3 23.6 -> 22.8 ms per
+  // solve, 24^3, p = 4 mixed 105 -> 100 (with the x of k_strips_grp through LDS).
+  std::vector<std::vector<const Part *>> runs;   // groups of a class; blocks alone last
+  {
+    std::map<int64_t, size_t> at;
+    for (const Part &q : parts) {
+      const auto it = q.g.gw > 1 ? at.emplace(q.g.ent, runs.size()).first : at.end();
+      if (it == at.end() || it->second == runs.size()) runs.emplace_back();
+      runs[it == at.end() ? runs.size() - 1 : it->second].push_back(&q);
+    }
+  }
   std::vector<int4> gud64;
   gnunits64 = 0;
-  for (const Part &q : parts) {
+  for (const auto &run : runs) {
     if (!fp64) break;
-    const int nt = q.g.nt, b = q.m[0];
+    const int nt = run[0]->g.nt;
     const int64_t each = colbase(nt) + (int64_t)nt * (nt + 1) / 2 * 32;
     for (int J = 0; J < nt; ++J)
-      for (int I0 = 0; I0 <= J; I0 += kSeg) {
+      for (int I0 = 0; I0 <= J; I0 += kSeg) for (const Part *pq : run) {
+        const Part &q = *pq;
+        const int b = q.m[0];
         const int64_t tile = q.g.ent + tile_entry(I0, J);
         const int64_t rd = I0 + 1 <= J ? row_slot(nt, I0 + 1, J) - row_slot(nt, I0, J) : 0;
         const int flags = (I0 + 1 <= J ? 1 : 0) | (I0 < J ? 2 : 0) | (I0 + 1 < J ? 4 : 0);
@@ -880,7 +920,7 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
                                   (int)(cpo[b] + colbase(J) + I0 / kSeg * 32), flags | q.g.gw << 8));
         gud64.push_back(make_int4((int)each, (int)cpo[b], 0, 0));
       }
-    if (q.g.gw > 1) gnunits64 = (int64_t)gud64.size() / 3;
+    if (run[0]->g.gw > 1) gnunits64 = (int64_t)gud64.size() / 3;
   }
   gall64 = (int64_t)gud64.size() / 3;
   std::vector<int2> rb;
@@ -964,12 +1004,14 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
         }
       }
     }
-    for (const Part &q : parts) {
-      if (q.g.gw == 1) continue;
-      const int nt = q.g.nt, np = (q.g.gw + kStripBlocks - 1) / kStripBlocks;
+    for (const auto &run : runs) {
+      if (run[0]->g.gw == 1) continue;
+      const int nt = run[0]->g.nt;
       const int64_t each = 32LL * (cbase[nt][nt] + strip_row_slots(nt));
       for (int st = 0; 2 * st < nt; ++st)
-        for (int c = 0; c * kChunk < strip_rows(nt, st); ++c)
+        for (int c = 0; c * kChunk < strip_rows(nt, st); ++c) for (const Part *pq : run) {
+          const Part &q = *pq;
+          const int np = (q.g.gw + kStripBlocks - 1) / kStripBlocks;
           for (int u = 0; u < np; ++u) {   // blocks m0 .. m1 - 1 of the group
             const int m0 = q.g.gw * u / np, m1 = q.g.gw * (u + 1) / np, b = q.m[m0];
             const int64_t tile = q.g.ent + tile_entry(0, 2 * st);
@@ -980,6 +1022,7 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
                                     (int)(scpo[b] + 32LL * (cbase[nt][2 * st] + c)), (int)srpo[b]));
             gud.push_back(make_int4((int)each, 0, 0, 0));
           }
+        }
     }
     snunits = (int64_t)sud.size() / 2;
     gnunits = (int64_t)gud.size() / 3;
