@@ -2394,16 +2394,19 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
       HIP_OK(hipStreamSynchronize(s));   // the lists built here are copied
       // work vectors
       const int64_t nc = c->lv[l - 1].num.n;
+      // r and x of its own where the V-cycle does not work on the CG's vectors
+      // (finest level, FP64) or the finer level's traces (order levels)
+      const bool own = l < c->L && !f.order;
       if (mixed) {
-        f.r32.alloc(f.nM, &c->bud);
-        f.x32.alloc(f.nM, &c->bud);
+        f.r32.alloc(own || l == c->L ? f.nM : 0, &c->bud);
+        f.x32.alloc(own || l == c->L ? f.nM : 0, &c->bud);
         f.res32.alloc(f.nM, &c->bud);
         f.rc32.alloc(nc, &c->bud);
         f.ec32.alloc(nc, &c->bud);
         f.c32.alloc((int64_t)f.nblk * f.nBf, &c->bud);
       } else {
-        f.r64.alloc(f.nM, &c->bud);
-        f.x64.alloc(f.nM, &c->bud);
+        f.r64.alloc(own ? f.nM : 0, &c->bud);
+        f.x64.alloc(own ? f.nM : 0, &c->bud);
         f.res64.alloc(f.nM, &c->bud);
         f.rc64.alloc(nc, &c->bud);
         f.ec64.alloc(nc, &c->bud);
