@@ -180,6 +180,7 @@ __device__ __forceinline__ void rows32(const RowUnit &u, const float2 *__restric
         for (int j = 0; j < 4; ++j)
           (j >> 1 ? l1 : l0)[(j & 1) + 32 * i] = make_float2(t[4 * i + j].x, -t[4 * i + j].y);
     };
+    wave_lds_fence();   // the tile before has been read
     if (J > I) {
       stage_up(up[0], up[1]);
     } else if (J < I) {
@@ -188,9 +189,7 @@ __device__ __forceinline__ void rows32(const RowUnit &u, const float2 *__restric
       stage_up(dup ? up[0] : away, dup ? up[1] : away);
       stage_lo(a < q ? lo[0] : away, a < q ? lo[1] : away);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
     const int Jn = min(J + 1, nt - 1);   // the loads after the last tile repeat it
     load_tile(Jn);
     __builtin_amdgcn_sched_barrier(0);
@@ -318,6 +317,7 @@ __device__ __forceinline__ void rows64(const RowUnit &u, const double2 *__restri
     const bool up = J >= I;
     // the lane holds stored entries (4a + i, 4q + j) at 4i + j; A_IJ is the
     // stored tile (J >= I) or the conjugate transpose of tile (J, I)
+    wave_lds_fence();   // the tile before has been read
     if (J != I) {
       const double sg = up ? 1.0 : -1.0;
 #pragma unroll
@@ -342,9 +342,7 @@ __device__ __forceinline__ void rows64(const RowUnit &u, const double2 *__restri
           if (a < q) buf[m * 33 + c] = make_double2(v.x, -v.y);
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
     const int Jn = min(J + 1, nt - 1);   // the loads after the last tile repeat it
     load_tile(Jn);
     __builtin_amdgcn_sched_barrier(0);

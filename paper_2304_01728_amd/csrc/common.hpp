@@ -157,6 +157,16 @@ struct ListPack {
   }
 };
 
+// Orders a wave's accesses to LDS that is its own: what its lanes wrote before is
+// there for all of them after, and nothing read before is overwritten by what is written
+// after.  No instruction but the waits (a wave's LDS operations run in order); the
+// compiler moves no LDS access across it.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
 // ---- kernel timing with HIP events (optional, per context) -------------------------

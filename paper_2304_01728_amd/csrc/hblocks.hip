@@ -279,9 +279,7 @@ __global__ __launch_bounds__(256) void k_units(const cplx_t<T> *__restrict__ til
   w.x = lane < nx ? v.x : 0;
   w.y = lane < nx ? v.y : 0;
   xw[lane] = w;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  wave_lds_fence();
   if (!off0) mask_lower(upper, t0);
   if (two && !off1) mask_lower(upper, t1);
   do_tile(t0, xJ, xw, off0 || strict, ra, cb, cacc, part + d1.x);
@@ -344,12 +342,9 @@ __global__ __launch_bounds__(256, 2) void k_units_grp(const cplx_t<T> *__restric
     C w, cacc[4], xc[4];
     w.x = lane < nx ? v.x : 0;
     w.y = lane < nx ? v.y : 0;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_fence();   // the block before has read its x
     xw[lane] = w;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
     const int mn = min(m + 1, gw - 1);
     v = xi[mn];
 #pragma unroll
@@ -525,14 +520,13 @@ __global__ __launch_bounds__(256, 2) void k_strips_grp(const cplx_t<T> *__restri
   load_x(Ia);
 #pragma unroll 1
   for (int I = Ia; I < Ib; ++I) {
+    wave_lds_fence();   // the row before has been read
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int e = lane + 64 * h;
       xw[e + 2 * (e / (4 * G))] = xn[h];
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
     const bool fa = I < J0, fb = two && I < J1;
     const bool ka = fa || (I == J0 && upper), kb = fb || (two && I == J1 && upper);
     const C *pa = fa ? t0 + (int64_t)kTileFull * I + lane : t0 + (int64_t)kTileFull * J0 + ds;
