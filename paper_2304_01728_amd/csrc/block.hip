@@ -72,8 +72,11 @@ __device__ __forceinline__ RowUnit row_unit(const int2 *__restrict__ rows, const
 
 typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 
-// Raw buffer over n entries at p (wave-uniform); reads past them give zero.  Under
-// 2 GB: the tiles of the largest block (order 4459 at p = 7) are 80 MB.
+// Raw buffer over n entries at p (wave-uniform); reads past them give zero.  Sizes and
+// offsets have 32 bits: one tile, or the columns of one group (32 kMaxTiles rows of
+// kMaxGroup kMaxCols columns at most).
+static_assert(32LL * kMaxTiles * kMaxGroup * kMaxCols * sizeof(float2) < (1LL << 31),
+              "X of a group beyond a buffer's offsets");
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const float2 *p, int64_t n) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float2 *>(p), 0, (int)(n * sizeof(float2)),
                                            0x00020000);
@@ -115,9 +118,9 @@ __device__ __forceinline__ void rows32(const RowUnit &u, const float2 *__restric
   // a diagonal tile stores the sub-blocks a <= q only (slot diag_slot(a, q))
   const bool dup = a <= q;
   const int dsl = dup ? diag_slot(a, q) : 0;
-  // tiles and X through buffer descriptors: a load is the lane's offset, fixed, and a
-  // scalar one, so that no vector instruction forms addresses
-  const auto rt = buffer_of(tiles + u.ent, tile_entry(0, nt));
+  // tiles (a descriptor each, at a 64-bit address) and X through buffer descriptors: a
+  // load is the lane's offset, fixed, and a scalar one, so that no vector instruction
+  // forms addresses
   const auto rx = buffer_of(xl + u.base, (int64_t)(32 * nt - 1) * u.ld + u.nc);
   const int xo = (ncl + kk * u.ld) * (int)sizeof(float2);
   const int xs = 64 / NC * u.ld * (int)sizeof(float2);   // step of a lane's X entries
@@ -133,11 +136,12 @@ __device__ __forceinline__ void rows32(const RowUnit &u, const float2 *__restric
   float2 t[16], x[NX];
   auto load_tile = [&](int J) {
     // lanes below the diagonal of a diagonal tile read slot 0 (in range)
-    const int e = (int)(J > I ? tile_entry(I, J) : tile_entry(J, I)) * (int)sizeof(float2);
-    const int step = (J != I ? 64 : kDiagSlots) * (int)sizeof(float2);
+    const TileSpan ts = tile_span(I, J);
+    const auto rt = buffer_of(tiles + u.ent + ts.first, ts.entries);
+    const int step = ts.step * (int)sizeof(float2);
     const int vo = (J != I ? lane : dsl) * (int)sizeof(float2);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) t[k] = buffer_at(rt, vo, e + k * step);
+    for (int k = 0; k < 16; ++k) t[k] = buffer_at(rt, vo, k * step);
   };
   // three real products (Gauss): p1 = Re A Re X, p2 = Im A Im X,
   // p3 = (Re A + Im A)(Re X + Im X); Re Y = p1 - p2, Im Y = p3 - p1 - p2

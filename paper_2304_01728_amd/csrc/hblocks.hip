@@ -947,7 +947,7 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
   for (size_t k = 0; k < rd.size(); ++k) {
     const int b = rw[k].x, I = rw[k].y, nt = (sizes[b] + 31) / 32;
     const int nseg = (I + kSeg) / kSeg, nrw = nt - I;
-    if (nt > 0xfff) throw DpgError(-1, "HermSet: block too large for row descriptors");
+    if (nt > kMaxTiles) throw DpgError(-1, "HermSet: block too large for row descriptors");
     rd[k] = make_int4((int)(cpo[b] + colbase(I)), (int)(rpo[b] + row_slot(nt, I, I)),
                       nseg | nrw << 12 | step[b] << 24, (int)(loff[b] + (int64_t)32 * I * step[b]));
   }
@@ -967,7 +967,7 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
     int64_t sp = 0;
     for (const Part &q : parts) {
       const int nt = q.g.nt;
-      if (nt > 0xfff) throw DpgError(-1, "HermSet: block too large for strip descriptors");
+      if (nt > kMaxTiles) throw DpgError(-1, "HermSet: block too large for strip descriptors");
       std::vector<int32_t> &cbv = cbase[nt];
       if (cbv.empty()) {
         cbv.assign(nt + 1, 0);

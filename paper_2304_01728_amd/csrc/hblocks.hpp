@@ -51,11 +51,26 @@ __host__ __device__ __forceinline__ int64_t tile_entry(int I, int J) {
   return (int64_t)kTileFull * ((int64_t)J * (J - 1) / 2 + I) + (int64_t)kTileDiag * J;
 }
 
+// The stored tile that A_IJ is read from (the transposed one below the diagonal): its
+// first entry inside the block, which passes 2^31 bytes from 725 tile columns on in
+// FP32 (the coarsest operator is one block), and its entries, in 16 slots `step` apart.
+struct TileSpan {
+  int64_t first;
+  int entries, step;
+};
+__host__ __device__ __forceinline__ TileSpan tile_span(int I, int J) {
+  if (J > I) return {tile_entry(I, J), kTileFull, kTileFull / 16};
+  return {tile_entry(J, I), J < I ? kTileFull : kTileDiag, J < I ? kTileFull / 16 : kDiagSlots};
+}
+
 // Slot of sub-block (ra, cb), ra <= cb, in a diagonal tile: row-major order
 // of the upper triangle of the 8 x 8 sub-block grid.
 __host__ __device__ __forceinline__ int diag_slot(int ra, int cb) {
   return ra * 8 - ra * (ra - 1) / 2 + (cb - ra);
 }
+
+// Most tile columns of a block (row and strip descriptors hold 12-bit counts).
+constexpr int kMaxTiles = 0xfff;
 
 // Blocks of one class that are applied together: column m of a group of gw
 // blocks is the local vector of its member m, row i at (base + i gw + m) (times
