@@ -1737,7 +1737,15 @@ int solve_columns(dpg_ctx *c, const double *rhs, int nrhs, double tol, double *x
     }
     int32_t it = 0;
     double rr = 0;
-    const int st = solve_one(c, sv, tol, c->xfull.p, &it, &rr, partial, sc);
+    int st;
+    try {
+      st = solve_one(c, sv, tol, c->xfull.p, &it, &rr, partial, sc);
+    } catch (...) {
+      // what was queued ahead still uses the scratch (shared by every context on the
+      // GPU in dpg_solve_noalloc): no call returns before it is done
+      (void)hipStreamSynchronize(c->stream);
+      throw;
+    }
     if (st != DPG_OK) status = st;
     if (iters_out) iters_out[k] = it;
     if (relres_out) relres_out[k] = rr;
