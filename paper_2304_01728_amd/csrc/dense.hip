@@ -70,7 +70,9 @@ __device__ __forceinline__ void tri_index(int t, int &lo, int &hi) {
 // tiles share in one L2 while items stay interleaved over the XCDs.  Items of
 // a last incomplete group of 8 keep the plain order.
 // 32-bit unsigned arithmetic: the tiled launches here have gridDim.x *
-// gridDim.y < 2^32 (at most a few thousand tiles times 65535 items).
+// gridDim.y < 2^32 (at most a few thousand tiles times kMaxItems items; the callers
+// cut factorisations and solves to that many, gemm_batched cuts its own).
+constexpr int kMaxItems = 65535;
 __device__ __forceinline__ void xcd_remap(int &bx, int &by) {
   const uint32_t gx = gridDim.x;
   const uint32_t L = blockIdx.x + blockIdx.y * gx;
@@ -982,10 +984,14 @@ void gemm_batched(int opa, int opb, double2 alpha, const double2 *abase, const d
                   int max_n, hipStream_t s, int mode) {
   if (nitems <= 0 || max_m <= 0 || max_n <= 0) return;
   const int tm = (int)cdiv(max_m, TM), tn = (int)cdiv(max_n, TN), t = std::max(tm, tn);
-  dim3 g(mode == GEMM_FULL ? tm * tn : t * (t + 1) / 2, nitems);
-  if (opa == OP_N) gemm_dispatch_b<OP_N>(opb, g, s, alpha, abase, bbase, beta, cbase, items_dev, tn, mode);
-  else if (opa == OP_T) gemm_dispatch_b<OP_T>(opb, g, s, alpha, abase, bbase, beta, cbase, items_dev, tn, mode);
-  else gemm_dispatch_b<OP_C>(opb, g, s, alpha, abase, bbase, beta, cbase, items_dev, tn, mode);
+  const int tiles = mode == GEMM_FULL ? tm * tn : t * (t + 1) / 2;
+  for (int i0 = 0; i0 < nitems; i0 += kMaxItems) {
+    const dim3 g(tiles, std::min(kMaxItems, nitems - i0));
+    const GemmItem *it = items_dev + i0;
+    if (opa == OP_N) gemm_dispatch_b<OP_N>(opb, g, s, alpha, abase, bbase, beta, cbase, it, tn, mode);
+    else if (opa == OP_T) gemm_dispatch_b<OP_T>(opb, g, s, alpha, abase, bbase, beta, cbase, it, tn, mode);
+    else gemm_dispatch_b<OP_C>(opb, g, s, alpha, abase, bbase, beta, cbase, it, tn, mode);
+  }
   LAUNCH_OK();
 }
 

@@ -126,3 +126,22 @@ def test_recomputed_patches_block_solve_and_batch():
     assert np.linalg.norm(x1 - alone[0]) <= 1e-8 * np.linalg.norm(alone[0])
     for c in ctxs.values():
         c.close()
+
+
+def test_more_equal_patches_than_a_launch_takes():
+    """41^3 = 68,921 vertex patches in a few classes (80^3, p = 1, uniform medium): the
+    products of one factor batch with all its patches are more than the 65,535 items of
+    a launch.  Against stored inverses, to the rounding bound of the smaller sizes."""
+    D = _D()
+    N, p, omega = 80, 1, 4 * np.pi
+    d = workloads.plane_wave_direction(2)
+    rec = _ctx(D, N, p, omega, d, (1, 1), D.DPG_RECOMPUTE_PATCHES)
+    x, it, rr, code = D.dpg_solve(rec, tol=1e-12)
+    rec.close()
+    sto = _ctx(D, N, p, omega, d, (1, 1), 0)
+    xs, its, _, codes = D.dpg_solve(sto, tol=1e-12)
+    sto.close()
+    print(f"  iterations {it} {its}", flush=True)
+    assert code == D.DPG_OK and codes == D.DPG_OK
+    assert abs(int(it[0]) - int(its[0])) <= 1
+    assert np.linalg.norm(x[0] - xs[0]) <= 1e-10 * np.linalg.norm(xs[0])
