@@ -1783,10 +1783,7 @@ void ensure_block(dpg_ctx *c, int nr) {
   if (nr <= c->bcap) return;
   const bool mixed = c->opt.precision == DPG_MIXED;
   Budget *bd = &c->bud;
-  for (LevelData &f : c->lv) {   // the partials are taken last, from what is left
-    f.Mb.part64.release();
-    f.Sb.part64.release();
-  }
+  c->bpart.release();   // taken last, from what is left
   for (int l = 1; l <= c->L; ++l) {
     LevelData &f = c->lv[l];
     const int64_t nc = c->lv[l - 1].num.n, nM = f.nM, ncb = (int64_t)f.nblk * f.nBf;
@@ -1826,11 +1823,24 @@ void ensure_block(dpg_ctx *c, int nr) {
     HIP_OK(hipHostMalloc((void **)&c->host_bsc, 8 * kMaxCols * sizeof(double), 0));
     HIP_OK(hipHostMalloc((void **)&c->host_bact, kMaxCols * sizeof(int), 0));
   }
-  for (int l = 1; l <= c->L; ++l) {
-    c->lv[l].Mb.ensure_part(c->lv[l].Mset, nr, bd);
-    c->lv[l].Sb.ensure_part(c->lv[l].Sset, nr, bd);
+  if (bd->limit <= 0) {
+    int64_t need = 0;
+    auto share = [&](const HermSet &H, HermBlockBufs &B) {
+      B.part = &c->bpart;
+      for (int q = std::min(nr, kUnitCols); q > 1; --q)
+        if (units_for(H, q)) need = std::max(need, std::min(H.npart * q, kPartEntries));
+    };
+    for (int l = 1; l <= c->L; ++l) {
+      share(c->lv[l].Mset, c->lv[l].Mb);
+      share(c->lv[l].Sset, c->lv[l].Sb);
+    }
+    share(c->T0set, c->T0b);
+    try {
+      c->bpart.alloc(need, bd);
+    } catch (const DpgError &) {   // the sets' own partials then, column by column
+      (void)hipGetLastError();
+    }
   }
-  c->T0b.ensure_part(c->T0set, nr, bd);
   c->bcap = nr;
 }
 

@@ -815,15 +815,10 @@ void HermBlockBufs::ensure(const HermSet &H, int nr, bool fp64, bool fp32, Budge
   cap = nr;
 }
 
-void HermBlockBufs::ensure_part(const HermSet &H, int nr, Budget *bud) {
-  const int64_t n = H.npart * std::min(nr, kUnitCols);
-  if (!H.t64.p || H.t32.p || H.gnunits64 > 0 || part64.n >= n) return;
-  if ((bud && bud->limit > 0) || n * 16 > 2000000000LL) return;
-  try {
-    part64.alloc(n, bud);
-  } catch (const DpgError &) {
-    (void)hipGetLastError();
-  }
+// (not in mixed precision, whose solutions feel the last bit of the outer iteration)
+bool units_for(const HermSet &H, int nr) {
+  return H.t64.p && !H.t32.p && H.gnunits64 == 0 && nr > 1 && nr <= kUnitCols &&
+         H.npart * nr <= kPartMost;
 }
 
 template <typename T>
@@ -904,10 +899,9 @@ void herm_apply_blk(HermSet &H, HermBlockBufs &W, const cplx_t<T> *X, cplx_t<T> 
   }
   bool rows = true;
   if constexpr (sizeof(T) == 8) {
-    // not in mixed precision, whose solutions feel the last bit of the outer
-    // iteration
-    if (nr <= kUnitCols && H.gnunits64 == 0 && !H.t32.p && W.part64.n >= H.npart * nr) {
-      launch_units_cols(H, xl, W.part64.p, yl, nr, s);
+    if (W.part && units_for(H, nr)) {
+      const bool own = W.part->n < H.max_slots;   // (also: of a larger block than it holds)
+      launch_units_cols(H, xl, own ? H.p64.p : W.part->p, own ? H.npart : W.part->n, yl, nr, s);
       rows = false;
     }
   }

@@ -23,11 +23,8 @@ struct HermBlockBufs {
   // local vectors zeroed when allocated: a forward (below) writes only the
   // rows a vector entry maps to
   void ensure(const HermSet &H, int nr, bool fp64, bool fp32, Budget *bud, hipStream_t s);
-  // Partials for at most kUnitCols columns (launch_units_cols): up to 2 GB a
-  // set, and none under a memory budget, which they must not use up; without
-  // them a block apply goes through launch_rows, which needs none.
-  DevBuf<double2> part64;
-  void ensure_part(const HermSet &H, int nr, Budget *bud);
+  // partials of launch_units_cols, the context's (null: not by units, see units_for)
+  const DevBuf<double2> *part = nullptr;
 };
 
 // Up to this many FP64 columns of a set without groups, each tile is read once
@@ -37,7 +34,18 @@ struct HermBlockBufs {
 // units, about 46 ms by rows.  The tiles of groups come from caches, there the
 // rows are faster (16^3, p = 3, uniform medium, 2 / 3 columns: 34 / 44 ms against
 // 41 / 53).
+//
+// The partials (up to a third of the tiles' bytes at seven columns) go through one
+// buffer of the context, of kPartEntries (512 MB) at most: larger sets run in ranges of
+// blocks (7 columns, 18^3, p = 3, 1.1 GB of partials: 175.3 ms in one go, 176.9 so).
+// Where that buffer could not be allocated, the same kernels run through the
+// set's own partials (more ranges, and a block alone column by column), so that
+// results do not depend on what could be allocated.  Sets whose
+// partials would pass kPartMost (2 GB) go by rows, and so do all under a memory budget,
+// which no buffer for speed alone may use up.
 constexpr int kUnitCols = 7;
+constexpr int64_t kPartEntries = 32 << 20, kPartMost = 125000000;
+bool units_for(const HermSet &H, int nr);
 
 // Y <- epilogue(sum_b R_b^T A_b R_b X) for nr columns (modes as herm_apply).
 // gathered: W already holds the local rows of X (a previous application

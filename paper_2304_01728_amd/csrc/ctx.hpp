@@ -262,6 +262,7 @@ struct dpg_ctx {
   // block PCG (interleaved [n][nr] vectors), allocated at the first block solve
   int bcap = 0;
   dpg::HermBlockBufs T0b;
+  dpg::DevBuf<double2> bpart;        // partials of few FP64 columns, of every block set in turn
   dpg::DevBuf<double2> bb, bx, br, bz, bzo, bp, bq, bsv, bxf, bcols;
   dpg::DevBuf<double> bpartial, bsc;
   dpg::DevBuf<int> bact;

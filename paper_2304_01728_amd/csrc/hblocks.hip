@@ -295,13 +295,14 @@ __global__ __launch_bounds__(256) void k_units(const cplx_t<T> *__restrict__ til
 // same.  Bound by the vector units and the cross-lane sums, about 1000 cycles per
 // block and tile against 7300 for the tile's 16 KB at a SIMD's share of the HBM
 // rate.  The x entries of the next block are loaded while one is multiplied.
-// The nr right-hand sides of a block alone are taken like the blocks of a group
-// (column k at i nr + k); its tiles are read once per application (NT: past the
-// caches).
+// The right-hand sides k0 .. k0 + q - 1 of a block alone are taken like the blocks of
+// a group (column k at i nr + k), with the partials of the blocks from slot0 on; its
+// tiles are read once per application (NT: past the caches).
 template <typename T, bool NT>
 __global__ __launch_bounds__(256, 2) void k_units_grp(const cplx_t<T> *__restrict__ tiles,
                                                       const int4 *__restrict__ units,
-                                                      int64_t nunits, int nr,
+                                                      int64_t nunits, int nr, int k0, int q,
+                                                      int64_t slot0,
                                                       const cplx_t<T> *__restrict__ xloc,
                                                       cplx_t<T> *__restrict__ part) {
   using C = cplx_t<T>;
@@ -312,9 +313,12 @@ __global__ __launch_bounds__(256, 2) void k_units_grp(const cplx_t<T> *__restric
   if (wv >= nunits) return;
   const int lane = threadIdx.x & 63, ra = lane >> 3, cb = lane & 7;
   const int4 d0 = units[3 * wv], d1 = units[3 * wv + 1], d2 = units[3 * wv + 2];
-  const int each = d2.x, gw = (d1.w >> 8) * nr;
+  const int each = d2.x, ld = (d1.w >> 8) * nr, gw = NT ? q : ld;
   const int64_t ent = (int64_t)(uint32_t)d0.x | ((int64_t)d0.y << 32);
-  part += (int64_t)d2.y * (nr - 1);   // slots of the block vectors before this group's
+  if (NT) {   // slots of the columns of the blocks before this one
+    part += (int64_t)d2.y * (q - 1) - slot0 * q;
+    xloc += k0;
+  }
   const bool two = d1.w & 1, off0 = d1.w & 2, off1 = d1.w & 4;
   const bool upper = ra <= cb, strict = ra < cb;
   const C *tp = tiles + ent;
@@ -329,11 +333,11 @@ __global__ __launch_bounds__(256, 2) void k_units_grp(const cplx_t<T> *__restric
     for (int k = 0; k < 16; ++k) t1[k] = NT ? ld_nt(p1 + k * s1) : p1[k * s1];
   }
   const int nx = 32 * (1 + two);
-  const C *xi = xloc + (int64_t)d0.z * nr + min(lane, nx - 1) * gw;
-  const C *xj = xloc + (int64_t)d0.w * nr + 4 * cb * gw;
+  const C *xi = xloc + (int64_t)d0.z * nr + min(lane, nx - 1) * ld;
+  const C *xj = xloc + (int64_t)d0.w * nr + 4 * cb * ld;
   C v = xi[0];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) xJ[j] = xj[j * gw];
+  for (int j = 0; j < 4; ++j) xJ[j] = xj[j * ld];
   if (!off0) mask_lower(upper, t0);
   if (two && !off1) mask_lower(upper, t1);
   C *xw = xs[wave];
@@ -350,7 +354,7 @@ __global__ __launch_bounds__(256, 2) void k_units_grp(const cplx_t<T> *__restric
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       xc[j] = xJ[j];
-      xJ[j] = xj[j * gw + mn];
+      xJ[j] = xj[j * ld + mn];
       cacc[j] = czero<C>();
     }
     C *pm = part + (int64_t)m * each;
@@ -619,20 +623,26 @@ __device__ __forceinline__ C row_total(const int4 d, int r, const C *__restrict_
   return acc[0];
 }
 
-// Half a wave per (block, tile row I) and column blockIdx.y of the local vectors
-// of nr right-hand sides; rowb gives {first slot of the block, slots of the block}
-// (read for nr > 1).
+// Half a wave per (block, tile row I).  With rowb ({first slot of the block, slots of
+// the block}): column k0 + blockIdx.y of the local vectors of nr right-hand sides, for
+// the blocks whose first slot is in [slot0, slot1), with the partials of gridDim.y
+// columns.
 template <typename T>
 __global__ __launch_bounds__(256) void k_rows(const int4 *__restrict__ rowd,
                                               const int2 *__restrict__ rowb, int64_t nrows, int nr,
+                                              int k0, int64_t slot0, int64_t slot1,
                                               const cplx_t<T> *__restrict__ part,
                                               cplx_t<T> *__restrict__ yl) {
   const int64_t hw = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 5;
   if (hw >= nrows) return;
   const int r = threadIdx.x & 31;
   const int4 d = rowd[hw];
-  if (nr > 1) part += (int64_t)rowb[hw].x * (nr - 1) + (int64_t)rowb[hw].y * blockIdx.y;
-  yl[(int64_t)(d.w + r * (d.z >> 24)) * nr + blockIdx.y] = row_total(d, r, part);
+  if (rowb) {
+    const int2 b = rowb[hw];
+    if (b.x < slot0 || b.x >= slot1) return;
+    part += (int64_t)b.x * (gridDim.y - 1) - slot0 * gridDim.y + (int64_t)b.y * blockIdx.y;
+  }
+  yl[(int64_t)(d.w + r * (d.z >> 24)) * nr + k0 + blockIdx.y] = row_total(d, r, part);
 }
 
 // With FWD the result of entry d is also written to every local row of the
@@ -900,6 +910,11 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
     if (!fp64) break;
     const int nt = run[0]->g.nt;
     const int64_t each = colbase(nt) + (int64_t)nt * (nt + 1) / 2 * 32;
+    if (gnunits64 == 0 && run[0]->g.gw == 1) {
+      unit0_h.push_back((int64_t)gud64.size() / 3);
+      slot0_h.push_back(cpo[run[0]->m[0]]);
+      max_slots = std::max(max_slots, each);
+    }
     for (int J = 0; J < nt; ++J)
       for (int I0 = 0; I0 <= J; I0 += kSeg) for (const Part *pq : run) {
         const Part &q = *pq;
@@ -917,6 +932,8 @@ void HermSet::build(const std::vector<int32_t> &sizes, const std::vector<int32_t
     if (run[0]->g.gw > 1) gnunits64 = (int64_t)gud64.size() / 3;
   }
   gall64 = (int64_t)gud64.size() / 3;
+  unit0_h.push_back(gall64);
+  slot0_h.push_back(npart);
   std::vector<int2> rb;
   for (const int2 &k : rw) {
     if (!fp64) break;
@@ -1105,7 +1122,7 @@ void launch_reduce(const HermSet &H, const cplx_t<T> *part, cplx_t<T> *yl, const
   const int4 *rowd = sizeof(T) == 8 ? H.rowd.p : H.srowd.p;
   if (yl) {
     hipLaunchKernelGGL((k_rows<T>), dim3(cdiv(H.nrows, 8)), dim3(256), 0, s, rowd,
-                       (const int2 *)nullptr, H.nrows, 1, part, yl);
+                       (const int2 *)nullptr, H.nrows, 1, 0, 0, 0, part, yl);
     LAUNCH_OK();
     if (fwd)
       hipLaunchKernelGGL((k_scatter<T, MODE, true>), g, dim3(256), 0, s, H.nvec, H.red_ptr.p,
@@ -1157,7 +1174,7 @@ void herm_apply(HermSet &H, const cplx_t<T> *x, cplx_t<T> *y, const cplx_t<T> *r
     if (H.gnunits64 > 0) {
       ProfScope ps(H.prof, DPG_K_APPLYG64, 8.0 * (double)H.full_grouped, s);
       hipLaunchKernelGGL((k_units_grp<T, false>), dim3(8 * cdiv(cdiv(H.gnunits64, 4), 8)),
-                         dim3(256), 0, s, tiles, H.gunits64.p, H.gnunits64, 1, xl, part);
+                         dim3(256), 0, s, tiles, H.gunits64.p, H.gnunits64, 1, 0, 1, 0, xl, part);
       LAUNCH_OK();
     }
     if (H.nunits > 0) {
@@ -1190,19 +1207,29 @@ void herm_apply(HermSet &H, const cplx_t<T> *x, cplx_t<T> *y, const cplx_t<T> *r
   LAUNCH_OK();
 }
 
-void launch_units_cols(HermSet &H, const double2 *xl, double2 *part, double2 *yl, int nr,
-                       hipStream_t s) {
-  const dim3 g(8 * cdiv(cdiv(H.gall64, 4), 8));
-  {
-    ProfScope ps(H.prof, DPG_K_APPLYG64, 8.0 * (double)H.full * nr, s);
-    hipLaunchKernelGGL((k_units_grp<double, true>), g, dim3(256), 0, s, H.t64.p, H.gunits64.p,
-                       H.gall64, nr, xl, part);
-    LAUNCH_OK();
+void launch_units_cols(HermSet &H, const double2 *xl, double2 *part, int64_t npart_max,
+                       double2 *yl, int nr, hipStream_t s) {
+  const int nb = (int)H.slot0_h.size() - 1, q = (int)std::min<int64_t>(nr, npart_max / H.max_slots);
+  if (q < 1) throw DpgError(-1, "block apply: no room for the partials");
+  for (int k0 = 0; k0 < nr; k0 += q) {
+    const int kc = std::min(q, nr - k0);
+    for (int b = 0, e; b < nb; b = e) {
+      for (e = b + 1; e < nb && (H.slot0_h[e + 1] - H.slot0_h[b]) * kc <= npart_max;) ++e;
+      const int64_t u0 = H.unit0_h[b], n = H.unit0_h[e] - u0;
+      {
+        ProfScope ps(H.prof, DPG_K_APPLYG64,
+                     8.0 * (double)H.full * kc * (double)n / (double)H.gall64, s);
+        hipLaunchKernelGGL((k_units_grp<double, true>), dim3(8 * cdiv(cdiv(n, 4), 8)), dim3(256),
+                           0, s, H.t64.p, H.gunits64.p + 3 * u0, n, nr, k0, kc, H.slot0_h[b], xl,
+                           part);
+        LAUNCH_OK();
+      }
+      ProfScope ps(H.prof, DPG_K_REDUCE, 0.0, s);
+      hipLaunchKernelGGL((k_rows<double>), dim3(cdiv(H.nrows, 8), kc), dim3(256), 0, s, H.rowd.p,
+                         H.rowb.p, H.nrows, nr, k0, H.slot0_h[b], H.slot0_h[e], part, yl);
+      LAUNCH_OK();
+    }
   }
-  ProfScope ps(H.prof, DPG_K_REDUCE, 0.0, s);
-  hipLaunchKernelGGL((k_rows<double>), dim3(cdiv(H.nrows, 8), nr), dim3(256), 0, s, H.rowd.p,
-                     H.rowb.p, H.nrows, nr, part, yl);
-  LAUNCH_OK();
 }
 
 template void herm_apply<double>(HermSet &, const double2 *, double2 *, const double2 *, int,

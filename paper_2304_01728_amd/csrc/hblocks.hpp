@@ -122,6 +122,10 @@ struct HermSet {
   DevList<int4> gunits64;     // three int4 per (group, J, tile-row pair), FP64; the first
   int64_t gnunits64 = 0;     // gnunits64 of groups of two and more blocks, gall64 in all
   int64_t gall64 = 0;
+  // without groups (FP64): first of gunits64 and first partial slot of each block, in
+  // the order of the partials, and where the last one ends; slots of the largest block
+  std::vector<int64_t> unit0_h, slot0_h;
+  int64_t max_slots = 0;
   DevList<int2> rowb;         // per (block, I): first partial slot of the block, its slots
   DevList<int4> tdesc;        // (representative block, I, J, 0) per stored tile (packing)
   DevList<int32_t> red_ptr;   // CSR over vector entries
@@ -166,8 +170,10 @@ void herm_apply(HermSet &H, const cplx_t<T> *x, cplx_t<T> *y, const cplx_t<T> *r
                 T theta, hipStream_t s, bool gathered = false, HermSet *fwd = nullptr);
 
 // yl = A xl for the nr interleaved columns of every block of a set without
-// groups, each tile read once for all of them (FP64; part: npart nr entries).
-void launch_units_cols(HermSet &H, const double2 *xl, double2 *part, double2 *yl, int nr,
-                       hipStream_t s);
+// groups, each tile read once for all of them (FP64).  part holds npart_max >=
+// max_slots entries: with fewer than npart nr the blocks are taken in ranges, and with
+// fewer than max_slots nr the columns in parts; a column's sums are the same.
+void launch_units_cols(HermSet &H, const double2 *xl, double2 *part, int64_t npart_max,
+                       double2 *yl, int nr, hipStream_t s);
 
 }  // namespace dpg
