@@ -618,7 +618,7 @@ void element_stage(dpg_ctx *c, int l, bool write_matrices, const IndicatorArgs *
   if (ind) {
     if (!fine || ind->nr < 1 || ind->nr > nr) throw DpgError(DPG_EINVAL, "bad indicator columns");
     for (int k = 0; k < P.ns; ++k) grow(P.X[k], (int64_t)C * m * ind->nr, &c->bud);
-    if (P.gR_nr != ind->nr || P.gR_C != C) {
+    if (P.gR_nr != ind->nr || P.gR_C != C || P.gR_mp != mp) {
       std::vector<GemmItem> gR(C);
       for (int i = 0; i < C; ++i)
         gR[i] = {(int64_t)i * nt * mp, (int64_t)i * m * ind->nr, (int64_t)i * nt * mp + (int64_t)m * nt,
@@ -627,6 +627,7 @@ void element_stage(dpg_ctx *c, int l, bool write_matrices, const IndicatorArgs *
       HIP_OK(hipStreamSynchronize(c->stream));
       P.gR_nr = ind->nr;
       P.gR_C = C;
+      P.gR_mp = mp;
     }
   }
   const double *kap = fine ? c->kappa.p : f.kappa.p, *Zel = fine ? c->Zel.p : f.Zel.p;

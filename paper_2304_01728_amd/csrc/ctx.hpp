@@ -56,7 +56,7 @@ struct ElemPlan {
   // residual products' items (for gR_nr columns, chunks of gR_C)
   DevBuf<double2> X[4];
   DevBuf<GemmItem> gR;
-  int gR_nr = 0, gR_C = 0;
+  int gR_nr = 0, gR_C = 0, gR_mp = 0;
   // with shared classes (nel = their number, mp = m): the loads by pieces
   DevBuf<double2> LB[4], KL[4], wkK[4];
   DevBuf<int32_t> mlist;             // elements sorted by class
