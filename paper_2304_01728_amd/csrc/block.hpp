@@ -47,6 +47,11 @@ constexpr int kUnitCols = 7;
 constexpr int64_t kPartEntries = 32 << 20, kPartMost = 125000000;
 bool units_for(const HermSet &H, int nr);
 
+// The products of the blocks with nr local vectors each (the columns of a group
+// together, see HermGroup) on the matrix cores: yl = A xl.
+template <typename T>
+void launch_rows(HermSet &H, const cplx_t<T> *xl, cplx_t<T> *yl, int nr, hipStream_t s);
+
 // Y <- epilogue(sum_b R_b^T A_b R_b X) for nr columns (modes as herm_apply).
 // gathered: W already holds the local rows of X (a previous application
 // forwarded them).  fwd, fwd_bufs: a block set on the same vector and its
@@ -55,11 +60,6 @@ bool units_for(const HermSet &H, int nr);
 // may hold stale finite values from another width; they meet only the zero
 // padding of the tiles.  One column goes through herm_apply (the single-
 // vector local vectors of the sets).
-// The products of the blocks with nr local vectors each (the columns of a group
-// together, see HermGroup) on the matrix cores: yl = A xl.
-template <typename T>
-void launch_rows(HermSet &H, const cplx_t<T> *xl, cplx_t<T> *yl, int nr, hipStream_t s);
-
 template <typename T>
 void herm_apply_blk(HermSet &H, HermBlockBufs &W, const cplx_t<T> *X, cplx_t<T> *Y,
                     const cplx_t<T> *R, int mode, T theta, int nr, hipStream_t s,

@@ -465,12 +465,14 @@ __global__ __launch_bounds__(256) void k_strips(const cplx_t<T> *__restrict__ ti
 // interleaved: row i of block m at i gw + m): each pair of tiles is loaded once
 // for all of them, from a cache except for the first group of its class, and
 // every block gets the arithmetic of k_strips in the same order, so the partials
-// are bit for bit the same.  Half of the time is vector work (some 300 instructions
-// per pair of tiles and block, 256 of them the products, 1200 cycles of 2440 at the
-// 34 TFLOP/s of 24^3, p = 4); two waves per SIMD do not hide all of the wait for the
-// tiles, and four blocks (16 column sums and 16 x entries each) fill their 256
-// registers.  The next tile row's x comes through LDS, loaded a row ahead (one load
-// per block and row, waited for at its use, 68.6 -> 66.5 ms of a solve).
+// are bit for bit the same.  Bound by the vector units: at 24^3, p = 4 (36 TFLOP/s of
+// products, of 78.6) they issue in 81 % of the busy cycles of a compute unit, and a wave
+// waits for memory in 17 % of its time; the tiles come from L2 for 66 % of the requests
+// and from memory at 0.8 TB/s (counters).  Of some 300 instructions per pair of tiles and
+// block 256 are the products.  Four blocks (16 column sums and 16 x entries each) fill
+// the 256 registers of two waves per SIMD.  The next tile row's x comes through LDS,
+// loaded a row ahead (one load per block and row, waited for at its use, 68.6 -> 66.5 ms
+// of a solve).
 template <typename T>
 __global__ __launch_bounds__(256, 2) void k_strips_grp(const cplx_t<T> *__restrict__ tiles,
                                                        const int4 *__restrict__ units,
