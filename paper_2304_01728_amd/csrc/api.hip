@@ -2553,6 +2553,9 @@ int dpg_release_setup(dpg_ctx *c) {
       if (x) HIP_OK(hipStreamSynchronize(x));
     const bool rec = c->opt.flags & DPG_RECOMPUTE_PATCHES;   // the smoother needs the
                                                              // patch work areas
+    // from here on no other call may count on them, also when the load maps below do
+    // not fit the memory
+    c->released = true;
     for (LevelData &f : c->lv) {
       f.E.release();
       f.Mfull.release();
@@ -2596,7 +2599,6 @@ int dpg_release_setup(dpg_ctx *c) {
       P.nel = -1;
       P.gR_nr = 0;
     }
-    c->released = true;
     return DPG_OK;
   });
 }

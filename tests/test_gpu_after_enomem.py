@@ -1,0 +1,58 @@
+"""Calls after one that ended with DPG_ENOMEM under a memory budget: they are refused or
+give what they give on a context on which nothing failed, bit for bit.
+
+Each budget is taken from a context without one that goes through the same calls, so
+that the call named by the test, and nothing before it, passes it."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _D():
+    from paper_2304_01728_amd import dpgmg as D
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return D
+
+
+def _loads(n):
+    rng = np.random.default_rng(5)
+    return [dict(dir=d / np.linalg.norm(d), amp=1.0) for d in rng.standard_normal((n, 3))]
+
+
+def _ctx(D, N, p, c, loads, budget=0, **kw):
+    print(f"[after enomem] N={N} p={p} loads={len(loads)} budget={budget} {kw}", flush=True)
+    opt = D.dpg_default_options(nu_pre=2, nu_post=2, hbm_budget=budget, **kw)
+    ctx = D.dpg_setup(N, p, 2 * np.pi * N / 5, loads, c=c, options=opt)
+    D.dpg_assemble(ctx)
+    D.dpg_build_hierarchy(ctx)
+    return ctx
+
+
+def _resident(D, ctx):
+    return int(D.dpg_info(ctx).resident_bytes)
+
+
+def _refused(D, code, f, *a, **kw):
+    with pytest.raises(D.DPGError) as e:
+        f(*a, **kw)
+    assert e.value.code == code
+
+
+def test_setup_after_failed_release():
+    """The load maps do not fit: the work areas are gone all the same, and assembly and
+    hierarchy are refused (they ran on freed memory); solves go on."""
+    D = _D()
+    c = 1.0 + np.random.default_rng(1).random(8)
+    ctx = _ctx(D, 2, 2, c, _loads(1))
+    budget = _resident(D, ctx)
+    ctx.close()
+    ctx = _ctx(D, 2, 2, c, _loads(1), budget)
+    x = D.dpg_solve(ctx, tol=1e-10)[0]
+    _refused(D, D.DPG_ENOMEM, D.dpg_release_setup, ctx)
+    _refused(D, D.DPG_ESTATE, D.dpg_assemble, ctx)
+    _refused(D, D.DPG_ESTATE, D.dpg_build_hierarchy, ctx)
+    y = D.dpg_solve(ctx, tol=1e-10)[0]
+    ctx.close()
+    assert np.array_equal(x, y)
