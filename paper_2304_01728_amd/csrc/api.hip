@@ -332,6 +332,7 @@ void plan_elements(dpg_ctx *c, int nel, int nr) {
   const int64_t groups = (nel + NS * cmax - 1) / (NS * cmax);
   const int C = (int)std::max<int64_t>(1, (nel + NS * groups - 1) / (NS * groups));
   P.ns = NS;
+  P.mp = P.nel = -1;   // until everything is there: an allocation may fail
   Budget *bd = &c->bud;
   for (int k = 0; k < NS; ++k) {
     grow(P.G[k], (int64_t)C * nt * nt, bd);
@@ -398,6 +399,7 @@ void plan_load_pieces(dpg_ctx *c, const Classes &ec, int nr) {
   const int most = (int)std::max<int64_t>(1, std::min<int64_t>(62500000LL / ((int64_t)nt * nr), 65535));
   HIP_OK(hipStreamSynchronize(s));   // the items of earlier pieces may still be read
   P.pieces.clear();
+  P.pieces_nr = -1;   // until everything is there: an allocation may fail
   P.mlist.upload(mlist, bd, s);
   int cap = 0;
   for (int e0 = 0, k = 0; e0 < ec.n; e0 += C, ++k) {
@@ -619,6 +621,7 @@ void element_stage(dpg_ctx *c, int l, bool write_matrices, const IndicatorArgs *
     if (!fine || ind->nr < 1 || ind->nr > nr) throw DpgError(DPG_EINVAL, "bad indicator columns");
     for (int k = 0; k < P.ns; ++k) grow(P.X[k], (int64_t)C * m * ind->nr, &c->bud);
     if (P.gR_nr != ind->nr || P.gR_C != C || P.gR_mp != mp) {
+      P.gR_nr = 0;
       std::vector<GemmItem> gR(C);
       for (int i = 0; i < C; ++i)
         gR[i] = {(int64_t)i * nt * mp, (int64_t)i * m * ind->nr, (int64_t)i * nt * mp + (int64_t)m * nt,

@@ -1,8 +1,8 @@
 """Calls after one that ended with DPG_ENOMEM under a memory budget: they are refused or
 give what they give on a context on which nothing failed, bit for bit.
 
-Each budget is taken from a context without one that goes through the same calls, so
-that the call named by the test, and nothing before it, passes it."""
+Each budget is taken from a context with a very large one that goes through the same
+calls, so that the call named by the test, and nothing before it, passes it."""
 import numpy as np
 import pytest
 
@@ -21,7 +21,7 @@ def _loads(n):
     return [dict(dir=d / np.linalg.norm(d), amp=1.0) for d in rng.standard_normal((n, 3))]
 
 
-def _ctx(D, N, p, c, loads, budget=0, **kw):
+def _ctx(D, N, p, c, loads, budget=int(200e9), **kw):
     print(f"[after enomem] N={N} p={p} loads={len(loads)} budget={budget} {kw}", flush=True)
     opt = D.dpg_default_options(nu_pre=2, nu_post=2, hbm_budget=budget, **kw)
     ctx = D.dpg_setup(N, p, 2 * np.pi * N / 5, loads, c=c, options=opt)
@@ -56,3 +56,32 @@ def test_setup_after_failed_release():
     y = D.dpg_solve(ctx, tol=1e-10)[0]
     ctx.close()
     assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("shared", [False, True])
+def test_loads_after_failed_element_plan(shared):
+    """A load update with many loads that does not fit the element stage's work areas,
+    then one with as many loads as before: planned anew, not taken for the plan that the
+    failed one replaced.  Media of more than 512 kinds of elements, whose load updates go
+    through the element stage: all elements different, or half of them equal."""
+    D = _D()
+    N, p, many = 12, 1, 48
+    rng = np.random.default_rng(2)
+    c = 1.0 + rng.random(N ** 3)
+    if shared:
+        c[rng.random(N ** 3) < 0.5] = 1.0
+    one, other, more = _loads(1), _loads(3)[2:], _loads(many)
+    ctx = _ctx(D, N, p, c, one)
+    before = _resident(D, ctx)
+    D.dpg_load_rhs(ctx, more)
+    after = _resident(D, ctx)
+    want = D.dpg_load_rhs(ctx, other)
+    ctx.close()
+    # the work areas are the last allocations of the update
+    ctx = _ctx(D, N, p, c, one, after - 4096)
+    print(f"  resident {before}, with {many} loads {after}", flush=True)
+    _refused(D, D.DPG_ENOMEM, D.dpg_load_rhs, ctx, more)
+    got = D.dpg_load_rhs(ctx, other)
+    x, it, rr, code = D.dpg_solve(ctx, tol=1e-8)
+    ctx.close()
+    assert np.array_equal(got, want) and code == D.DPG_OK
