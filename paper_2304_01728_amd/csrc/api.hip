@@ -1303,6 +1303,7 @@ void smooth_recompute(dpg_ctx *c, int l, const double2 *x, double2 *y, const dou
   const hipStream_t s = c->stream;
   if (nr < 1 || nr > kMaxCols || (nr > 1 && nr > f.Sb.cap))
     throw DpgError(DPG_EINVAL, "bad column count");
+  if (c->ptmp.n < H.nloc * nr) throw DpgError(DPG_ENOMEM, "no room for the recomputed patches");
   double2 *xl = nr == 1 ? H.xl64.p : f.Sb.xl64.p, *yl = nr == 1 ? H.yl64.p : f.Sb.yl64.p;
   herm_gather_cols(H, x, xl, nr, s);
   for (PatchBatch &B : P.batches) {
@@ -1781,10 +1782,25 @@ template <> struct LBB<float> {
   static float2 *cc(LevelData &f) { return f.bc32.p; }
 };
 
+void drop_block(dpg_ctx *c) {
+  c->bcap = 0;
+  for (LevelData &f : c->lv) {
+    for (auto *v : {&f.br64, &f.bx64, &f.bres64, &f.brc64, &f.bec64, &f.bc64}) v->release();
+    for (auto *v : {&f.br32, &f.bx32, &f.bres32, &f.brc32, &f.bec32, &f.bc32}) v->release();
+    f.Mb.release();
+    f.Sb.release();
+  }
+  c->T0b.release();
+  for (auto *v : {&c->bb, &c->bx, &c->br, &c->bz, &c->bzo, &c->bp, &c->bq, &c->bsv, &c->bxf,
+                  &c->bcols, &c->bpart})
+    v->release();
+  if (c->opt.flags & DPG_RECOMPUTE_PATCHES)   // shared with the single-column solve
+    for (LevelData &f : c->lv) grow(c->ptmp, f.Sset.nloc, &c->bud);
+}
+
 // Block work vectors for nr columns on every level (same shapes as the
 // single-column ones, times nr).
-void ensure_block(dpg_ctx *c, int nr) {
-  if (nr <= c->bcap) return;
+void alloc_block(dpg_ctx *c, int nr) {
   const bool mixed = c->opt.precision == DPG_MIXED;
   Budget *bd = &c->bud;
   c->bpart.release();   // taken last, from what is left
@@ -1812,7 +1828,6 @@ void ensure_block(dpg_ctx *c, int nr) {
     f.Sb.ensure(f.Sset, nr, f.Sset.t64.p != nullptr || rec, f.Sset.t32.p != nullptr, bd,
                 c->stream);
     if (rec) grow(c->ptmp, f.Sset.nloc * nr, bd);
-    f.bcap = nr;
   }
   c->T0b.ensure(c->T0set, nr, c->T0set.t64.p != nullptr, c->T0set.t32.p != nullptr, bd,
                 c->stream);
@@ -1823,10 +1838,10 @@ void ensure_block(dpg_ctx *c, int nr) {
   c->bpartial.alloc(2LL * kColDotBlocks * kMaxCols, bd);
   c->bsc.alloc(8 * kMaxCols, bd);
   c->bact.alloc(kMaxCols, bd);
-  if (!c->host_bsc) {
+  if (!c->host_bsc)
     HIP_OK(hipHostMalloc((void **)&c->host_bsc, 8 * kMaxCols * sizeof(double), 0));
+  if (!c->host_bact)
     HIP_OK(hipHostMalloc((void **)&c->host_bact, kMaxCols * sizeof(int), 0));
-  }
   if (bd->limit <= 0) {
     int64_t need = 0;
     auto share = [&](const HermSet &H, HermBlockBufs &B) {
@@ -1846,6 +1861,18 @@ void ensure_block(dpg_ctx *c, int nr) {
     }
   }
   c->bcap = nr;
+}
+
+// The block vectors hold at least nr columns, or none (and the call has thrown).
+void ensure_block(dpg_ctx *c, int nr) {
+  if (nr <= c->bcap) return;
+  c->bcap = 0;
+  try {
+    alloc_block(c, nr);
+  } catch (...) {
+    drop_block(c);   // some have been replaced: the next call starts anew
+    throw;
+  }
 }
 
 // The smoother's patch sum on level l for nr columns: stored inverses, or

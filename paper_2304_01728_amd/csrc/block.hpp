@@ -23,6 +23,13 @@ struct HermBlockBufs {
   // local vectors zeroed when allocated: a forward (below) writes only the
   // rows a vector entry maps to
   void ensure(const HermSet &H, int nr, bool fp64, bool fp32, Budget *bud, hipStream_t s);
+  void release() {
+    cap = 0;
+    xl64.release();
+    yl64.release();
+    xl32.release();
+    yl32.release();
+  }
   // partials of launch_units_cols, the context's (null: not by units, see units_for)
   const DevBuf<double2> *part = nullptr;
 };

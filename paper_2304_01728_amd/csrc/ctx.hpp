@@ -160,8 +160,7 @@ struct LevelData {
   // mesh's traces; c = per-block condensation contributions of this level.
   DevBuf<double2> r64, x64, res64, rc64, ec64, c64;
   DevBuf<float2> r32, x32, res32, rc32, ec32, c32;
-  // the same for block (multi-right-hand-side) solves, bcap columns
-  int bcap = 0;
+  // the same for block (multi-right-hand-side) solves, dpg_ctx::bcap columns
   DevBuf<double2> br64, bx64, bres64, brc64, bec64, bc64;
   DevBuf<float2> br32, bx32, bres32, brc32, bec32, bc32;
   HermBlockBufs Mb, Sb;

@@ -85,3 +85,37 @@ def test_loads_after_failed_element_plan(shared):
     x, it, rr, code = D.dpg_solve(ctx, tol=1e-8)
     ctx.close()
     assert np.array_equal(got, want) and code == D.DPG_OK
+
+
+@pytest.mark.parametrize("flags,precision", [(0, "fp64"), (0, "mixed"), (8, "fp64")])
+def test_solves_after_a_block_solve_that_does_not_fit(flags, precision):
+    """32 columns that do not fit, in the middle of the block vectors: solves of one and two
+    columns, and a batch of two, go on as before (recomputed patches share a buffer between
+    block and single-column solves)."""
+    D = _D()
+    N, p = 4, 2
+    kw = dict(flags=flags, precision=D.DPG_MIXED if precision == "mixed" else D.DPG_FP64)
+    ctx = _ctx(D, N, p, None, _loads(1), **kw)
+    n = D.dpg_info(ctx).n_trace
+    rng = np.random.default_rng(8)
+    b = rng.standard_normal((32, n)) + 1j * rng.standard_normal((32, n))
+    x2 = D.dpg_solve(ctx, rhs=b[:2], nrhs=2, tol=1e-8)[0]
+    small = _resident(D, ctx)
+    D.dpg_solve(ctx, rhs=b, nrhs=32, tol=1e-8)
+    large = _resident(D, ctx)
+    ctx.close()
+    for budget in (small + (large - small) // 4, (small + large) // 2, large - 4096):
+        ctx = _ctx(D, N, p, None, _loads(1), budget, **kw)
+        x1 = D.dpg_solve(ctx, rhs=b[:1], nrhs=1, tol=1e-8)[0]
+        assert np.array_equal(D.dpg_solve(ctx, rhs=b[:2], nrhs=2, tol=1e-8)[0], x2)
+        _refused(D, D.DPG_ENOMEM, D.dpg_solve, ctx, rhs=b, nrhs=32, tol=1e-8)
+        assert np.array_equal(D.dpg_solve(ctx, rhs=b[:1], nrhs=1, tol=1e-8)[0], x1)
+        assert np.array_equal(D.dpg_solve(ctx, rhs=b[:2], nrhs=2, tol=1e-8)[0], x2)
+        _refused(D, D.DPG_ENOMEM, D.dpg_batch_open, ctx, 32)
+        _refused(D, D.DPG_ESTATE, D.dpg_batch_step, ctx, 1)
+        D.dpg_batch_open(ctx, 2)
+        assert D.dpg_batch_add(ctx, b[0], tol=1e-8) == 0
+        assert D.dpg_batch_step(ctx, 200) == [0]
+        y = D.dpg_batch_take(ctx, 0)[0]
+        assert np.linalg.norm(y - x1[0]) <= 1e-6 * np.linalg.norm(x1[0])
+        ctx.close()
