@@ -95,14 +95,20 @@ std::vector<std::pair<int, int>> level_plan(int N, int p, int p_min, int nlevels
   return plan;
 }
 
-void set_loads(dpg_ctx *c, const dpg_load *loads, int nrhs) {
-  c->nrhs = nrhs;
-  c->ld_h.assign(nrhs, LoadDesc{});
-  c->src_h.clear();
+struct LoadSet {
+  std::vector<LoadDesc> ld;
+  std::vector<double> src;
   std::vector<double2> u0;
+};
+
+// Throws for loads that cannot be taken, before anything of the context changes.
+LoadSet check_loads(const dpg_ctx *c, const dpg_load *loads, int nrhs) {
+  LoadSet L;
+  L.ld.assign(nrhs, LoadDesc{});
+  std::vector<double2> &u0 = L.u0;
   const int64_t nbp = boundary_points(c);
   for (int r = 0; r < nrhs; ++r) {
-    LoadDesc &d = c->ld_h[r];
+    LoadDesc &d = L.ld[r];
     d.u0_off = -1;
     if (loads[r].u0_qp) {
       d.u0_off = (int64_t)u0.size();
@@ -116,19 +122,29 @@ void set_loads(dpg_ctx *c, const dpg_load *loads, int nrhs) {
     for (int k = 0; k < 3; ++k) d.dir[k] = loads[r].dir[k];
     d.amp[0] = loads[r].amp[0];
     d.amp[1] = loads[r].amp[1];
-    d.src0 = (int)(c->src_h.size() / 6);
+    d.src0 = (int)(L.src.size() / 6);
     d.nsrc = loads[r].nsrc;
     if (d.nsrc < 0 || (d.nsrc > 0 && !loads[r].src)) throw DpgError(DPG_EINVAL, "bad source list");
-    for (int k = 0; k < 6 * d.nsrc; ++k) c->src_h.push_back(loads[r].src[k]);
+    for (int k = 0; k < 6 * d.nsrc; ++k) L.src.push_back(loads[r].src[k]);
     for (int k = 0; k < d.nsrc; ++k)
       if (!(loads[r].src[6 * k + 3] > 0.0)) throw DpgError(DPG_EINVAL, "source width must be > 0");
   }
-  c->ld.upload(c->ld_h, &c->bud, c->stream);
-  if (u0.empty()) c->u0q.release();
-  else c->u0q.upload(u0, &c->bud, c->stream);
+  return L;
+}
+
+// The context's loads; none of them while an upload fails.
+void set_loads(dpg_ctx *c, LoadSet L) {
+  c->nrhs = 0;
+  c->ld_h.clear();
+  c->ld.upload(L.ld, &c->bud, c->stream);
+  if (L.u0.empty()) c->u0q.release();
+  else c->u0q.upload(L.u0, &c->bud, c->stream);
+  c->src_h = std::move(L.src);
   if (c->src_h.empty()) c->src_h.push_back(0.0);
   c->src.upload(c->src_h, &c->bud, c->stream);
   HIP_OK(hipStreamSynchronize(c->stream));
+  c->ld_h = std::move(L.ld);
+  c->nrhs = (int)c->ld_h.size();
 }
 
 // Elements that a new set of loads needs.  Returns true (all elements) unless
@@ -889,6 +905,46 @@ void load_by_maps(dpg_ctx *c, const std::vector<int32_t> &list, const int32_t *l
   for (int r = 0; r < nr; ++r)
     launch_assemble_vec(f.num.n, c->asm_ptr.p, c->asm_ent.p, c->s_elem.p + (int64_t)r * nel * ntr,
                         0, c->s_asm.p + (int64_t)r * f.num.n, s);
+}
+
+// New loads for the operator, assembled.
+void update_loads(dpg_ctx *c, LoadSet L) {
+  LevelData &top = c->lv[c->L];
+  const int nrhs = (int)L.ld.size();
+  set_loads(c, std::move(L));
+  c->s_elem.ensure((int64_t)nrhs * top.nel * c->n_tr, &c->bud);
+  c->s_asm.ensure((int64_t)nrhs * top.num.n, &c->bud);
+  if (c->keep_recovery)
+    c->rec_Yb.ensure((int64_t)top.nel * c->n_field * c->nrhs, &c->bud);
+  std::vector<int32_t> list;
+  const bool everywhere = source_elements(c, list);
+  if (c->lm.state == 0) build_load_maps(c);
+  if (c->lm.state == 1) {
+    // the class maps: the load kernel and one product per element
+    const hipStream_t s = c->stream;
+    if (!everywhere) {
+      launch_zero(c->s_elem.n, c->s_elem.p, s);
+      if (c->keep_recovery) launch_zero(c->rec_Yb.n, c->rec_Yb.p, s);
+      grow(c->elist, std::max<int64_t>(1, (int64_t)list.size()), &c->bud);
+      if (!list.empty())
+        HIP_OK(hipMemcpyAsync(c->elist.p, list.data(), list.size() * sizeof(int32_t),
+                              hipMemcpyHostToDevice, s));
+    }
+    load_by_maps(c, list, c->elist.p, everywhere);
+  } else if (everywhere) {
+    element_stage(c, c->L, false);
+  } else {
+    // point sources only: the elements near a source carry the whole load
+    const hipStream_t s = c->stream;
+    launch_zero(c->s_elem.n, c->s_elem.p, s);
+    if (c->keep_recovery) launch_zero(c->rec_Yb.n, c->rec_Yb.p, s);
+    grow(c->elist, std::max<int64_t>(1, (int64_t)list.size()), &c->bud);
+    if (!list.empty())
+      HIP_OK(hipMemcpyAsync(c->elist.p, list.data(), list.size() * sizeof(int32_t),
+                            hipMemcpyHostToDevice, s));
+    HIP_OK(hipStreamSynchronize(s));
+    element_stage(c, c->L, false, nullptr, c->elist.p, (int)list.size());
+  }
 }
 
 // ---- hierarchy -------------------------------------------------------------------------
@@ -2333,7 +2389,7 @@ int dpg_setup(const dpg_mesh *mesh, int p, int dp, double omega, const dpg_mater
     if ((int)trial.size() != c->m) throw DpgError(DPG_EINVAL, "descriptor size mismatch");
     c->testd.upload(test, &c->bud, c->stream);
     c->triald.upload(trial, &c->bud, c->stream);
-    set_loads(c, loads, nrhs);
+    set_loads(c, check_loads(c, loads, nrhs));
     if (c->opt.p_min < 0 || c->opt.p_min > p)
       throw DpgError(DPG_EINVAL, "p_min must lie in [1, p] (0: no order levels)");
     const std::vector<std::pair<int, int>> plan =
@@ -2543,15 +2599,21 @@ int dpg_assemble(dpg_ctx *c) {
     if (c->released) throw DpgError(DPG_ESTATE, "setup data released");
     auto t0 = clk::now();
     LevelData &top = c->lv[c->L];
-    top.E.ensure((int64_t)top.ec.n * c->n_tr * c->n_tr, &c->bud);
-    c->s_elem.ensure(std::max<int64_t>(1, (int64_t)c->nrhs * top.nel * c->n_tr), &c->bud);
-    c->s_asm.ensure(std::max<int64_t>(1, (int64_t)c->nrhs * top.num.n), &c->bud);
-    if (c->keep_recovery) {
-      c->rec_L.ensure((int64_t)top.ec.n * c->n_field * c->n_field, &c->bud);
-      c->rec_Y.ensure((int64_t)top.ec.n * c->n_field * c->n_tr, &c->bud);
-      c->rec_Yb.ensure(std::max<int64_t>(1, (int64_t)top.nel * c->n_field * c->nrhs), &c->bud);
+    c->nrhs = (int)c->ld_h.size();
+    try {
+      top.E.ensure((int64_t)top.ec.n * c->n_tr * c->n_tr, &c->bud);
+      c->s_elem.ensure(std::max<int64_t>(1, (int64_t)c->nrhs * top.nel * c->n_tr), &c->bud);
+      c->s_asm.ensure(std::max<int64_t>(1, (int64_t)c->nrhs * top.num.n), &c->bud);
+      if (c->keep_recovery) {
+        c->rec_L.ensure((int64_t)top.ec.n * c->n_field * c->n_field, &c->bud);
+        c->rec_Y.ensure((int64_t)top.ec.n * c->n_field * c->n_tr, &c->bud);
+        c->rec_Yb.ensure(std::max<int64_t>(1, (int64_t)top.nel * c->n_field * c->nrhs), &c->bud);
+      }
+      element_stage(c, c->L, true);
+    } catch (const DpgError &e) {
+      if (e.code == DPG_ENOMEM) c->nrhs = 0;   // the loads may not be there
+      throw;
     }
-    element_stage(c, c->L, true);
     c->prof.flush();
     c->ms[1] = ms_since(t0);
     c->stage = 2;
@@ -2638,45 +2700,18 @@ int dpg_load_rhs(dpg_ctx *c, const dpg_load *loads, int nrhs, double *s_out) {
   return guarded(c, [&]() {
     if (c->stage < 2) throw DpgError(DPG_ESTATE, "dpg_assemble first");
     if (nrhs < 1 || !loads) throw DpgError(DPG_EINVAL, "need at least one load");
-    LevelData &top = c->lv[c->L];
-    set_loads(c, loads, nrhs);
-    c->s_elem.ensure((int64_t)nrhs * top.nel * c->n_tr, &c->bud);
-    c->s_asm.ensure((int64_t)nrhs * top.num.n, &c->bud);
-    if (c->keep_recovery)
-      c->rec_Yb.ensure((int64_t)top.nel * c->n_field * c->nrhs, &c->bud);
-    std::vector<int32_t> list;
-    const bool everywhere = source_elements(c, list);
-    if (c->lm.state == 0) build_load_maps(c);
-    if (c->lm.state == 1) {
-      // the class maps: the load kernel and one product per element
-      const hipStream_t s = c->stream;
-      if (!everywhere) {
-        launch_zero(c->s_elem.n, c->s_elem.p, s);
-        if (c->keep_recovery) launch_zero(c->rec_Yb.n, c->rec_Yb.p, s);
-        grow(c->elist, std::max<int64_t>(1, (int64_t)list.size()), &c->bud);
-        if (!list.empty())
-          HIP_OK(hipMemcpyAsync(c->elist.p, list.data(), list.size() * sizeof(int32_t),
-                                hipMemcpyHostToDevice, s));
-      }
-      load_by_maps(c, list, c->elist.p, everywhere);
-    } else if (everywhere) {
-      element_stage(c, c->L, false);
-    } else {
-      // point sources only: the elements near a source carry the whole load
-      const hipStream_t s = c->stream;
-      launch_zero(c->s_elem.n, c->s_elem.p, s);
-      if (c->keep_recovery) launch_zero(c->rec_Yb.n, c->rec_Yb.p, s);
-      grow(c->elist, std::max<int64_t>(1, (int64_t)list.size()), &c->bud);
-      if (!list.empty())
-        HIP_OK(hipMemcpyAsync(c->elist.p, list.data(), list.size() * sizeof(int32_t),
-                              hipMemcpyHostToDevice, s));
-      HIP_OK(hipStreamSynchronize(s));
-      element_stage(c, c->L, false, nullptr, c->elist.p, (int)list.size());
+    const int64_t nT = c->lv[c->L].num.n;
+    LoadSet L = check_loads(c, loads, nrhs);
+    try {
+      update_loads(c, std::move(L));
+    } catch (...) {
+      c->nrhs = 0;   // neither the loads before nor the new ones are there
+      throw;
     }
     c->prof.flush();
     if (s_out) {
       const bool dev = c->opt.flags & DPG_DEVICE_PTRS;
-      HIP_OK(hipMemcpyAsync(s_out, c->s_asm.p, (size_t)nrhs * top.num.n * 16,
+      HIP_OK(hipMemcpyAsync(s_out, c->s_asm.p, (size_t)nrhs * nT * 16,
                             dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, c->stream));
       HIP_OK(hipStreamSynchronize(c->stream));
     }

@@ -119,3 +119,42 @@ def test_solves_after_a_block_solve_that_does_not_fit(flags, precision):
         y = D.dpg_batch_take(ctx, 0)[0]
         assert np.linalg.norm(y - x1[0]) <= 1e-6 * np.linalg.norm(x1[0])
         ctx.close()
+
+
+def test_solves_after_a_load_update_that_failed():
+    """Refused loads (a source of no width) leave the loads before in place, with their
+    number; loads that do not fit leave none, and the next update goes on as on a context
+    on which nothing failed."""
+    D = _D()
+    N, p = 6, 2
+    one, other, more = _loads(1), _loads(3)[2:], _loads(256)
+    bad = more[:7] + [dict(amp=0.0, sources=[[0.5, 0.5, 0.5, 0.0, 1.0, 0.0]])]
+    ctx = _ctx(D, N, p, None, one)
+    x = D.dpg_solve(ctx, tol=1e-8)[0]
+    want = D.dpg_load_rhs(ctx, other)
+    y = D.dpg_solve(ctx, tol=1e-8)[0]
+    small = _resident(D, ctx)
+    D.dpg_load_rhs(ctx, more)
+    large = _resident(D, ctx)
+    ctx.close()
+    through = 0
+    for budget in (small + 4096, (small + large) // 2, large - 4096):
+        ctx = _ctx(D, N, p, None, one, budget)
+        _refused(D, D.DPG_EINVAL, D.dpg_load_rhs, ctx, bad)
+        _refused(D, D.DPG_EINVAL, D.dpg_solve, ctx, nrhs=8, tol=1e-8)
+        assert np.array_equal(D.dpg_solve(ctx, tol=1e-8)[0], x)
+        try:
+            D.dpg_load_rhs(ctx, other)   # builds the class maps, whose work areas may not fit
+        except D.DPGError as e:
+            assert e.code == D.DPG_ENOMEM
+            ctx.close()
+            continue
+        _refused(D, D.DPG_ENOMEM, D.dpg_load_rhs, ctx, more)
+        for call, kw in ((D.dpg_solve, dict(nrhs=1)), (D.dpg_solve_noalloc, dict(nrhs=1))):
+            _refused(D, D.DPG_EINVAL, call, ctx, tol=1e-8, **kw)
+        _refused(D, D.DPG_EINVAL, D.dpg_get_fields, ctx, x)
+        assert np.array_equal(D.dpg_load_rhs(ctx, other), want)
+        assert np.array_equal(D.dpg_solve(ctx, tol=1e-8)[0], y)
+        ctx.close()
+        through += 1
+    assert through >= 1
