@@ -2030,6 +2030,18 @@ void batch_close(dpg_ctx *c) {
   S.done.clear();   // finished slots not taken (dpg_solve's block path takes none)
 }
 
+// The rows of the local vectors past a block's size, which nobody writes, are those of
+// other columns in another width.  They may hold anything finite (it meets zeros of the
+// tiles), so once a column has not been finite they are cleared at every change.
+void clear_local(dpg_ctx *c) {
+  const hipStream_t s = c->stream;
+  for (LevelData &f : c->lv)
+    for (HermBlockBufs *B : {&f.Mb, &f.Sb}) {
+      if (B->xl64.n > 0) launch_zero(B->xl64.n, B->xl64.p, s);
+      if (B->xl32.n > 0) launch_zero(B->xl32.n, B->xl32.p, s);
+    }
+}
+
 void batch_open(dpg_ctx *c, int max_slots) {
   if (max_slots < 1 || max_slots > kMaxCols)
     throw DpgError(DPG_EINVAL, "a batch holds 1 to 32 columns");
@@ -2041,6 +2053,9 @@ void batch_open(dpg_ctx *c, int max_slots) {
   for (auto *v : {&c->bx, &c->br, &c->bp, &c->bz, &c->bzo}) launch_zero(top.nM * max_slots, v->p, s);
   launch_zero(top.num.n * max_slots, c->bsv.p, s);
   launch_zero(4 * kMaxCols, reinterpret_cast<double2 *>(c->bsc.p), s);
+  if (c->nonfinite) clear_local(c);
+  c->nonfinite = false;   // the columns are new
+  S.lw = 0;
   for (int k = 0; k < kMaxCols; ++k) {
     S.state[k] = 0;
     S.iters[k] = 0;
@@ -2131,6 +2146,8 @@ void batch_step(dpg_ctx *c, int max_iters) {
       S.act_dirty = false;
     }
     const int w = S.w;
+    if (S.lw != w && c->nonfinite) clear_local(c);
+    S.lw = w;
     auto part_a = [&]() {
       herm_apply_blk<double>(top.Mset, top.Mb, c->bp.p, c->bq.p, nullptr, RED_SET, 1.0, w, s);
       PROF(DPG_K_CG, 0);
@@ -2170,6 +2187,7 @@ void batch_step(dpg_ctx *c, int max_iters) {
       const double rr = std::sqrt(Sc[4 * kMaxCols + k] / S.bb[k]);
       if (Sc[6 * kMaxCols + k] != 0.0 || !std::isfinite(rr)) {
         S.state[k] = 4;                      // breakdown (p^H M p <= 0 or not finite)
+        c->nonfinite = true;
       } else {
         S.rr[k] = rr;
         if (rr <= S.tol[k]) S.state[k] = 2;

@@ -64,8 +64,8 @@ void launch_rows(HermSet &H, const cplx_t<T> *xl, cplx_t<T> *yl, int nr, hipStre
 // forwarded them).  fwd, fwd_bufs: a block set on the same vector and its
 // buffers, whose local vectors receive the new Y for an application of fwd
 // to Y that follows with gathered = true.  Rows of a block past its size
-// may hold stale finite values from another width; they meet only the zero
-// padding of the tiles.  One column goes through herm_apply (the single-
+// may hold stale finite values from another width (the caller clears what is not
+// finite); they meet only the zero padding of the tiles.  One column goes through herm_apply (the single-
 // vector local vectors of the sets).
 template <typename T>
 void herm_apply_blk(HermSet &H, HermBlockBufs &W, const cplx_t<T> *X, cplx_t<T> *Y,

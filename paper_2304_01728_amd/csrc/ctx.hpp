@@ -196,6 +196,7 @@ struct BatchSession {
   std::vector<int> done;             // finished slots not taken yet, in finishing order
   std::unique_ptr<GraphSet> graphs;  // captured for width gw
   int gw = 0;
+  int lw = 0;                        // width of the last iteration
 };
 
 }  // namespace dpg
@@ -268,6 +269,7 @@ struct dpg_ctx {
   double *host_bsc = nullptr;        // pinned, 8 x kMaxCols
   int *host_bact = nullptr;          // pinned, kMaxCols
   dpg::BatchSession bs;
+  bool nonfinite = false;            // a column of a block solve ended in a breakdown
   double ms[4] = {0, 0, 0, 0};
   dpg::Prof prof;
 };

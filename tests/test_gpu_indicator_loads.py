@@ -11,6 +11,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("first,then", [(3, 1), (1, 3)])
 def test_indicator_after_other_number_of_loads(first, then):
     from paper_2304_01728_amd import dpgmg as D
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
     N, p = 4, 2
     rng = np.random.default_rng(3)
     c = 1.0 + rng.random(N ** 3)
