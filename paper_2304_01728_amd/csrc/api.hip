@@ -2764,7 +2764,14 @@ int dpg_solve(dpg_ctx *c, const double *rhs, int nrhs, double tol, double *x_out
         }
         std::vector<int32_t> it(nr);
         std::vector<double> rr(nr);
-        const int st = solve_block(c, sv, nr, tol, c->bcols.p, it.data(), rr.data());
+        int st;
+        try {
+          st = solve_block(c, sv, nr, tol, c->bcols.p, it.data(), rr.data());
+        } catch (...) {
+          (void)hipStreamSynchronize(c->stream);
+          batch_close(c);   // the batch is this call's own
+          throw;
+        }
         if (st != DPG_OK) status = st;
         for (int k = 0; k < nr; ++k) {
           if (iters_out) iters_out[k0 + k] = it[k];

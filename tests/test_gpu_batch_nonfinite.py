@@ -47,3 +47,30 @@ def test_nonfinite_column_stays_alone(medium, nu):
         for x, it, code in (got[k], again[k], (alone[0][k], int(alone[1][k]), alone[3])):
             assert code == D.DPG_OK and abs(it - want[k][1]) <= 1
             assert np.linalg.norm(x - want[k][0]) <= 1e-8 * np.linalg.norm(want[k][0])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_block_solves_after_one_that_failed(precision):
+    """A block solve that is refused (NaN) or breaks down leaves no batch open, and the
+    next one gives what it gave before, bit for bit."""
+    from paper_2304_01728_amd import dpgmg as D
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    N, p = 4, 2
+    print(f"[nonfinite] N={N} p={p} {precision}", flush=True)
+    opt = D.dpg_default_options(precision=D.DPG_MIXED if precision == "mixed" else D.DPG_FP64)
+    ctx = D.dpg_setup(N, p, 2 * np.pi, [dict(dir=[0, 0.6, 0.8], amp=1.0)], options=opt)
+    D.dpg_assemble(ctx)
+    D.dpg_build_hierarchy(ctx)
+    n = D.dpg_info(ctx).n_trace
+    rng = np.random.default_rng(6)
+    b = rng.standard_normal((3, n)) + 1j * rng.standard_normal((3, n))
+    x = D.dpg_solve(ctx, rhs=b, nrhs=3, tol=1e-8)[0]
+    for scale in [np.nan] + [1e60] * (precision == "mixed"):
+        bad = b.copy()
+        bad[1] *= scale
+        with pytest.raises(D.DPGError) as e:
+            D.dpg_solve(ctx, rhs=bad, nrhs=3, tol=1e-8)
+        assert e.value.code == (D.DPG_EBREAKDOWN if np.isfinite(scale) else D.DPG_EINVAL)
+        assert np.array_equal(D.dpg_solve(ctx, rhs=b, nrhs=3, tol=1e-8)[0], x)
+    ctx.close()
