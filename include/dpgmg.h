@@ -196,7 +196,9 @@ int dpg_build_hierarchy(dpg_ctx *ctx);
  * (the others get zero loads).  With more classes (a wave speed that varies
  * from element to element) every update runs the element chain of
  * dpg_assemble again on those elements.  Output: the condensed trace loads,
- * n_trace x nrhs, if s_out is not NULL. */
+ * n_trace x nrhs, if s_out is not NULL.  Loads that are refused (DPG_EINVAL)
+ * leave those before in place; after DPG_ENOMEM the context has none until a
+ * call has gone through. */
 int dpg_load_rhs(dpg_ctx *ctx, const dpg_load *loads, int nrhs, double *s_out);
 
 /* Frees what only dpg_assemble and dpg_build_hierarchy use: the element and
@@ -207,7 +209,8 @@ int dpg_load_rhs(dpg_ctx *ctx, const dpg_load *loads, int nrhs, double *s_out);
  * working; dpg_assemble, dpg_build_hierarchy and the exports of the freed
  * matrices return DPG_ESTATE afterwards.  For callers that keep many
  * hierarchies resident (a solve server).  Requires a built hierarchy
- * (DPG_ESTATE otherwise). */
+ * (DPG_ESTATE otherwise).  DPG_ENOMEM when the load maps do not fit: the rest is
+ * freed all the same, and dpg_load_rhs tries to form them again. */
 int dpg_release_setup(dpg_ctx *ctx);
 
 /* Solves T x = rhs for nrhs right-hand sides (rhs: n_trace x nrhs trace
